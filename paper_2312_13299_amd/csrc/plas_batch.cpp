@@ -465,6 +465,10 @@ class BatchRun {
     run_list_.clear();
     for (const Sort& s : sorts_)
       if (s.running) run_list_.push_back(s.slot);
+    // Largest sides first: blocks start in map order, and the longest lines
+    // started last would leave the chip to themselves at a launch's end.
+    std::stable_sort(run_list_.begin(), run_list_.end(),
+                     [&](int a, int c) { return sorts_[a].w > sorts_[c].w; });
     const size_t nslots = sorts_.size();
     size_t off = align_up(nslots * sizeof(plas::BatchGrid));
     const size_t o_list = off;

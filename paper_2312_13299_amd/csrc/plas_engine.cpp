@@ -81,8 +81,7 @@ int32_t plas_create(plas_handle* out, int32_t device) {
     delete h;
     return PLAS_ERR_HIP;
   }
-  bool ok = hipHostMalloc(reinterpret_cast<void**>(&h->status_host), sizeof(HostStatus)) == hipSuccess &&
-            hipHostMalloc(reinterpret_cast<void**>(&h->range_host), (2 * 64 + 1) * sizeof(float)) == hipSuccess &&
+  bool ok = hipHostMalloc(reinterpret_cast<void**>(&h->range_host), (2 * 64 + 1) * sizeof(float)) == hipSuccess &&
             hipHostMalloc(reinterpret_cast<void**>(&h->u64_host), 16 * sizeof(unsigned long long)) == hipSuccess &&
             hipHostMalloc(reinterpret_cast<void**>(&h->state_host), sizeof(DevState)) == hipSuccess &&
             reserve(h->state, sizeof(DevState)) == hipSuccess &&
@@ -113,7 +112,6 @@ int32_t plas_destroy(plas_handle h) {
                           &h->range_part, &h->range_out, &h->levels, &h->trace, &h->state,
                           &h->stage_state, &h->scratch, &h->vad};
   for (DeviceBuffer* b : bufs) release(*b);
-  if (h->status_host) (void)hipHostFree(h->status_host);
   if (h->range_host) (void)hipHostFree(h->range_host);
   if (h->u64_host) (void)hipHostFree(h->u64_host);
   if (h->state_host) (void)hipHostFree(h->state_host);
@@ -245,11 +243,10 @@ int32_t plas_sort(plas_handle h, const void* features, int64_t n, int32_t d, int
     }
     const int64_t first_slot = slots;
     slots += chunk;
-    PLAS_HIP(h, hipMemcpyAsync(h->status_host, &Sd->done, sizeof(int32_t), hipMemcpyDeviceToHost, h->stream));
-    PLAS_HIP(h, hipMemcpyAsync(&h->status_host->k, &Sd->k, sizeof(int64_t), hipMemcpyDeviceToHost, h->stream));
+    PLAS_HIP(h, hipMemcpyAsync(S, Sd, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
     PLAS_HIP(h, hipStreamSynchronize(h->stream));
-    const bool done = h->status_host->done != 0;
-    const int64_t k_now = h->status_host->k;
+    const bool done = S->done != 0;
+    const int64_t k_now = S->k;
     if (profile) {
       // Slots at or after the end of the sort returned at once.
       const int64_t ran = done ? std::max<int64_t>(0, std::min<int64_t>(chunk, k_now - k0 - first_slot)) : chunk;
@@ -273,7 +270,6 @@ int32_t plas_sort(plas_handle h, const void* features, int64_t n, int32_t d, int
 
   PLAS_HIP(h, hipMemcpyAsync(perm_out, P, static_cast<size_t>(n) * sizeof(int32_t), hipMemcpyDeviceToDevice,
                              h->stream));
-  PLAS_HIP(h, hipMemcpyAsync(S, Sd, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
   PLAS_HIP(h, hipStreamSynchronize(h->stream));
   if (stats != nullptr) {
     stats->levels = S->levels_run;

@@ -62,7 +62,6 @@ struct plas_context {
   plas_host::DeviceBuffer vad;                     // VAD partial sums and results
   void* noalloc = nullptr;                         // the device's scratch of plas_grid_energy_noalloc
   // Pinned host memory for small read-backs.
-  HostStatus* status_host = nullptr;
   float* range_host = nullptr;
   unsigned long long* u64_host = nullptr;
   DevState* state_host = nullptr;

@@ -37,9 +37,6 @@ constexpr int kRangeBlocks = 256;
 #ifndef PLAS_ASSIGN_MAX_BLOCKS
 #define PLAS_ASSIGN_MAX_BLOCKS 4096
 #endif
-// Waves per block of the staged blur (each wave walks one group of 64/dp
-// lines): two-wave blocks of 48 KB LDS let three blocks share a CU.
-constexpr int kBlurWavesPerBlock = 2;
 constexpr int kMaxGridBlocks = 4096;
 
 inline int blocks_for(int64_t threads, int64_t cap = kMaxGridBlocks) {
@@ -460,44 +457,13 @@ __global__ __launch_bounds__(kBlock) void k_blur(const S* __restrict__ in, S* __
   if (table != nullptr) fill_group_table<kBlock>(table, st->beta, st->keys, blockIdx.x, gridDim.x);
 }
 
-// Cache hints, measured on whole sorts. The assignment reads every cell of G
+// Cache hint, measured on whole sorts. The assignment reads every cell of G
 // and T once per reorder, in random group order: streaming (non-temporal)
 // loads keep those reads from evicting what the next blur pass reads (1024^2
-// float32 with normal loads: assignment 109 -> 132 us). The staged blur
-// stores its lines normally where the grid is about the size of the 256 MB
-// Infinity Cache (the 128-row ring: 1024^2 float32 and 1448^2 bfloat16
-// grids), as the next kernel reads them soon after: streaming stores made
-// those sorts 3.7 % and 1.4 % slower. float32 grids of more than 1024 lines
-// (the 64-row ring) are twice that size or more; there streaming stores are
-// faster (1448^2: 5568 against 5668 ms; 2091^2: 15.5 against 16.3 s).
-template <int RR>
-constexpr bool blur_stream_stores() {
-  return RR < 128;
-}
+// float32 with normal loads: assignment 109 -> 132 us).
 constexpr bool kAssignStreamLoads = true;
 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-
-// 16-byte load / store with a streaming hint (the data is not used again
-// from the cache) when `nt`.
-template <bool nt>
-__device__ __forceinline__ uint4 load16(const void* p) {
-  if constexpr (nt) {
-    const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-  } else {
-    return *reinterpret_cast<const uint4*>(p);
-  }
-}
-template <bool nt>
-__device__ __forceinline__ void store16(void* p, uint4 v) {
-  if constexpr (nt) {
-    u32x4_t u = {v.x, v.y, v.z, v.w};
-    __builtin_nontemporal_store(u, reinterpret_cast<u32x4_t*>(p));
-  } else {
-    *reinterpret_cast<uint4*>(p) = v;
-  }
-}
 
 typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 
@@ -515,114 +481,73 @@ __device__ __forceinline__ Q load_quad(const Q* p) {
   }
 }
 
-// Blur pass for cells of at least 16 bytes, staged through LDS. Same
-// arithmetic as k_blur (one running sum per line and channel, same operation
-// order); the memory side is built on gfx950's direct global -> LDS loads.
+// Blur pass for cells of at least 16 bytes: same arithmetic as k_blur (one
+// running sum per line and channel, same operation order), with the work of a
+// group of 64 / DP lines split over three waves of a block that meet at a
+// barrier once per chunk of 16 positions:
 //
-// A wave walks 64 / DP lines side by side (DP = 64: one line). LDS row p holds
-// one position of all of them: element l * DP + c is channel c of line l, and
-// lane l * DP + c runs that chain. A load instruction fills kPos consecutive
-// rows (1 KB): load lane (q, j) moves the 16-byte piece j of position q, piece
-// j belonging to line j / kPiecesPerCell, and the data goes straight to LDS
-// without passing through registers, so several chunks can be in flight per
-// wave. Outputs are summed into LDS rows and leave as 16-byte stores (cache
-// hints: blur_stream_stores).
+//  - the loading wave moves 16-byte pieces from global memory straight to an
+//    LDS ring (gfx950's direct loads: the data never passes through
+//    registers). A ring row holds one position of all the group's lines
+//    (element l * DP + c is channel c of line l). It does nothing else, so its
+//    waits never hold up the sums, and it runs kDepth chunks ahead of them;
+//  - the summing wave runs the chains, lane l * DP + c that of channel c of
+//    line l: per position one addition, one subtraction and one LDS write of
+//    the sum. It reads a step's values during the step before, because an LDS
+//    read beside the direct loads' writes takes hundreds of cycles;
+//  - the storing wave multiplies the sums of the step before by 1 / count and
+//    stores them as 16-byte pieces.
 //
-// Chunks are kChunk positions aligned to multiples of kChunk (a row walk then
-// reads and writes whole aligned 4 KB blocks). The line is loaded chunk by
-// chunk into a ring of rows (row = position modulo the ring). Step e takes
-// chunk e: first its positions up to min(r, w - 1) go into the starting sum,
-// then, from step A = ceil(r / kChunk) on, the outputs x of chunk e - A (x + r
-// lies in chunk e or e - 1). While the ring also holds every leaving position
-// x - r - 1 still to come beside the chunks in flight, leaving values are read
-// back from it; otherwise the ring is split in two halves and the leaving
-// chunks reach the upper half from KR register slots, where each chunk was
-// kept since it entered (float32 over large working sets: 24 slots with the
-// 128-row ring, 48 <= r <= 192; 8 with the 64-row ring, 16 <= r <= 64), or
-// from a second load stream (the same positions again).
+// What bounds it: with few lines (small or narrow grids) the serial chain,
+// about 41 cycles per position; with many, memory. One wave that did all three
+// in turn took 135 cycles per position, waiting for its own LDS round trips:
+// 512^2 x 4 float32 33 -> 12 us per pass (r = 1; 42 -> 22 us at r = 255), 700^2
+// x 16 float32 45 -> 18 us, 300^2 x 64 float32 23 -> 12 us, 724^2 x 64 bfloat16
+// 57 -> 26 us, 2091^2 x 64 float32 641 -> 455 us (r = 20). Two waves (the sums
+// stored by the summing wave) reached 15 us on the first of these.
+//
+// Steps walk t = 0 .. w - 1 + r. Every t < w adds value t to the sum (up to t
+// = r that is the starting sum, from then on the entering value of output
+// x = t - r), every t >= 2r + 1 subtracts value t - 2r - 1 (the leaving value
+// of x), and every t >= r gives output x. So the values a step adds are
+// exactly one loaded chunk. While the ring holds the leaving values beside
+// the chunks in flight they are read back from it; otherwise its second half
+// holds leaving chunks, loaded a second time (the same positions, cut so that
+// a step's leaving values are exactly one chunk).
+//
 // Loads are issued at positions clamped into the line (a clamped load fetches
-// a value the sums never use), so every chunk is exactly kVec load
-// instructions.
-//
-// Waits. Vector memory operations of a wave complete in issue order, so
-// "chunk c has arrived" is "at most n operations are outstanding", n being the
-// number of loads and stores issued after chunk c's last load. Every step
-// issues, in this order, the stores of the chunk it summed and then the loads
-// of issue slot e + kDepth - 1 (entering chunk, then leaving chunk); n follows
-// from that schedule (ops_after). The loads are written as asm so that the
-// compiler does not add its own conservative wait (every load done) before
-// each LDS read; M0 (the LDS base of a load) is set in the same asm statement,
-// and no compiler-generated code of these kernels uses M0.
-template <typename S, int RR, int KR = 0>
-struct RingShape {
-  static constexpr int kRowBytes = 64 * static_cast<int>(sizeof(S));  // one position of the wave's lines
+// a value the sums never use), so every chunk is exactly kVec instructions.
+// Vector memory operations of a wave complete in issue order, so "slot u has
+// arrived" is "at most as many operations are outstanding as were issued
+// after slot u". The loads are written as asm so that the compiler does not
+// add its own wait for all of them; M0 (the LDS base of a load) is set in the
+// same asm statement, and no compiler-generated code of these kernels uses M0.
+constexpr int kRelayRows = 128;  // ring rows
+constexpr int kRelayWaves = 3;   // waves per line group
+template <typename S>
+struct RelayShape {
+  static constexpr int kRowBytes = 64 * static_cast<int>(sizeof(S));  // one position of the group's lines
   static constexpr int kLanesPerRow = kRowBytes / 16;
   static constexpr int kPos = 64 / kLanesPerRow;  // positions per load instruction: 4 (float32), 8 (bfloat16)
   static constexpr int kChunk = 16;               // positions per chunk
   static constexpr int kVec = kChunk / kPos;      // load instructions per chunk
-#ifndef PLAS_BLUR_DEPTH
-#define PLAS_BLUR_DEPTH 3
-#endif
-#ifndef PLAS_BLUR_EARLY
-#define PLAS_BLUR_EARLY 0
-#endif
-  // issue slots in flight, the one being summed included (two with the
-  // small ring, whose split halves hold two chunks)
-  static constexpr int kDepth = RR >= 128 ? PLAS_BLUR_DEPTH : 2;
-  static constexpr bool kEarly = PLAS_BLUR_EARLY;  // a step issues its loads before summing (else after)
-  static constexpr int kRingRows = RR;
-  static constexpr int kSlots = kRingRows / kChunk;
-  static constexpr int kRegChunks = KR;  // register slots of leaving chunks (0: none)
-  static constexpr int kRegWords = kChunk * static_cast<int>(sizeof(S)) / 4;  // registers per chunk
-  static constexpr int kHalfRows = kRingRows / 2;  // rows of each stream when the ring is split
-  static_assert(kRingRows % kChunk == 0 && (kRingRows & (kRingRows - 1)) == 0, "ring shape");
-  static_assert(KR == 0 || sizeof(S) == 4, "register slots hold float32 chunks");
-  static_assert(kHalfRows / kChunk >= kDepth + (kEarly ? 1 : 0), "a split half holds the chunks in use and in flight");
+  static constexpr int kSlots = kRelayRows / kChunk;      // chunks of the whole ring
+  static constexpr int kHalf = kSlots / 2;        // chunks of each region of the split ring
+  // Chunks the loads run ahead of the sums.
+  static constexpr int kDepth = kHalf;
+  static_assert(kRelayRows % kChunk == 0 && kDepth >= 2, "ring shape");
+  static_assert(2 * kVec * (kDepth - 2) < 64, "loads in flight fit the wait counter");
 };
 
-// LDS of one wave: (RR + 16) rows of 256 B (float32) or 128 B (bfloat16),
-// 36 KB / 18 KB with the 128-row ring.
-template <typename S, int RR>
-struct alignas(16) RingLds {
-  S ring[RingShape<S, RR>::kRingRows][64];
-  S out[RingShape<S, RR>::kChunk][64];
+// LDS of one line group: the ring, and the sums of two steps (40 KB float32,
+// 24 KB bfloat16: four float32 groups share a CU).
+template <typename S>
+struct alignas(16) RelayLds {
+  S ring[kRelayRows][64];
+  float sums[2 * RelayShape<S>::kChunk][64];
 };
 
-// Leaving values come from the entering ring when, at every step, the chunk
-// issued then does not overwrite a leaving position still to come: with A =
-// ceil(r / kChunk) chunks between a step's chunk and its outputs and
-// ceil((r + 1) / kChunk) between an output chunk and its leaving positions,
-// A + ceil((r + 1) / kChunk) <= kSlots + 1 - kDepth.
-template <typename S, int RR>
-__device__ __forceinline__ bool ring_leave(int r) {
-  using Sh = RingShape<S, RR>;
-  const int a = (r + Sh::kChunk - 1) / Sh::kChunk;
-  const int b = (r + Sh::kChunk) / Sh::kChunk;
-  return a + b <= Sh::kSlots + (Sh::kEarly ? 0 : 1) - Sh::kDepth;
-}
-
-// One direct load: 16 bytes per lane from `src` to LDS byte address
-// m0 + 16 * lane, with a streaming hint (the data is not read again through
-// the cache) when `nt`. A preceding LDS read of the rows it overwrites must
-// have completed: lgkmcnt(0) first.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"  // M0 is named as clobbered on purpose
-template <bool nt>
-__device__ __forceinline__ void dma16(const void* src, uint32_t m0) {
-  if constexpr (nt)
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
-                 :
-                 : "v"(src), "s"(m0)
-                 : "memory", "m0");
-  else
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :
-                 : "v"(src), "s"(m0)
-                 : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-// Cache hints of the two load streams. The leaving stream (a second read of
+// Cache hints of the load streams. The leaving stream (a second read of
 // positions the entering stream read 2r + 1 positions earlier) streams
 // through, so that it does not evict entering data the L2 still holds for
 // it. The entering stream streams in the column pass when the grids in
@@ -634,12 +559,478 @@ __device__ __forceinline__ void dma16(const void* src, uint32_t m0) {
 // holds whole ran 1-2 % slower with streaming column loads.
 constexpr bool kBlurLeaveStream = true;
 
-// s_waitcnt vmcnt(n) for a run-time n (rounded down, which only waits
-// longer).
+// One direct load: 16 bytes per lane from `src` to LDS byte address
+// m0 + 16 * lane, with a streaming hint (the data is not read again through
+// the cache) when `nt`.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // M0 is named as clobbered on purpose
+template <bool nt>
+__device__ __forceinline__ void dma16_load(const void* src, uint32_t m0) {
+  if constexpr (nt)
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
+                 :
+                 : "v"(src), "s"(m0)
+                 : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :
+                 : "v"(src), "s"(m0)
+                 : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
 template <int N>
 __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
+
+// s_waitcnt vmcnt(n) for n = chunks * VEC loads, n uniform.
+template <int VEC, int MAXC>
+__device__ __forceinline__ void wait_chunks(int chunks) {
+  if constexpr (MAXC == 0) {
+    wait_vm<0>();
+  } else {
+    if (chunks >= MAXC)
+      wait_vm<VEC * MAXC>();
+    else
+      wait_chunks<VEC, MAXC - 1>(chunks);
+  }
+}
+
+// All of this wave's LDS accesses done, then the block's barrier.
+__device__ __forceinline__ void relay_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
+
+// One chunk's stored values of a lane, widened where they are used (not where
+// they are read: that would wait for the reads).
+template <typename S>
+struct ChunkValues;
+template <>
+struct ChunkValues<float> {
+  float v[16];
+  __device__ __forceinline__ void set(int i, float x) { v[i] = x; }
+  __device__ __forceinline__ float get(int i) const { return v[i]; }
+};
+
+template <>
+struct ChunkValues<uint16_t> {
+  uint32_t v[16];
+  __device__ __forceinline__ void set(int i, uint16_t x) { v[i] = x; }
+  __device__ __forceinline__ float get(int i) const { return bf16_to_float(v[i]); }
+};
+
+template <typename S, int DP>
+struct RelayLine {
+  using Sh = RelayShape<S>;
+  static constexpr int kChunk = Sh::kChunk;
+  static constexpr int kPiecesPerCell = DP * static_cast<int>(sizeof(S)) / 16;
+  static_assert(kPiecesPerCell >= 1, "a cell must hold at least one 16-byte piece");
+  int w, r;
+  int n_chunks;  // chunks of the line
+  int n_steps;   // chunks of t = 0 .. w - 1 + r
+  bool split;    // the leaving values have their own region (the ring's second half)
+  bool stream;   // the entering loads stream
+  int lane;
+  S (*ring)[64];
+  float (*sums)[64];
+
+  __device__ __forceinline__ void init(int w_, int r_, bool stream_, int lane_, RelayLds<S>& lds) {
+    w = w_;
+    r = r_;
+    lane = lane_;
+    stream = stream_;
+    ring = lds.ring;
+    sums = lds.sums;
+    n_chunks = (w + kChunk - 1) / kChunk;
+    n_steps = (w + r + kChunk - 1) / kChunk;
+    split = (2 * r + kChunk) / kChunk > Sh::kSlots - Sh::kDepth;  // ceil((2r + 1) / kChunk)
+  }
+
+  // ---- loading wave
+
+  // kVec loads of positions pos0 .. pos0 + kChunk - 1 (clamped into the
+  // line) into slot `slot`. p0: this lane's piece at position 0; step:
+  // elements between positions.
+  template <bool nt>
+  __device__ __forceinline__ void load_chunk(const S* p0, int64_t step, int pos0, int slot, uint32_t ring_m0) const {
+    const int q = lane / Sh::kLanesPerRow;
+    const uint32_t m0 = ring_m0 + static_cast<uint32_t>(slot * kChunk * Sh::kRowBytes);
+    if (pos0 >= 0 && pos0 + kChunk - 1 <= w - 1) {
+      const S* p = p0 + static_cast<int64_t>(pos0 + q) * step;
+      const int64_t inc = static_cast<int64_t>(Sh::kPos) * step;
+#pragma unroll
+      for (int i = 0; i < Sh::kVec; ++i) dma16_load<nt>(p + i * inc, m0 + i * 1024u);
+    } else {
+#pragma unroll
+      for (int i = 0; i < Sh::kVec; ++i) {
+        const int t = pos0 + Sh::kPos * i + q;
+        dma16_load<nt>(p0 + static_cast<int64_t>(t < 0 ? 0 : t < w ? t : w - 1) * step, m0 + i * 1024u);
+      }
+    }
+  }
+
+  __device__ __forceinline__ void load_side(const S* p0, int64_t step, uint32_t ring_m0) const {
+    const int enter_slots = split ? Sh::kHalf : Sh::kSlots;
+    const int lag = (2 * r + 1) / kChunk;  // the first step with a leaving value
+    int enter_slot = 0, leave_slot = 0;
+    auto issue = [&](int u) {
+      if (u < n_chunks) {
+        if (stream)
+          load_chunk<true>(p0, step, u * kChunk, enter_slot, ring_m0);
+        else
+          load_chunk<false>(p0, step, u * kChunk, enter_slot, ring_m0);
+        enter_slot = enter_slot + 1 == enter_slots ? 0 : enter_slot + 1;
+      }
+      if (split && u < n_steps) {
+        if (u >= lag)
+          load_chunk<kBlurLeaveStream>(p0, step, u * kChunk - 2 * r - 1, Sh::kHalf + leave_slot, ring_m0);
+        leave_slot = leave_slot + 1 == Sh::kHalf ? 0 : leave_slot + 1;
+      }
+    };
+    // Chunks issued by slots u0 .. u1.
+    auto issued = [&](int u0, int u1) {
+      const int e = min(u1, n_chunks - 1) - u0 + 1;
+      const int l = split ? min(u1, n_steps - 1) - max(u0, lag) + 1 : 0;
+      return max(e, 0) + max(l, 0);
+    };
+    for (int u = 0; u < Sh::kDepth; ++u) issue(u);
+    wait_chunks<Sh::kVec, 2 * (Sh::kDepth - 2)>(issued(2, Sh::kDepth - 1));
+    relay_barrier();
+    relay_barrier();
+    for (int e = 0; e < n_steps; ++e) {
+      issue(e + Sh::kDepth);
+      wait_chunks<Sh::kVec, 2 * (Sh::kDepth - 2)>(issued(e + 3, e + Sh::kDepth));
+      relay_barrier();
+    }
+    relay_barrier();
+  }
+
+  // ---- summing wave
+
+  // What a step adds (e) and subtracts (l).
+  static_assert(kChunk == 16, "ChunkValues holds 16 positions");
+  struct Values {
+    ChunkValues<S> e, l;
+  };
+  // Where the summing wave stands: the step, the region rows of its chunk and
+  // of its first leaving position, and the running sum.
+  struct Cursor {
+    int e, row, lb, erows, lbase;
+    float s;
+  };
+
+  // kChunk rows from row b of the region of `rows` rows at `base`.
+  __device__ __forceinline__ void read_rows(ChunkValues<S>& v, int base, int b, int rows) const {
+    if (b + kChunk <= rows) {
+      const S* p = &ring[base + b][lane];
+#pragma unroll
+      for (int i = 0; i < kChunk; ++i) v.set(i, p[i * 64]);
+      asm volatile("" : : : "memory");  // keeps the two ways apart
+    } else {
+      // Byte offsets from the region's start: past its end the smaller of
+      // the offset and the (unsigned) offset less the region's size.
+      const char* from = reinterpret_cast<const char*>(&ring[base][0]);
+      const uint32_t size = static_cast<uint32_t>(rows) * Sh::kRowBytes;
+      uint32_t at = static_cast<uint32_t>(b) * Sh::kRowBytes + static_cast<uint32_t>(lane * sizeof(S));
+      asm volatile("" : "+v"(at));  // the offsets below are made here, not kept in registers all along
+#pragma unroll
+      for (int i = 0; i < kChunk; ++i) {
+        const uint32_t o = at + i * Sh::kRowBytes;
+        v.set(i, *reinterpret_cast<const S*>(from + min(o, o - size)));
+      }
+      asm volatile("" : : : "memory");
+    }
+  }
+  // The values of the step at c.row / c.lb, which then moves on.
+  __device__ __forceinline__ void read_values(Cursor& c, Values& v) const {
+    const S* p = &ring[c.row][lane];
+#pragma unroll
+    for (int i = 0; i < kChunk; ++i) v.e.set(i, p[i * 64]);
+    read_rows(v.l, c.lbase, c.lb, c.erows);
+    c.row = c.row + kChunk == c.erows ? 0 : c.row + kChunk;
+    c.lb = c.lb + kChunk >= c.erows ? c.lb + kChunk - c.erows : c.lb + kChunk;
+  }
+
+  // One step whose every t adds (ADD) and subtracts (SUB) a value, or none does.
+  template <bool ADD, bool SUB>
+  __device__ __forceinline__ void even_step(const Values& cur, Values& next, Cursor& c) const {
+    read_values(c, next);
+    __builtin_amdgcn_sched_barrier(0);
+    float* o = &sums[(c.e & 1) * kChunk][lane];
+#pragma unroll
+    for (int p = 0; p < kChunk; ++p) {
+      if (ADD) c.s = c.s + cur.e.get(p);
+      if (SUB) c.s = c.s - cur.l.get(p);
+      o[p * 64] = c.s;
+    }
+    ++c.e;
+    relay_barrier();
+  }
+  // n such steps; the values of the first are in a, and so are in the end
+  // those of the step after the last.
+  template <bool ADD, bool SUB>
+  __device__ __forceinline__ void even_steps(int n, Values& a, Values& b, Cursor& c) const {
+    for (; n >= 2; n -= 2) {
+      even_step<ADD, SUB>(a, b, c);
+      even_step<ADD, SUB>(b, a, c);
+    }
+    if (n == 1) {
+      even_step<ADD, SUB>(a, b, c);
+      a = b;
+    }
+  }
+  // Any step. Where no value enters, -0 is added and where none leaves, +0
+  // is subtracted: both leave every sum as it is.
+  __device__ __forceinline__ void mixed_step(Values& a, Cursor& c) const {
+    const int t0 = c.e * kChunk;
+    const int no_add = w - t0, sub_from = 2 * r + 1 - t0;
+    float* o = &sums[(c.e & 1) * kChunk][lane];
+#pragma unroll
+    for (int p = 0; p < kChunk; ++p) {
+      c.s = c.s + (p < no_add ? a.e.get(p) : -0.0f);
+      c.s = c.s - (p >= sub_from ? a.l.get(p) : 0.0f);
+      o[p * 64] = c.s;
+    }
+    read_values(c, a);
+    ++c.e;
+    relay_barrier();
+  }
+
+  __device__ __forceinline__ void sum_side() const {
+    // Chunks wholly below these bounds of t: every t adds, no t subtracts yet.
+    const int adds = w / kChunk, no_sub = (2 * r + 1) / kChunk;
+    Cursor c;
+    c.e = 0;
+    c.row = 0;
+    c.erows = (split ? Sh::kHalf : Sh::kSlots) * kChunk;
+    c.lbase = split ? Sh::kHalf * kChunk : 0;
+    // Split: step e reads slot e of the second region. Else the position's row.
+    c.lb = split ? 0 : c.erows - 2 * r - 1;
+    c.s = -0.0f;  // adding the first value to it gives that value
+    Values a, b;
+    relay_barrier();
+    read_values(c, a);
+    relay_barrier();  // the first chunk may be overwritten
+    while (c.e < n_steps) {
+      const int t0 = c.e * kChunk;
+      const bool all_sub = t0 >= 2 * r + 1;
+      if (c.e < adds && all_sub)
+        even_steps<true, true>(adds - c.e, a, b, c);
+      else if (c.e < min(adds, no_sub))
+        even_steps<true, false>(min(adds, no_sub) - c.e, a, b, c);
+      else if (t0 >= w && all_sub)
+        even_steps<false, true>(n_steps - c.e, a, b, c);
+      else
+        mixed_step(a, c);
+    }
+    relay_barrier();
+  }
+
+  // ---- storing wave
+
+  // Output x = t - r of a sum is s / count. Lane (q, j) stores the 16-byte
+  // piece j of positions q, q + kPos, ..; dst0: its address at position 0.
+  __device__ __forceinline__ void store_side(S* dst0, int64_t step, bool ok) const {
+    constexpr int kPiece = 16 / static_cast<int>(sizeof(S));  // values of a piece
+    const int q = lane / Sh::kLanesPerRow, j = lane % Sh::kLanesPerRow;
+    const float m_inner = 1.0f / static_cast<float>(2 * r + 1);
+    S* at = dst0 + static_cast<int64_t>(q - r) * step;
+    const int64_t inc = Sh::kPos * step;
+    const float* from = &sums[q][kPiece * j];
+    relay_barrier();
+    relay_barrier();
+    for (int e = 0; e < n_steps; ++e) {
+      const int x0 = e * kChunk - r;
+      const bool inner = x0 >= r && x0 + kChunk - 1 + r <= w - 1;
+      float m[Sh::kVec];
+#pragma unroll
+      for (int i = 0; i < Sh::kVec; ++i) m[i] = m_inner;
+      if (!inner) {
+#pragma unroll
+        for (int i = 0; i < Sh::kVec; ++i) {
+          const int t = x0 + Sh::kPos * i + q;
+          const int x = t < 0 ? 0 : t < w - 1 ? t : w - 1;
+          m[i] = 1.0f / static_cast<float>((x + r < w - 1 ? x + r : w - 1) - (x - r > 0 ? x - r : 0) + 1);
+        }
+      }
+      relay_barrier();
+      const float* rows = from + (e & 1) * kChunk * 64;
+      float v[Sh::kVec][kPiece];
+#pragma unroll
+      for (int i = 0; i < Sh::kVec; ++i)
+#pragma unroll
+        for (int k = 0; k < kPiece; k += 4) {
+          const float4 f = *reinterpret_cast<const float4*>(rows + i * Sh::kPos * 64 + k);
+          v[i][k] = f.x * m[i];
+          v[i][k + 1] = f.y * m[i];
+          v[i][k + 2] = f.z * m[i];
+          v[i][k + 3] = f.w * m[i];
+        }
+      S* p = at;
+      if (inner) {
+        if (ok) {
+#pragma unroll
+          for (int i = 0; i < Sh::kVec; ++i, p += inc) store_piece(p, v[i]);
+        }
+      } else {
+#pragma unroll
+        for (int i = 0; i < Sh::kVec; ++i, p += inc) {
+          const int x = x0 + Sh::kPos * i + q;
+          if (x >= 0 && x < w && ok) store_piece(p, v[i]);
+        }
+      }
+      at += kChunk * step;
+    }
+    relay_barrier();
+  }
+  __device__ static __forceinline__ void store_piece(S* dst, const float (&v)[16 / sizeof(S)]) {
+    if constexpr (sizeof(S) == 4) {
+      *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+      uint4 u;
+      u.x = float_to_bf16(v[0]) | (float_to_bf16(v[1]) << 16);
+      u.y = float_to_bf16(v[2]) | (float_to_bf16(v[3]) << 16);
+      u.z = float_to_bf16(v[4]) | (float_to_bf16(v[5]) << 16);
+      u.w = float_to_bf16(v[6]) | (float_to_bf16(v[7]) << 16);
+      *reinterpret_cast<uint4*>(dst) = u;
+    }
+  }
+};
+
+// Lines of one relay blur pass, GPB line groups (GPB * kRelayWaves waves) per
+// block: group `sub` of block `bid` takes lines (bid * GPB + sub) * 64/DP ..
+// and walks on with a stride. Every group of a block takes the same number of
+// steps (past the last line it repeats that line without storing), so that
+// all its waves meet at the same barriers.
+template <typename S, int DP, int GPB>
+__device__ __forceinline__ void blur_relay_lines(const S* __restrict__ in, S* __restrict__ out, int w, int r,
+                                                 int vertical, bool stream, int64_t bid, int64_t nblocks,
+                                                 RelayLds<S>* lds) {
+  constexpr int kLines = 64 / DP;
+  using Sh = RelayShape<S>;
+  using L_t = RelayLine<S, DP>;
+  const int wib = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63;
+  const int sub = wib / kRelayWaves, role = wib % kRelayWaves;
+  const int64_t step = vertical ? static_cast<int64_t>(w) * DP : DP;       // elements between positions of a line
+  const int64_t line_step = vertical ? DP : static_cast<int64_t>(w) * DP;  // and between lines
+  if (r == 0) {
+    if (role != 0) return;
+    for (int64_t g = bid * GPB + sub; g * kLines < w; g += nblocks * GPB) {
+      const int64_t line = g * kLines + lane / DP;
+      if (line >= w) continue;
+      const int64_t base = line * line_step + lane % DP;
+      for (int x = 0; x < w; ++x) out[base + x * step] = in[base + x * step];
+    }
+    return;
+  }
+  // Every window of half-width w - 1 or more is the whole line.
+  if (r > w - 1) r = w - 1;
+  L_t L;
+  L.init(w, r, stream, lane, lds[sub]);
+  const int j = lane % Sh::kLanesPerRow;
+  // Each role has its own loop over the line groups, so that a wave holds its
+  // own role's values only.
+  auto each_group = [&](auto&& work) __attribute__((always_inline)) {
+    for (int64_t g0 = bid * GPB; g0 * kLines < w; g0 += nblocks * GPB) {
+      const int64_t want = (g0 + sub) * kLines + j / L_t::kPiecesPerCell;
+      const int64_t line = want < w ? want : w - 1;
+      work(line * line_step + (j % L_t::kPiecesPerCell) * (16 / static_cast<int>(sizeof(S))), want < w);
+    }
+  };
+  if (role == 0) {
+    const uint32_t ring_m0 = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(
+        reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) S*)(&lds[sub].ring[0][0]))));
+    each_group([&](int64_t piece, bool) { L.load_side(in + piece, step, ring_m0); });
+  } else if (role == 1) {
+    each_group([&](int64_t, bool) { L.sum_side(); });
+  } else {
+    each_group([&](int64_t piece, bool ok) { L.store_side(out + piece, step, ok); });
+  }
+}
+
+// Waves per SIMD of a relay kernel: what its LDS lets share a CU (four
+// float32 groups; six bfloat16 groups, or one block of four).
+template <typename S, int GPB>
+constexpr int relay_waves_per_eu() {
+  return sizeof(S) == 4 || GPB == 4 ? 3 : 5;
+}
+
+template <typename S, int DP, int GPB>
+__global__ __launch_bounds__(GPB * kRelayWaves * 64) __attribute__((amdgpu_waves_per_eu(relay_waves_per_eu<S, GPB>())))
+void k_blur_relay(const S* __restrict__ in, S* __restrict__ out, int w, const DevState* __restrict__ st, int radius,
+                  int vertical, int stream, int32_t* __restrict__ table) {
+  __shared__ RelayLds<S> s_lds[GPB];
+  int r;
+  if (!pass_radius(st, radius, r)) return;
+  blur_relay_lines<S, DP, GPB>(in, out, w, r, vertical, stream != 0, blockIdx.x, gridDim.x, s_lds);
+  if (table != nullptr) fill_group_table<GPB * kRelayWaves * 64>(table, st->beta, st->keys, blockIdx.x, gridDim.x);
+}
+
+// Blur pass of large float32 grids at middle radii (see blur_pass_dp): one
+// wave per group of 64 / DP lines loads, sums and stores, and keeps leaving
+// values in registers. Same arithmetic, LDS rows and direct loads as the
+// relay pass.
+//
+// The line is loaded chunk by chunk (16 positions aligned to multiples of 16)
+// into a ring of rows (row = position modulo the ring). Step e takes chunk e:
+// first its positions up to min(r, w - 1) go into the starting sum, then, from
+// step A = ceil(r / kChunk) on, the outputs x of chunk e - A (x + r lies in
+// chunk e or e - 1). While the ring also holds every leaving position
+// x - r - 1 still to come beside the chunks in flight, leaving values are read
+// back from it; otherwise the ring is split in two halves and the leaving
+// chunks reach the upper half from 24 register slots, where each chunk was
+// kept since it entered (48 <= r <= 192), or from a second load stream (the
+// same positions again). Loads are issued at positions clamped into the line,
+// so every chunk is exactly kVec load instructions.
+//
+// Waits. Every step issues, in this order, the stores of the chunk it summed
+// and then the loads of issue slot e + kDepth - 1 (entering chunk, then leaving
+// chunk); the number of operations issued after a chunk's last load follows
+// from that schedule (ops_after).
+struct RingShape {
+  static constexpr int kRowBytes = 256;  // one position of the wave's lines
+  static constexpr int kLanesPerRow = kRowBytes / 16;
+  static constexpr int kPos = 64 / kLanesPerRow;  // positions per load instruction
+  static constexpr int kChunk = 16;               // positions per chunk
+  static constexpr int kVec = kChunk / kPos;      // load instructions per chunk
+  static constexpr int kDepth = 3;                // issue slots in flight, the one being summed included
+  static constexpr int kRingRows = 128;
+  static constexpr int kSlots = kRingRows / kChunk;
+  static constexpr int kRegChunks = 24;      // register slots of leaving chunks
+  static constexpr int kRegWords = kChunk;   // registers per chunk
+  static constexpr int kHalfRows = kRingRows / 2;  // rows of each stream when the ring is split
+  static_assert((kRingRows & (kRingRows - 1)) == 0, "ring shape");
+  static_assert(kHalfRows / kChunk >= kDepth, "a split half holds the chunks in use and in flight");
+};
+
+// LDS of one wave: 36 KB.
+struct alignas(16) RingLds {
+  float ring[RingShape::kRingRows][64];
+  float out[RingShape::kChunk][64];
+};
+
+// Leaving values come from the entering ring when, at every step, the chunk
+// issued then does not overwrite a leaving position still to come: with A =
+// ceil(r / kChunk) chunks between a step's chunk and its outputs and
+// ceil((r + 1) / kChunk) between an output chunk and its leaving positions,
+// A + ceil((r + 1) / kChunk) <= kSlots + 1 - kDepth.
+__device__ __forceinline__ bool ring_leave(int r) {
+  using Sh = RingShape;
+  const int a = (r + Sh::kChunk - 1) / Sh::kChunk;
+  const int b = (r + Sh::kChunk) / Sh::kChunk;
+  return a + b <= Sh::kSlots + 1 - Sh::kDepth;
+}
+
+// One direct load whose LDS rows this wave may still be reading: those reads
+// must have completed first.
+template <bool nt>
+__device__ __forceinline__ void dma16(const void* src, uint32_t m0) {
+  asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+  dma16_load<nt>(src, m0);
+}
+
+// s_waitcnt vmcnt(n) for a run-time n (rounded down, which only waits
+// longer).
 __device__ __forceinline__ void wait_vm_dyn(int n) {
   switch (n < 0 ? 0 : n) {
     case 0: wait_vm<0>(); break;
@@ -662,14 +1053,13 @@ __device__ __forceinline__ void wait_vm_dyn(int n) {
   }
 }
 
-template <typename S, int DP, int RR, int KR, bool NT>
+template <int DP, bool NT>
 struct RingLine {
-  using Sh = RingShape<S, RR, KR>;
+  using Sh = RingShape;
   static constexpr int kChunk = Sh::kChunk;
-  static constexpr int kPiecesPerCell = DP * static_cast<int>(sizeof(S)) / 16;
-  static_assert(kPiecesPerCell >= 1, "a cell must hold at least one 16-byte piece");
-  const S* __restrict__ src;  // the pass's input grid
-  S* __restrict__ dst;        // and output grid
+  static constexpr int kPiecesPerCell = DP / 4;
+  const float* __restrict__ src;  // the pass's input grid
+  float* __restrict__ dst;        // and output grid
   int64_t step;     // elements between consecutive positions of a line
   int64_t ld_off;   // element offset of this lane's load piece at position 0
   bool ld_ok;       // the load piece's line exists (else its loads are clamped and its stores skipped)
@@ -683,7 +1073,7 @@ struct RingLine {
   bool regs;         // split, and the leaving chunks come from registers instead of a second load stream
   int enter_mask;    // ring rows of the entering stream - 1
   uint32_t ring_m0;  // LDS byte address of ring row 0 (the same for all lanes)
-  RingLds<S, RR>* lds;
+  RingLds* lds;
 
   __device__ __forceinline__ int clamp_pos(int t) const { return t < 0 ? 0 : (t > w - 1 ? w - 1 : t); }
 
@@ -693,7 +1083,7 @@ struct RingLine {
     const int pos0 = m * kChunk;
     const uint32_t m0 = ring_m0 + static_cast<uint32_t>(row0 * Sh::kRowBytes);
     if (pos0 + kChunk - 1 <= w - 1) {
-      const S* p = src + ld_off + static_cast<int64_t>(pos0 + q) * step;
+      const float* p = src + ld_off + static_cast<int64_t>(pos0 + q) * step;
       const int64_t inc = static_cast<int64_t>(Sh::kPos) * step;
 #pragma unroll
       for (int i = 0; i < Sh::kVec; ++i) dma16<nt>(p + i * inc, m0 + i * 1024u);
@@ -727,7 +1117,7 @@ struct RingLine {
     int n = 0;
 #pragma unroll
     for (int u = 1; u <= Sh::kDepth - 2; ++u) n += slot_loads(e + u);
-    const int first = e - Sh::kDepth + (Sh::kEarly ? 1 : 2);
+    const int first = e - Sh::kDepth + 2;
     const int s0 = first > 0 ? first : 0;
     for (int s = s0; s < e; ++s) n += step_stores(s);
     return n;
@@ -739,10 +1129,10 @@ struct RingLine {
     return split ? Sh::kHalfRows + (t & (Sh::kHalfRows - 1)) : (t & (Sh::kRingRows - 1));
   }
   __device__ __forceinline__ float enter_val(int x) const {
-    return Storage<S>::widen(lds->ring[enter_row(x)][lane]);
+    return (lds->ring[enter_row(x)][lane]);
   }
   __device__ __forceinline__ float leave_val(int x) const {
-    return Storage<S>::widen(lds->ring[leave_row(x)][lane]);
+    return (lds->ring[leave_row(x)][lane]);
   }
 
   // Outputs x0 .. x0 + kChunk - 1, all inside the grid, all with (ENTER) or
@@ -763,12 +1153,12 @@ struct RingLine {
     const bool l_flat = !LEAVE || (lb & (split ? Sh::kHalfRows - 1 : Sh::kRingRows - 1)) + kChunk <=
                                       (split ? Sh::kHalfRows : Sh::kRingRows);
     if (e_flat && l_flat) {
-      const S* ep = &lds->ring[ENTER ? eb : 0][lane];
-      const S* lp = &lds->ring[LEAVE ? lb : 0][lane];
+      const float* ep = &lds->ring[ENTER ? eb : 0][lane];
+      const float* lp = &lds->ring[LEAVE ? lb : 0][lane];
 #pragma unroll
       for (int p = 0; p < kChunk; ++p) {
-        if (ENTER) e[p] = Storage<S>::widen(ep[p * 64]);
-        if (LEAVE) l[p] = Storage<S>::widen(lp[p * 64]);
+        if (ENTER) e[p] = (ep[p * 64]);
+        if (LEAVE) l[p] = (lp[p * 64]);
       }
     } else {
 #pragma unroll
@@ -783,7 +1173,7 @@ struct RingLine {
       if (ENTER) s = s + e[p];
       if (LEAVE) s = s - l[p];
       const float m = kConstMult ? m_const : __int_as_float(__builtin_amdgcn_readlane(mult_bits, p));
-      lds->out[p][lane] = Storage<S>::narrow(s * m);
+      lds->out[p][lane] = s * m;
     }
   }
 
@@ -805,7 +1195,7 @@ struct RingLine {
       s = (inside && x + r <= w - 1) ? with_enter : s;
       const float with_leave = s - l[p];
       s = (inside && x - r - 1 >= 0) ? with_leave : s;
-      lds->out[p][lane] = Storage<S>::narrow(s * __int_as_float(__builtin_amdgcn_readlane(mult_bits, p)));
+      lds->out[p][lane] = s * __int_as_float(__builtin_amdgcn_readlane(mult_bits, p));
     }
   }
 
@@ -815,7 +1205,7 @@ struct RingLine {
     const int t0 = e * kChunk;
     float v[kChunk];
 #pragma unroll
-    for (int p = 0; p < kChunk; ++p) v[p] = Storage<S>::widen(lds->ring[(t0 + p) & enter_mask][lane]);
+    for (int p = 0; p < kChunk; ++p) v[p] = (lds->ring[(t0 + p) & enter_mask][lane]);
     if (t0 > 0 && t0 + kChunk - 1 <= first_hi) {
 #pragma unroll
       for (int p = 0; p < kChunk; ++p) s = s + v[p];
@@ -860,8 +1250,8 @@ struct RingLine {
     for (int i = 0; i < Sh::kVec; ++i) {
       const int x = x0 + Sh::kPos * i + q;
       if (x < w && ld_ok)
-        store16<blur_stream_stores<RR>()>(dst + ld_off + static_cast<int64_t>(x) * step,
-                                   *reinterpret_cast<const uint4*>(&lds->out[Sh::kPos * i + q][16 / sizeof(S) * j]));
+        *reinterpret_cast<float4*>(dst + ld_off + static_cast<int64_t>(x) * step) =
+            *reinterpret_cast<const float4*>(&lds->out[Sh::kPos * i + q][4 * j]);
     }
   }
 
@@ -918,22 +1308,19 @@ struct RingLine {
   }
 
   __device__ __forceinline__ void run_regs() const {
-    if constexpr (Sh::kRegChunks > 0) {
-      // Zeroed: the first lag steps read a slot (and drop the value) before
-      // its first chunk arrives.
-      Word keep[Sh::kRegChunks][kWords] = {};
-      for (int u = 0; u <= Sh::kDepth - 2; ++u) issue(u);
-      float s = 0.0f;
-      int slot = 0;
-      for (int e = 0; e < n_steps; ++e) {
-        if (slot_loads(e) > 0) wait_vm_dyn(ops_after(e));
-        if (Sh::kEarly) issue(e + Sh::kDepth - 1);
-        exchange<Sh::kRegChunks>(keep, slot, e);
-        if (e * kChunk <= first_hi) start_sum(e, s);
-        if (e >= ahead) outputs(e - ahead, s);
-        if (!Sh::kEarly) issue(e + Sh::kDepth - 1);
-        slot = slot + 1 == lag ? 0 : slot + 1;
-      }
+    // Zeroed: the first lag steps read a slot (and drop the value) before
+    // its first chunk arrives.
+    Word keep[Sh::kRegChunks][kWords] = {};
+    for (int u = 0; u <= Sh::kDepth - 2; ++u) issue(u);
+    float s = 0.0f;
+    int slot = 0;
+    for (int e = 0; e < n_steps; ++e) {
+      if (slot_loads(e) > 0) wait_vm_dyn(ops_after(e));
+      exchange<Sh::kRegChunks>(keep, slot, e);
+      if (e * kChunk <= first_hi) start_sum(e, s);
+      if (e >= ahead) outputs(e - ahead, s);
+      issue(e + Sh::kDepth - 1);
+      slot = slot + 1 == lag ? 0 : slot + 1;
     }
   }
 
@@ -946,21 +1333,19 @@ struct RingLine {
     float s = 0.0f;
     for (int e = 0; e < n_steps; ++e) {
       if (slot_loads(e) > 0) wait_vm_dyn(ops_after(e));
-      if (Sh::kEarly) issue(e + Sh::kDepth - 1);
       if (e * kChunk <= first_hi) start_sum(e, s);
       if (e >= ahead) outputs(e - ahead, s);
-      if (!Sh::kEarly) issue(e + Sh::kDepth - 1);
+      issue(e + Sh::kDepth - 1);
     }
   }
 };
 
-// Lines line0 .. line0 + 64/DP - 1 of a staged blur pass (those below w),
-// by one wave.
-template <typename S, int DP, int RR, int KR, bool NT>
-__device__ __forceinline__ void blur_staged_line(const S* __restrict__ in, S* __restrict__ out, int w, int r,
-                                                 int vertical, int64_t line0, int lane, RingLds<S, RR>* lds) {
-  using Sh = RingShape<S, RR, KR>;
-  using L_t = RingLine<S, DP, RR, KR, NT>;
+// Lines line0 .. line0 + 64/DP - 1 of a ring pass (those below w), by one wave.
+template <int DP, bool NT>
+__device__ __forceinline__ void blur_ring_line(const float* __restrict__ in, float* __restrict__ out, int w, int r,
+                                               int vertical, int64_t line0, int lane, RingLds* lds) {
+  using Sh = RingShape;
+  using L_t = RingLine<DP, NT>;
   L_t L;
   // Element offset of line l at position 0, and between positions.
   auto line_off = [&](int64_t l) { return vertical ? l * DP : l * w * DP; };
@@ -973,7 +1358,7 @@ __device__ __forceinline__ void blur_staged_line(const S* __restrict__ in, S* __
   L.j = lane % Sh::kLanesPerRow;
   const int64_t ld_line = line0 + L.j / L_t::kPiecesPerCell;
   L.ld_ok = ld_line < w;
-  L.ld_off = line_off(L.ld_ok ? ld_line : w - 1) + (L.j % L_t::kPiecesPerCell) * (16 / static_cast<int>(sizeof(S)));
+  L.ld_off = line_off(L.ld_ok ? ld_line : w - 1) + (L.j % L_t::kPiecesPerCell) * 4;
   L.lane = lane;
   L.lds = lds;
   if (r == 0) {
@@ -987,7 +1372,7 @@ __device__ __forceinline__ void blur_staged_line(const S* __restrict__ in, S* __
   L.n_chunks = (w + Sh::kChunk - 1) / Sh::kChunk;
   L.ahead = (r + Sh::kChunk - 1) / Sh::kChunk;
   L.n_steps = L.ahead + L.n_chunks;
-  L.split = !ring_leave<S, RR>(r);
+  L.split = !ring_leave(r);
   // Step e sums outputs of chunk k = e - A, whose leaving positions reach
   // up to k kChunk + kChunk - 2 - r: chunk e - lag.
   L.lag = L.ahead - ((Sh::kChunk - 2 - r) >= 0 ? (Sh::kChunk - 2 - r) / Sh::kChunk
@@ -995,53 +1380,26 @@ __device__ __forceinline__ void blur_staged_line(const S* __restrict__ in, S* __
   L.regs = L.split && L.lag <= Sh::kRegChunks;
   L.enter_mask = (L.split ? Sh::kHalfRows : Sh::kRingRows) - 1;
   L.ring_m0 = __builtin_amdgcn_readfirstlane(
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) S*)(&lds->ring[0][0]))));
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) float*)(&lds->ring[0][0]))));
   L.run();
 }
 
-// Waves per SIMD a staged kernel keeps room for in registers: one float32
-// wave with the 128-row ring (its LDS allows no more), else two.
-template <typename S, int RR>
-constexpr int staged_waves_per_eu() {
-  return sizeof(S) == 4 && RR >= 128 ? 1 : 2;
-}
-
-// One group of 64/DP lines per wave, WPB waves per block: block `bid` of
-// `nblocks` takes groups bid * WPB + wave, and walks on with a stride if
-// there are more groups than waves.
-template <typename S, int DP, int WPB, int RR, int KR, bool NT>
-__device__ __forceinline__ void blur_staged_lines(const S* __restrict__ in, S* __restrict__ out, int w, int r,
-                                                  int vertical, int64_t bid, int64_t nblocks, RingLds<S, RR>* stage) {
-  constexpr int kLinesPerWave = 64 / DP;
-  const int wib = threadIdx.x >> 6;
-  const int lane = threadIdx.x & 63;
-  for (int64_t g = bid * WPB + wib; g * kLinesPerWave < w; g += nblocks * WPB)
-    blur_staged_line<S, DP, RR, KR, NT>(in, out, w, r, vertical, g * kLinesPerWave, lane, stage + wib);
-}
-
-// Staged blur pass for cells of at least 16 bytes (DP * sizeof(S) >= 16),
-// with a ring of RR rows per wave and KR register slots; NT: the entering
-// loads stream.
-template <typename S, int DP, int WPB, int RR, int KR, bool NT>
-__global__ __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(staged_waves_per_eu<S, RR>())))
-void k_blur_staged(const S* __restrict__ in, S* __restrict__ out, int w, const DevState* __restrict__ st, int radius,
-                   int vertical, int32_t* __restrict__ table) {
-  __shared__ RingLds<S, RR> s_stage[WPB];
+// One group of 64/DP lines per wave; two-wave blocks of 72 KB LDS, so that
+// four waves share a CU, one per SIMD with all its registers.
+constexpr int kRingWavesPerBlock = 2;
+template <int DP, bool NT>
+__global__ __launch_bounds__(kRingWavesPerBlock * 64) __attribute__((amdgpu_waves_per_eu(1)))
+void k_blur_ring(const float* __restrict__ in, float* __restrict__ out, int w, const DevState* __restrict__ st,
+                 int radius, int vertical, int32_t* __restrict__ table) {
+  __shared__ RingLds s_ring[kRingWavesPerBlock];
   int r;
   if (!pass_radius(st, radius, r)) return;
-  blur_staged_lines<S, DP, WPB, RR, KR, NT>(in, out, w, r, vertical, blockIdx.x, gridDim.x, s_stage);
-  if (table != nullptr) fill_group_table<WPB * 64>(table, st->beta, st->keys, blockIdx.x, gridDim.x);
-}
-
-// Register slots a wave keeps for the leaving values (float32): 24 with the
-// 128-row ring (384 registers; one wave per SIMD, as the ring's LDS allows),
-// 8 with the 64-row ring (128 registers; two waves per SIMD). bfloat16
-// passes run two waves per SIMD and keep the second load stream: with 16
-// slots they measured no faster (1448^2, r = 48..128: 146 / 144 us per
-// row / column pass, against 138 / 148 us).
-template <typename S, int RR>
-constexpr int ring_register_chunks() {
-  return sizeof(S) == 4 ? (RR >= 128 ? 24 : 8) : 0;
+  const int wib = threadIdx.x >> 6;
+  const int64_t nwaves = static_cast<int64_t>(gridDim.x) * kRingWavesPerBlock;
+  for (int64_t g = static_cast<int64_t>(blockIdx.x) * kRingWavesPerBlock + wib; g * (64 / DP) < w; g += nwaves)
+    blur_ring_line<DP, NT>(in, out, w, r, vertical, g * (64 / DP), threadIdx.x & 63, s_ring + wib);
+  if (table != nullptr)
+    fill_group_table<kRingWavesPerBlock * 64>(table, st->beta, st->keys, blockIdx.x, gridDim.x);
 }
 
 // Cells of DP * sizeof(S) bytes are moved in 16-byte pieces when they hold
@@ -1051,11 +1409,7 @@ constexpr bool staged_cells() {
   return DP * static_cast<int>(sizeof(S)) >= 16;
 }
 
-// float32 waves of a staged pass with the 128-row ring (37 KB of LDS each)
-// that fit on the chip at once: 4 per CU, 256 CUs.
-constexpr int64_t kStagedWavesAtLargeRing = 1024;
-
-// Wave groups (of 64/DP lines) of a staged pass over w lines.
+// Groups of 64/DP lines of a pass over w lines.
 template <int DP>
 inline int64_t staged_groups(int w) {
   return (w + 64 / DP - 1) / (64 / DP);
@@ -1751,14 +2105,10 @@ __device__ __forceinline__ S* route_grid(const BatchGridView& g, int sel) {
   return global_ptr<S>(sel == 0 ? g.G : sel == 1 ? g.H : g.T);
 }
 
-// Ring rows of the batched staged pass (grids of a batch take whole lines
-// by the thousand; the larger ring keeps leaving values on chip up to r = 47).
-constexpr int kBatchRingRows = 128;
-
-template <typename S, int DP, int WPB, int KR, bool NT>
-__global__ __launch_bounds__(WPB * 64) __attribute__((amdgpu_waves_per_eu(staged_waves_per_eu<S, kBatchRingRows>())))
-void k_blur_staged_batch(const BatchGrid* __restrict__ grids, const uint32_t* __restrict__ map, int route) {
-  __shared__ RingLds<S, kBatchRingRows> s_stage[WPB];
+template <typename S, int DP, int GPB>
+__global__ __launch_bounds__(GPB * kRelayWaves * 64) __attribute__((amdgpu_waves_per_eu(relay_waves_per_eu<S, GPB>())))
+void k_blur_relay_batch(const BatchGrid* __restrict__ grids, const uint32_t* __restrict__ map, int route, int stream) {
+  __shared__ RelayLds<S> s_lds[GPB];
   uint32_t local;
   const BatchGridView& g = batch_grid(grids, map, local);
   const DevState* st = global_ptr<const DevState>(g.state);
@@ -1767,9 +2117,9 @@ void k_blur_staged_batch(const BatchGrid* __restrict__ grids, const uint32_t* __
   const int vertical = route_vertical(route);
   const S* in = route_grid<S>(g, (route >> 1) & 3);
   S* out = route_grid<S>(g, (route >> 3) & 3);
-  blur_staged_lines<S, DP, WPB, kBatchRingRows, KR, NT>(in, out, g.w, r, vertical, local, g.blur_blocks, s_stage);
+  blur_relay_lines<S, DP, GPB>(in, out, g.w, r, vertical, stream != 0, local, g.blur_blocks, s_lds);
   if (route_table(route))
-    fill_group_table<WPB * 64>(global_ptr<int32_t>(g.table), st->beta, st->keys, local, g.blur_blocks);
+    fill_group_table<GPB * kRelayWaves * 64>(global_ptr<int32_t>(g.table), st->beta, st->keys, local, g.blur_blocks);
 }
 
 template <int DP, typename S>
@@ -1964,26 +2314,34 @@ hipError_t launch_gather(const void* X, const int32_t* P, void* G, int64_t n, in
   return hipGetLastError();
 }
 
-// A staged pass with ring RR: over a large working set with register slots
-// (float32) and, in the column pass, streaming entering loads; else with
-// neither.
-template <typename S, int DP, int WPB, int RR>
-hipError_t staged_launch(int blocks, bool large, int vertical, hipStream_t stream, const S* src, S* dst, int w,
-                         const DevState* st, int radius, int32_t* table) {
-  constexpr int kR = ring_register_chunks<S, RR>();
-  constexpr int kThreads = WPB * 64;
-  if (!large)
-    k_blur_staged<S, DP, WPB, RR, 0, false><<<blocks, kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, table);
-  else if (vertical)
-    k_blur_staged<S, DP, WPB, RR, kR, true><<<blocks, kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, table);
-  else
-    k_blur_staged<S, DP, WPB, RR, kR, false><<<blocks, kThreads, 0, stream>>>(src, dst, w, st, radius, vertical,
-                                                                             table);
-  return hipGetLastError();
+// Line groups of a pass that takes the ring kernel (float32, grids in flight
+// over kLargeWorkingSetBytes): about one per SIMD. There memory bounds the
+// pass, and the register slots spare the second read of leaving values that
+// the relay ring does not hold (1024^2 x 64, row / column pass inside sorts:
+// 97 / 90 us against 126 / 122 us at radii 32 to 192, 117 / 114 against 122 /
+// 119 above, 92 / 86 both below). With fewer groups a wave that loads, sums
+// and stores in turn is the bound (2091^2 x 16, 523 groups: 140 / 138 us
+// against 117 / 129); with more than fit the chip at four per CU its waves
+// run in two rounds.
+constexpr int64_t kRingMinGroups = 769, kRingMaxGroups = 1024;
+
+// Line groups per block of a relay column pass over a large working set:
+// neighbouring groups walk down the same grid rows at the same time, and one
+// CU reads them as longer runs. As many as keep every group of the pass on
+// the chip at once: float32 blocks of two groups leave room for four groups
+// per CU and blocks of three for three, bfloat16 blocks of three for six.
+// Column passes inside sorts, one / two / three groups per block: 1448^2 x 64
+// bfloat16 117 / 112 / 97 us (r <= 31) and 149 / 143 / 135 (above); 2091^2 x 16
+// float32 126 / 132 / 125 and 171 / 199 / 159. Row passes read long runs with
+// one (two: 97 -> 117 us), and grids the Infinity Cache holds are not bound
+// by memory (723^2 x 64 float32: 47 us with one, 48 with two).
+template <typename S>
+inline int relay_column_groups(int64_t groups) {
+  return sizeof(S) == 2 || groups <= 768 ? 3 : 2;
 }
 
-// One pass for storage S and DP channels: the staged kernel when cells
-// hold whole 16-byte pieces, else the register kernel.
+// One pass for storage S and DP channels: the relay or ring kernel when
+// cells hold whole 16-byte pieces, else the register kernel.
 template <typename S, int DP>
 hipError_t blur_pass_dp(const void* in, void* out, int w, const DevState* st, int radius, int vertical,
                         const float* inv, hipStream_t stream, const TableArgs& ta) {
@@ -1994,26 +2352,40 @@ hipError_t blur_pass_dp(const void* in, void* out, int w, const DevState* st, in
     const int64_t need = std::min<int64_t>(1024, (ta.max_cells + threads - 1) / threads);
     return static_cast<int>(std::max<int64_t>(blocks, need));
   };
+  const S* src = static_cast<const S*>(in);
+  S* dst = static_cast<S*>(out);
   if constexpr (staged_cells<S, DP>()) {
-    constexpr int kThreads = kBlurWavesPerBlock * 64;
     const int64_t groups = staged_groups<DP>(w);
-    const int blocks = with_table((groups + kBlurWavesPerBlock - 1) / kBlurWavesPerBlock, kThreads);
-    // The 128-row ring while every wave of the pass fits on the chip at
-    // once with it (4 float32 waves per CU), else the 64-row ring (8 per CU);
-    // register slots for the leaving values and streaming column loads on
-    // grids the Infinity Cache does not hold twice over.
     const bool large = blur_large_working_set(static_cast<int64_t>(w) * w * DP * static_cast<int64_t>(sizeof(S)));
-    const S* src = static_cast<const S*>(in);
-    S* dst = static_cast<S*>(out);
-    if (sizeof(S) == 2 || groups <= kStagedWavesAtLargeRing)
-      return staged_launch<S, DP, kBlurWavesPerBlock, 128>(blocks, large, vertical, stream, src, dst, w, st, radius,
-                                                           ta.table);
-    return staged_launch<S, DP, kBlurWavesPerBlock, 64>(blocks, large, vertical, stream, src, dst, w, st, radius,
-                                                        ta.table);
+    const int streams = large && vertical ? 1 : 0;
+    if constexpr (sizeof(S) == 4) {
+      if (large && groups >= kRingMinGroups && groups <= kRingMaxGroups) {
+        const int blocks = with_table((groups + kRingWavesPerBlock - 1) / kRingWavesPerBlock, kRingWavesPerBlock * 64);
+        if (streams)
+          k_blur_ring<DP, true><<<blocks, kRingWavesPerBlock * 64, 0, stream>>>(src, dst, w, st, radius, vertical, ta.table);
+        else
+          k_blur_ring<DP, false><<<blocks, kRingWavesPerBlock * 64, 0, stream>>>(src, dst, w, st, radius, vertical, ta.table);
+        return hipGetLastError();
+      }
+    }
+    const int per_block = large && vertical ? relay_column_groups<S>(groups) : 1;
+    const int blocks = with_table((groups + per_block - 1) / per_block, per_block * kRelayWaves * 64);
+    constexpr int kThreads = kRelayWaves * 64;
+    switch (per_block) {
+      case 1:
+        k_blur_relay<S, DP, 1><<<blocks, kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, streams, ta.table);
+        break;
+      case 2:
+        k_blur_relay<S, DP, 2><<<blocks, 2 * kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, streams,
+                                                                   ta.table);
+        break;
+      default:
+        k_blur_relay<S, DP, 3><<<blocks, 3 * kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, streams,
+                                                                   ta.table);
+    }
   } else {
     const int blocks = with_table((blur_reg_waves<DP>(w) + kWavesPerBlock - 1) / kWavesPerBlock, kBlock);
-    k_blur<DP, S><<<blocks, kBlock, 0, stream>>>(static_cast<const S*>(in), static_cast<S*>(out), w, st, radius,
-                                                 vertical, inv, ta.table);
+    k_blur<DP, S><<<blocks, kBlock, 0, stream>>>(src, dst, w, st, radius, vertical, inv, ta.table);
   }
   return hipGetLastError();
 }
@@ -2093,17 +2465,13 @@ hipError_t launch_vad(const void* features, int input_bf16, const int32_t* perm,
 
 bool staged_blur(int dp, int storage) { return dp * (storage == kStorageBF16 ? 2 : 4) >= 16; }
 
-// The second read of a pass's leaving values comes from the 256 MB Infinity
-// Cache when the grids in flight are well inside it, and there the register
-// slots only add work: measured on float32 sorts, single 4-64 MiB grids ran
-// 2-4 % faster without them; single 256 MiB and larger grids, and a batch
-// of 64 grids of up to 121 MiB (3 GB together), ran 3-8 % faster with them.
-// The same bound decides the column pass's streaming loads.
+// Above this the Infinity Cache (256 MB) does not hold a pass's input and
+// output beside what the assignment reads next.
 constexpr int64_t kLargeWorkingSetBytes = int64_t(128) << 20;
 
 bool blur_large_working_set(int64_t working_bytes) { return working_bytes > kLargeWorkingSetBytes; }
 
-int batch_blur_blocks(int w, int dp, int storage, int waves_per_block, int64_t max_cells) {
+int batch_blur_blocks(int w, int dp, int storage, int groups_per_block, int64_t max_cells) {
   int64_t blocks = 0, threads = 0;
   int64_t groups = 0, waves = 0;
   switch (dp) {
@@ -2114,8 +2482,8 @@ int batch_blur_blocks(int w, int dp, int storage, int waves_per_block, int64_t m
     default: groups = staged_groups<64>(w); waves = blur_reg_waves<64>(w); break;
   }
   if (staged_blur(dp, storage)) {
-    blocks = (groups + waves_per_block - 1) / waves_per_block;
-    threads = 64 * waves_per_block;
+    blocks = (groups + groups_per_block - 1) / groups_per_block;
+    threads = kRelayWaves * 64 * groups_per_block;
   } else {
     blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
     threads = kBlock;
@@ -2135,35 +2503,18 @@ int assign_blocks_cap(int storage) {
   return PLAS_ASSIGN_MAX_BLOCKS;
 }
 
-template <typename S, int DP, int KR, bool NT>
-hipError_t blur_batch_staged(const BatchGrid* grids, const uint32_t* map, int blocks, int waves_per_block,
-                             int route, hipStream_t stream) {
-  switch (waves_per_block) {
-    case 1:
-      k_blur_staged_batch<S, DP, 1, KR, NT><<<blocks, 64, 0, stream>>>(grids, map, route);
-      break;
-    case 2:
-      k_blur_staged_batch<S, DP, 2, KR, NT><<<blocks, 128, 0, stream>>>(grids, map, route);
-      break;
-    case 4:
-      k_blur_staged_batch<S, DP, 4, KR, NT><<<blocks, 256, 0, stream>>>(grids, map, route);
-      break;
-    default:
-      return hipErrorInvalidValue;
-  }
-  return hipSuccess;
-}
-
 template <typename S, int DP>
-hipError_t blur_batch_dp(const BatchGrid* grids, const uint32_t* map, int blocks, int waves_per_block,
+hipError_t blur_batch_dp(const BatchGrid* grids, const uint32_t* map, int blocks, int groups_per_block,
                          int route, int large, hipStream_t stream) {
   if constexpr (staged_cells<S, DP>()) {
-    constexpr int kR = ring_register_chunks<S, kBatchRingRows>();
-    const hipError_t e =
-        large == 0 ? blur_batch_staged<S, DP, 0, false>(grids, map, blocks, waves_per_block, route, stream)
-        : route_vertical(route) ? blur_batch_staged<S, DP, kR, true>(grids, map, blocks, waves_per_block, route, stream)
-                                : blur_batch_staged<S, DP, kR, false>(grids, map, blocks, waves_per_block, route, stream);
-    if (e != hipSuccess) return e;
+    const int streams = large && route_vertical(route) ? 1 : 0;
+    constexpr int kThreads = kRelayWaves * 64;
+    switch (groups_per_block) {
+      case 1: k_blur_relay_batch<S, DP, 1><<<blocks, kThreads, 0, stream>>>(grids, map, route, streams); break;
+      case 2: k_blur_relay_batch<S, DP, 2><<<blocks, 2 * kThreads, 0, stream>>>(grids, map, route, streams); break;
+      case 4: k_blur_relay_batch<S, DP, 4><<<blocks, 4 * kThreads, 0, stream>>>(grids, map, route, streams); break;
+      default: return hipErrorInvalidValue;
+    }
   } else {
     k_blur_batch<DP, S><<<blocks, kBlock, 0, stream>>>(grids, map, route);
   }
@@ -2175,11 +2526,11 @@ int blur_route(int vertical, int src, int dst, int with_table) {
 }
 
 hipError_t launch_blur_batch(const BatchGrid* grids, const uint32_t* map, int blocks, int dp, int storage,
-                             int waves_per_block, int route, int large, hipStream_t stream) {
+                             int groups_per_block, int route, int large, hipStream_t stream) {
   const int src = (route >> 1) & 3, dst = (route >> 3) & 3;
   if (src > 2 || dst < 1 || dst > 2 || src == dst) return hipErrorInvalidValue;
   PLAS_DISPATCH_STORAGE(storage, {
-    PLAS_DISPATCH_DP(dp, return (blur_batch_dp<SV, DPV>(grids, map, blocks, waves_per_block, route, large, stream)));
+    PLAS_DISPATCH_DP(dp, return (blur_batch_dp<SV, DPV>(grids, map, blocks, groups_per_block, route, large, stream)));
   });
   return hipSuccess;
 }

@@ -94,7 +94,7 @@ bool staged_blur(int dp, int storage);
 bool blur_large_working_set(int64_t working_bytes);
 // Blur blocks: enough for every line, and for filling a grouping table of
 // max_cells entries at about one entry per thread.
-int batch_blur_blocks(int w, int dp, int storage, int waves_per_block, int64_t max_cells);  // wpb: 1, 2, 4
+int batch_blur_blocks(int w, int dp, int storage, int groups_per_block, int64_t max_cells);  // wpb: 1, 2, 4
 int batch_assign_blocks(int64_t max_items, int dp, int storage, int cap);  // cap <= 0: the single-sort default
 int assign_blocks_cap(int storage);  // blocks of an assignment launch without a tuned value
 // A batch blur pass's route: its axis (vertical 0: rows, 1: columns), its
@@ -105,7 +105,7 @@ int blur_route(int vertical, int src, int dst, int with_table);
 // One blur pass along `route` of every mapped grid, all of dp channels and
 // `storage`; large: blur_large_working_set holds for the running grids.
 hipError_t launch_blur_batch(const BatchGrid* grids, const uint32_t* map, int blocks, int dp, int storage,
-                             int waves_per_block, int route, int large, hipStream_t stream);
+                             int groups_per_block, int route, int large, hipStream_t stream);
 // One assignment of every mapped grid; each grid's last block runs its
 // control step.
 hipError_t launch_assign_batch(const BatchGrid* grids, const uint32_t* map, int blocks, int dp, int storage,
