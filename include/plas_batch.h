@@ -55,7 +55,7 @@ typedef struct {
     int32_t blur_waves_per_block; /* blur of cells of 16 bytes or more: summing waves per block, each
                                      walking 64/dp lines (with a loading and a storing wave beside
                                      it); 1, 2 or 4; 0: the library's choice */
-    int32_t assign_blocks;        /* blocks per sort for the assignment; 0: the plas_sort default */
+    int32_t assign_blocks;        /* blocks per sort for the assignment; 0: the library's choice */
 } plas_tune_entry;
 
 typedef struct {

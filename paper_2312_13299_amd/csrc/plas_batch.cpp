@@ -21,10 +21,15 @@ using namespace plas_host;
 
 namespace {
 
-constexpr int kDefaultWavesPerBlock = 2;  // as plas_sort
-// Assignment blocks per sort when the tuning table names none (as a lone
-// sort's launch).
-constexpr int kBatchAssignBlocks = 4096;
+// Line groups per block of the blur (ms over 384 reorders of a batch of twelve
+// grids, one / two / four: bfloat16 66 / 71 / 72, float32 131 in all).
+constexpr int kDefaultWavesPerBlock = 1;
+// Assignment blocks of a launch over all sorts, in multiples of a lone sort's:
+// a launch ends with the blocks of several sorts, and shorter ones even that
+// out. Twelve grids of 131^2 to 724^2, ms of assignment over 384 reorders with 1
+// / 2 / 3 / 4 / 6: float32 79 / 76 / 75 / 71 / 72, bfloat16 44 / 39 / 37 / 38 /
+// 41 (4096 blocks for every sort: 145 and 103).
+constexpr int64_t kBatchAssignShare = 4;
 constexpr int kMaxSlots = 1 << 16;     // grid index field of a block map entry
 constexpr int kMaxLocalBlocks = 1 << 16;  // block index field
 
@@ -253,7 +258,7 @@ class BatchRun {
     if (st != PLAS_OK) return fail(h_, st, "bad schedule parameters");
     for (const LevelInfo& lv : s.levels) {
       s.max_cells = std::max<int64_t>(s.max_cells, static_cast<int64_t>(lv.beta) * lv.beta);
-      s.max_items = std::max<int64_t>(s.max_items, lv.groups + lv.singles);
+      s.max_items = std::max(s.max_items, level_items(lv));
     }
     s.max_k = reorder_bound(s.levels.size(), prm_.inv_threshold);
     st = apply_tuning(s);
@@ -279,8 +284,7 @@ class BatchRun {
     g.state = reinterpret_cast<DevState*>(base + o_state);
     g.w = s.w;
     g.blur_blocks = plas::batch_blur_blocks(s.w, s.dp, s.storage, s.wpb, s.max_cells);
-    g.assign_blocks = plas::batch_assign_blocks(s.max_items, s.dp, s.storage,
-                                                s.assign_cap > 0 ? s.assign_cap : kBatchAssignBlocks);
+    // The assignment's share is set with the plan (rebuild).
 
     // Features -> X in T, the start arrangement, G = X[P] (as plas_sort).
     hipStream_t stream = b_->stream;
@@ -469,6 +473,17 @@ class BatchRun {
     // started last would leave the chip to themselves at a launch's end.
     std::stable_sort(run_list_.begin(), run_list_.end(),
                      [&](int a, int c) { return sorts_[a].w > sorts_[c].w; });
+    // Assignment blocks: what the tuning table says, else the sort's share of
+    // the blocks that a launch over all of them takes.
+    int64_t all_items = 0;
+    for (int slot : run_list_) all_items += sorts_[slot].max_items;
+    for (int slot : run_list_) {
+      Sort& s = sorts_[slot];
+      const int64_t most = kBatchAssignShare * static_cast<int64_t>(plas::assign_blocks_cap(s.storage));
+      const int share = static_cast<int>(std::max<int64_t>(1, (most * s.max_items + all_items - 1) / all_items));
+      s.grid.assign_blocks =
+          plas::batch_assign_blocks(s.max_items, s.dp, s.storage, s.assign_cap > 0 ? s.assign_cap : share);
+    }
     const size_t nslots = sorts_.size();
     size_t off = align_up(nslots * sizeof(plas::BatchGrid));
     const size_t o_list = off;

@@ -9,6 +9,14 @@ namespace plas {
 // atomics over (the controller adds them up).
 constexpr int kAccSlots = 32;
 
+// Division by a fixed 1 <= d < 2^31: a / d = (2 a mul) / 2^32 >> shift for 0 <=
+// a < 2^31, with shift = ceil(log2 d) and mul = ceil(2^(31 + shift) / d) (the
+// product is off by a (mul d - 2^(31 + shift)) < 2^31 2^shift).
+struct Divisor {
+  uint32_t mul;
+  uint32_t shift;
+};
+
 // One radius level, prepared on the host (Sec. 3.1): real radius phi, blur
 // half-width r = floor(phi), block side beta = clamp(r + 1, min_block, w),
 // nb = floor(w / beta) blocks per side, floor(beta^2 / 4) groups per block.
@@ -21,6 +29,7 @@ struct LevelInfo {
   int64_t groups_per_block;
   int64_t groups;   // nb^2 * groups_per_block
   int64_t singles;  // cells in no group: w^2 - (nb*beta)^2 + nb^2 * (beta^2 mod 4)
+  Divisor by_gpb, by_nb, by_rest;  // by groups_per_block, nb and w - nb*beta (1 where that is 0)
 };
 
 // Device-resident state of one sort. The parameters block is what every
@@ -39,6 +48,7 @@ struct DevState {
   int64_t groups_per_block;
   int64_t groups;
   int64_t singles;
+  Divisor by_gpb, by_nb, by_rest, by_w;
   uint64_t keys[4];  // round keys of the grouping bijection
   // ---- written by the assignment kernel
   unsigned long long energy_acc[kAccSlots];

@@ -150,7 +150,7 @@ int32_t plas_sort(plas_handle h, const void* features, int64_t n, int32_t d, int
   int64_t max_cells = 0, max_items = 0;
   for (const LevelInfo& lv : levels) {
     max_cells = std::max<int64_t>(max_cells, static_cast<int64_t>(lv.beta) * lv.beta);
-    max_items = std::max<int64_t>(max_items, lv.groups + lv.singles);
+    max_items = std::max(max_items, level_items(lv));
   }
 
   // Workspace.
@@ -456,14 +456,8 @@ static int32_t upload_stage_state(plas_handle h, int32_t side, int32_t beta, int
   LevelInfo lv{};
   lv.phi = static_cast<double>(beta - 1);
   lv.r = beta - 1;
-  lv.beta = beta;
-  lv.nb = side / beta;
-  const int64_t cells = static_cast<int64_t>(beta) * beta;
-  lv.groups_per_block = cells / 4;
-  lv.groups = static_cast<int64_t>(lv.nb) * lv.nb * lv.groups_per_block;
-  const int64_t covered = static_cast<int64_t>(lv.nb) * beta;
-  lv.singles = static_cast<int64_t>(side) * side - covered * covered +
-               static_cast<int64_t>(lv.nb) * lv.nb * (cells % 4);
+  set_blocks(&lv, side, beta);
+  S->by_w = make_divisor(side);
   fill_state_for_level(S, lv);
   for (int i = 0; i < 4; ++i) S->keys[i] = keys[i];
   PLAS_HIP(h, hipMemcpyAsync(h->stage_state.ptr, S, sizeof(DevState), hipMemcpyHostToDevice, h->stream));
@@ -500,7 +494,7 @@ int32_t plas_stage_assign(plas_handle h, void* grid, const void* target, int32_t
   if (st != PLAS_OK) return st;
   DevState* Sd = as<DevState>(h->stage_state);
   PLAS_HIP(h, plas::launch_group_table(as<int32_t>(h->table), Sd, cells, h->stream));
-  const int64_t items = h->state_host->groups + h->state_host->singles;
+  const int64_t items = h->state_host->groups + (h->state_host->singles + 3) / 4;
   PLAS_HIP(h, plas::launch_assign(grid, target, perm, as<int32_t>(h->table), Sd, dp, storage, items, h->stream));
   PLAS_HIP(h, hipMemcpyAsync(h->state_host, Sd, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
   PLAS_HIP(h, hipStreamSynchronize(h->stream));

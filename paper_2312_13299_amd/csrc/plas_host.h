@@ -150,6 +150,34 @@ inline int padded_channels(int d) {
   return dp;
 }
 
+inline plas::Divisor make_divisor(int64_t d) {
+  if (d < 1) d = 1;
+  plas::Divisor v;
+  v.shift = 0;
+  while ((int64_t{1} << v.shift) < d) ++v.shift;
+  v.mul = static_cast<uint32_t>(((uint64_t{1} << (31 + v.shift)) + static_cast<uint64_t>(d) - 1) /
+                                static_cast<uint64_t>(d));
+  return v;
+}
+
+// The block geometry of a level with block side beta on a grid of side w.
+inline void set_blocks(LevelInfo* lv, int32_t w, int32_t beta) {
+  lv->beta = beta;
+  lv->nb = w / beta;
+  const int64_t cells = static_cast<int64_t>(beta) * beta;
+  lv->groups_per_block = cells / 4;
+  lv->groups = static_cast<int64_t>(lv->nb) * lv->nb * lv->groups_per_block;
+  const int64_t covered = static_cast<int64_t>(lv->nb) * beta;
+  lv->singles = static_cast<int64_t>(w) * w - covered * covered +
+                static_cast<int64_t>(lv->nb) * lv->nb * (cells % 4);
+  lv->by_gpb = make_divisor(lv->groups_per_block);
+  lv->by_nb = make_divisor(lv->nb);
+  lv->by_rest = make_divisor(w - covered);
+}
+
+// Items of a level's assignment: its groups, and packs of four singles.
+inline int64_t level_items(const LevelInfo& lv) { return lv.groups + (lv.singles + 3) / 4; }
+
 // The radius schedule of Sec. 3.1 with the block geometry of each level.
 inline int32_t build_schedule(int32_t w, double decay, int32_t min_block, double start_radius,
                        std::vector<LevelInfo>* out) {
@@ -163,14 +191,7 @@ inline int32_t build_schedule(int32_t w, double decay, int32_t min_block, double
     // r beyond w - 1 blurs whole lines; the cap only keeps x + r in range.
     const double rf = std::floor(phi);
     lv.r = rf > 1073741824.0 ? 1073741824 : static_cast<int32_t>(rf);
-    lv.beta = std::min(w, std::max(min_block, lv.r + 1));
-    lv.nb = w / lv.beta;
-    const int64_t cells = static_cast<int64_t>(lv.beta) * lv.beta;
-    lv.groups_per_block = cells / 4;
-    lv.groups = static_cast<int64_t>(lv.nb) * lv.nb * lv.groups_per_block;
-    const int64_t covered = static_cast<int64_t>(lv.nb) * lv.beta;
-    lv.singles = static_cast<int64_t>(w) * w - covered * covered +
-                 static_cast<int64_t>(lv.nb) * lv.nb * (cells % 4);
+    set_blocks(&lv, w, std::min(w, std::max(min_block, lv.r + 1)));
     out->push_back(lv);
     phi = phi * decay;
   }
@@ -284,6 +305,9 @@ inline void fill_state_for_level(DevState* s, const LevelInfo& lv) {
   s->groups_per_block = lv.groups_per_block;
   s->groups = lv.groups;
   s->singles = lv.singles;
+  s->by_gpb = lv.by_gpb;
+  s->by_nb = lv.by_nb;
+  s->by_rest = lv.by_rest;
 }
 
 // The state before a sort's first reorder: level 0 with its block shift
@@ -292,6 +316,7 @@ inline void init_sort_state(DevState* S, int32_t w, int32_t s, const std::vector
                             const plas_sort_params& prm, uint64_t seed) {
   std::memset(S, 0, sizeof(DevState));
   S->w = w;
+  S->by_w = make_divisor(w);
   S->s = s;
   fill_state_for_level(S, levels[0]);
   S->nlevels = static_cast<int32_t>(levels.size());

@@ -30,13 +30,6 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / 64;
 constexpr int kRangeBlocks = 256;
-// Blocks of an assignment launch (its waves stride over the items). 4096 is
-// the measured best over grid sides and storages together: 8192 gains 2 %
-// on a 1024^2 float32 assignment and loses more on 512^2..724^2 grids and
-// on bfloat16.
-#ifndef PLAS_ASSIGN_MAX_BLOCKS
-#define PLAS_ASSIGN_MAX_BLOCKS 4096
-#endif
 constexpr int kMaxGridBlocks = 4096;
 
 inline int blocks_for(int64_t threads, int64_t cap = kMaxGridBlocks) {
@@ -460,8 +453,13 @@ __global__ __launch_bounds__(kBlock) void k_blur(const S* __restrict__ in, S* __
 // Cache hint, measured on whole sorts. The assignment reads every cell of G
 // and T once per reorder, in random group order: streaming (non-temporal)
 // loads keep those reads from evicting what the next blur pass reads (1024^2
-// float32 with normal loads: assignment 109 -> 132 us).
-constexpr bool kAssignStreamLoads = true;
+// float32 with normal loads: assignment 109 -> 132 us). Cells smaller than a
+// 128-byte line share it with neighbours that other groups read, so there the
+// lines stay (2091^2 x 16 float32: 198 -> 187 us; 512^2 x 4: 15.8 -> 14.5).
+template <typename S, int DP>
+constexpr bool assign_stream_loads() {
+  return DP * static_cast<int>(sizeof(S)) >= 128;
+}
 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
@@ -1472,12 +1470,12 @@ __device__ inline unsigned long long wave_sum_u64(unsigned long long v) {
   return v;
 }
 
-
 // The 24 orderings of (0,1,2,3) in lexicographic order as position codes
 // (sigma(i) in bits 2i..2i+1), eight codes per 64-bit word, ordering m in
 // byte m mod 8 of word m / 8:
 //   0123 0132 0213 0231 0312 0321 1023 1032 | 1203 1230 1302 1320 2013 2031
 //   2103 2130 | 2301 2310 3012 3021 3102 3120 3201 3210
+// Ordering 2p + 1 is ordering 2p with its last two places swapped.
 __device__ __forceinline__ uint32_t order_code(int m) {
   constexpr uint64_t kOrders0 = 0xB1E16C9C78D8B4E4ull;
   constexpr uint64_t kOrders1 = 0x36C672D22D8D39C9ull;
@@ -1486,230 +1484,336 @@ __device__ __forceinline__ uint32_t order_code(int m) {
   return static_cast<uint32_t>((word >> (8 * (m & 7))) & 0xff);
 }
 
-// One reorder's blockwise assignment. Items are the groups of every block
-// (item < groups) followed by the cells in no group (singles), whose
-// distance still counts towards the energy. LG = DP / C lanes serve one
-// item, C = assign_channels<S, DP>() (4, or 8 for bfloat16 cells of 8 or
-// more channels): lane `sub` holds channels C*sub .. C*sub+C-1 of the item's
-// four grid cells and four target cells and forms all 16 pair partials as
-// the lowest levels of the channel tree. The rest of the work is split
-// across the LG lanes:
-//  - a transposed butterfly: at tree level b each lane keeps the pairs whose
-//    bit b matches its own lane bit, adds the partner's partial for them and
-//    hands over the others, so after log2(LG) levels lane L holds the exact
-//    distances of pairs q = t*LG + L (each still summed left half + right
-//    half, level by level, as the channel tree prescribes);
-//  - the quantised pair costs go to LDS; lane L evaluates orderings
-//    L, L+LG, ... and the lanes pick the first minimum with a butterfly on
-//    (cost, ordering index).
-// Exact quotient a / d for 0 <= a < 2^31 and 1 <= d < 2^30 from a float64
-// reciprocal: the estimate is off by at most one (relative error of the
-// product below 2^-51), and the remainder's sign fixes it.
-struct FastDiv {
-  uint32_t d;
-  double inv;
-  __device__ __forceinline__ void init(uint32_t divisor) {
-    d = divisor;
-    inv = 1.0 / static_cast<double>(divisor);
-  }
-  __device__ __forceinline__ uint32_t div(uint32_t a) const {
-    uint32_t q = static_cast<uint32_t>(static_cast<double>(a) * inv);
-    const int32_t r = static_cast<int32_t>(a - q * d);
-    if (r < 0)
-      --q;
-    else if (r >= static_cast<int32_t>(d))
-      ++q;
-    return q;
-  }
-};
+// a / d for 0 <= a < 2^31 (Divisor: made by the host).
+__device__ __forceinline__ uint32_t quotient(uint32_t a, Divisor d) { return __umulhi(a << 1, d.mul) >> d.shift; }
 
-// Geometry of one reorder's items, read once per thread. Item indices, cell
-// indices and counts stay below 2^31 (side <= 46340).
+// A value all lanes hold, in a scalar register (the compiler cannot know that
+// of what it loads from the state).
+__device__ __forceinline__ int32_t uniform(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint32_t uniform(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int32_t>(v)));
+}
+__device__ __forceinline__ Divisor uniform(Divisor d) { return Divisor{uniform(d.mul), uniform(d.shift)}; }
+
+// Geometry of one reorder's items, read once per thread. Items are the
+// groups of every block (item < groups), then packs of four cells in no group
+// (singles), whose distance still counts towards the energy. Item indices,
+// cell indices and counts stay below 2^31 (side <= 46340).
 struct ItemGeometry {
   const int32_t* __restrict__ table;
-  int w, beta, nb, dy, dx, R;
-  uint32_t groups, total, strip_rows, strip;
-  FastDiv by_gpb, by_nb, by_w, by_rest;
+  int w, beta, nb, dy, dx, s;
+  uint32_t gpb, groups, singles, total;
+  Divisor by_gpb, by_nb, by_rest, by_w;
 
   __device__ __forceinline__ void init(const DevState* __restrict__ st, const int32_t* __restrict__ tbl) {
     table = tbl;
-    w = st->w;
-    beta = st->beta;
-    nb = st->nb;
-    dy = st->dy;
-    dx = st->dx;
-    R = nb * beta;
-    groups = static_cast<uint32_t>(st->groups);
-    total = static_cast<uint32_t>(st->groups + st->singles);
-    strip_rows = static_cast<uint32_t>(w - R) * static_cast<uint32_t>(w);
-    strip = static_cast<uint32_t>(w) * w - static_cast<uint32_t>(R) * R;
-    by_gpb.init(static_cast<uint32_t>(st->groups_per_block > 0 ? st->groups_per_block : 1));
-    by_nb.init(static_cast<uint32_t>(nb));
-    by_w.init(static_cast<uint32_t>(w));
-    by_rest.init(static_cast<uint32_t>(w - R > 0 ? w - R : 1));
+    w = uniform(st->w);
+    beta = uniform(st->beta);
+    nb = uniform(st->nb);
+    dy = uniform(st->dy);
+    dx = uniform(st->dx);
+    s = uniform(st->s);
+    gpb = uniform(static_cast<uint32_t>(st->groups_per_block));
+    groups = uniform(static_cast<uint32_t>(st->groups));
+    singles = uniform(static_cast<uint32_t>(st->singles));
+    total = groups + (singles + 3) / 4;
+    by_gpb = uniform(st->by_gpb);
+    by_nb = uniform(st->by_nb);
+    by_rest = uniform(st->by_rest);
+    by_w = uniform(st->by_w);
   }
 
-  // The four cells of group `item`, or four times the cell of single `item`
-  // (cells in no group: first the rolled-grid rows below the nb*beta square,
-  // then the columns right of it, then the left-over cell pi(beta^2 - 1) of
-  // each block when beta is odd). Inactive items map to cell 0.
-  __device__ __forceinline__ void cells(uint32_t item, int32_t cell[4]) const {
-    if (item < groups) {
-      const uint32_t b = by_gpb.div(item);
-      const uint32_t g = item - b * by_gpb.d;
-      const int by = static_cast<int>(by_nb.div(b));
-      const int bx = static_cast<int>(b) - by * nb;
-      const int4 t4 = reinterpret_cast<const int4*>(table)[g];
-      const int32_t t[4] = {t4.x, t4.y, t4.z, t4.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        int y = dy + by * beta + (t[i] >> 16);
-        int x = dx + bx * beta + (t[i] & 0xffff);
-        if (y >= w) y -= w;
-        if (x >= w) x -= w;
-        cell[i] = y * w + x;
-      }
-      return;
+  __device__ __forceinline__ int32_t wrapped(int y, int x) const {
+    if (y >= w) y -= w;
+    if (x >= w) x -= w;
+    return y * w + x;
+  }
+  // Where the grid block of group `item` starts (rolled grid), and the
+  // group's first table entry.
+  __device__ __forceinline__ void group_origin(uint32_t item, int& y0, int& x0, uint32_t& entry) const {
+    const uint32_t b = quotient(item, by_gpb);
+    const uint32_t by = quotient(b, by_nb);
+    y0 = dy + static_cast<int>(by) * beta;
+    x0 = dx + static_cast<int>(b - by * static_cast<uint32_t>(nb)) * beta;
+    entry = 4 * (item - b * gpb);
+  }
+  __device__ __forceinline__ int32_t group_cell(int y0, int x0, int32_t t) const {
+    return wrapped(y0 + (t >> 16), x0 + (t & 0xffff));
+  }
+  // Single t: first the rolled-grid rows below the nb*beta square, then the
+  // columns right of it, then the left-over cell pi(beta^2 - 1) of each block
+  // when beta is odd. 0 past the last single.
+  __device__ __forceinline__ int32_t single_cell(uint32_t t) const {
+    if (t >= singles) return 0;
+    const uint32_t R = static_cast<uint32_t>(nb) * beta, W = static_cast<uint32_t>(w);
+    const uint32_t strip_rows = (W - R) * W, strip = W * W - R * R;
+    uint32_t u, v;
+    if (t < strip_rows) {
+      const uint32_t qy = quotient(t, by_w);
+      u = R + qy;
+      v = t - qy * W;
+    } else if (t < strip) {
+      const uint32_t t2 = t - strip_rows;
+      u = quotient(t2, by_rest);
+      v = R + t2 - u * (W - R);
+    } else {
+      const uint32_t b = t - strip;
+      const uint32_t by = quotient(b, by_nb);
+      const int32_t tt = table[static_cast<int64_t>(beta) * beta - 1];
+      u = by * beta + static_cast<uint32_t>(tt >> 16);
+      v = (b - by * static_cast<uint32_t>(nb)) * beta + static_cast<uint32_t>(tt & 0xffff);
     }
-    int32_t p = 0;
-    if (item < total) {
-      const uint32_t t = item - groups;
-      int u, v;
-      if (t < strip) {
-        if (t < strip_rows) {
-          const uint32_t qy = by_w.div(t);
-          u = R + static_cast<int>(qy);
-          v = static_cast<int>(t - qy * by_w.d);
-        } else {
-          const uint32_t t2 = t - strip_rows;
-          const uint32_t qy = by_rest.div(t2);
-          u = static_cast<int>(qy);
-          v = R + static_cast<int>(t2 - qy * by_rest.d);
-        }
-      } else {
-        const uint32_t b = t - strip;
-        const int by = static_cast<int>(by_nb.div(b));
-        const int bx = static_cast<int>(b) - by * nb;
-        const int32_t tt = table[static_cast<int64_t>(beta) * beta - 1];
-        u = by * beta + (tt >> 16);
-        v = bx * beta + (tt & 0xffff);
-      }
-      int y = u + dy, x = v + dx;
-      if (y >= w) y -= w;
-      if (x >= w) x -= w;
-      p = y * w + x;
-    }
-    cell[0] = cell[1] = cell[2] = cell[3] = p;
+    return wrapped(static_cast<int>(u) + dy, static_cast<int>(v) + dx);
   }
 };
 
-// Cross-lane moves within 16-lane rows (DPP): the value of lane i ^ (1 << b).
-// Rows are rotated for b = 2 (i + 4 or i - 4 depending on bit 2) and b = 3.
+// Cross-lane moves within quads (DPP): the value of lane i ^ (1 << B).
 template <int B>
-__device__ __forceinline__ int dpp_xor(int v) {
-  if constexpr (B == 0) {
-    return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
-  } else if constexpr (B == 1) {
-    return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
-  } else if constexpr (B == 2) {
-    const int up = __builtin_amdgcn_update_dpp(0, v, 0x12C, 0xF, 0xF, false);    // row_ror 12: lane i + 4
-    const int down = __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, false);  // row_ror 4: lane i - 4
-    return (__lane_id() & 4) ? down : up;
+__device__ __forceinline__ int quad_xor(int v) {
+  static_assert(B == 0 || B == 1, "within a quad");
+  return __builtin_amdgcn_mov_dpp(v, B == 0 ? 0xB1 : 0x4E, 0xF, 0xF, true);  // quad_perm [1,0,3,2], [2,3,0,1]
+}
+template <int I>
+__device__ __forceinline__ int quad_lane(int v) {  // the value of lane I of the quad
+  return __builtin_amdgcn_mov_dpp(v, I * 0x55, 0xF, 0xF, true);
+}
+// The same for the lane 16 (ROW = 16) or 32 lanes away, as an exchange of
+// whole rows: row halves of a and b meet, so that afterwards a holds, for the
+// lanes with the ROW bit clear, a of both lanes of each pair in a and b.
+template <int ROW>
+__device__ __forceinline__ void row_swap(uint32_t& a, uint32_t& b) {
+  if constexpr (ROW == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
   } else {
-    return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);  // row_ror 8: lane i ^ 8
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
   }
 }
 
-template <int B>
-__device__ __forceinline__ float dpp_xor_f(float v) {
-  return __int_as_float(dpp_xor<B>(__float_as_int(v)));
-}
+// How the lanes of a wave serve items: LG lanes per item, IPW items per wave.
+// Lane bits 0 and 1 are the two lowest bits of the lane's chunk of the cell
+// (so that a quad reads 64 consecutive bytes); the next one or two bits of
+// the chunk are whole rows of lanes (bit 4 and 5), which exchange data with
+// one instruction for two values. The item slot takes the bits between.
+template <int LG>
+struct ItemLanes {
+  static constexpr int kQuad = LG < 4 ? LG : 4;
+  static constexpr int IPW = 64 / LG;
+  static constexpr int kRowA = LG == 16 ? 16 : 32;  // lanes between the halves of chunk bit 2
+  __device__ static __forceinline__ int chunk(int lane) {
+    if constexpr (LG <= 4) return lane % LG;
+    else if constexpr (LG == 8) return (lane & 3) | ((lane >> 3) & 4);
+    else return (lane & 3) | ((lane >> 2) & 12);
+  }
+  __device__ static __forceinline__ int slot(int lane) {
+    if constexpr (LG <= 4) return lane / LG;
+    else if constexpr (LG == 8) return (lane >> 2) & 7;
+    else return (lane >> 2) & 3;
+  }
+};
 
-template <int B>
-__device__ __forceinline__ unsigned long long dpp_xor_u64(unsigned long long v) {
-  const int lo = dpp_xor<B>(static_cast<int>(v & 0xffffffffull));
-  const int hi = dpp_xor<B>(static_cast<int>(v >> 32));
-  return (static_cast<unsigned long long>(static_cast<uint32_t>(hi)) << 32) | static_cast<uint32_t>(lo);
-}
-
-// One level of the transposed butterfly over the item's pair partials: lanes
-// with bit B clear keep the even pairs, the others the odd ones, each adding
-// its partner's partial of the kept pair (partner = lane ^ (1 << B)).
-template <int B, int N>
-__device__ __forceinline__ void transpose_level(float* part, bool upper) {
+// One level of the transposed butterfly over the item's pair partials, chunk
+// bit B: lanes with the bit clear keep the even pairs, the others the odd
+// ones, each adding its partner's partial of the kept pair.
+template <int LG, int B, int N>
+__device__ __forceinline__ void transpose_level(float* part, int lane) {
 #pragma unroll
   for (int t = 0; t < N; ++t) {
-    const float lo = part[2 * t], hi = part[2 * t + 1];
-    const float sum_lo = lo + dpp_xor_f<B>(lo);
-    const float sum_hi = hi + dpp_xor_f<B>(hi);
-    part[t] = upper ? sum_hi : sum_lo;
+    if constexpr (B < 2) {
+      const float lo = part[2 * t], hi = part[2 * t + 1];
+      const float sum_lo = lo + __int_as_float(quad_xor<B>(__float_as_int(lo)));
+      const float sum_hi = hi + __int_as_float(quad_xor<B>(__float_as_int(hi)));
+      part[t] = (lane & (1 << B)) ? sum_hi : sum_lo;
+    } else {
+      uint32_t a = __float_as_uint(part[2 * t]), b = __float_as_uint(part[2 * t + 1]);
+      row_swap<B == 2 ? ItemLanes<LG>::kRowA : 32>(a, b);
+      part[t] = __uint_as_float(a) + __uint_as_float(b);
+    }
   }
 }
 
-// First minimum across the item's lanes at level B: smaller cost, then
-// smaller ordering index.
-template <int B>
-__device__ __forceinline__ void argmin_level(unsigned long long& best, int& best_m) {
-  const unsigned long long oc = dpp_xor_u64<B>(best);
-  const int om = dpp_xor<B>(best_m);
-  if (oc < best || (oc == best && om < best_m)) {
-    best = oc;
-    best_m = om;
+// The smaller of the two keys of each pair of lanes that differ in chunk bit B.
+template <int LG, int B>
+__device__ __forceinline__ unsigned long long min_level(unsigned long long key) {
+  uint32_t lo = static_cast<uint32_t>(key), hi = static_cast<uint32_t>(key >> 32);
+  uint32_t lo2, hi2;
+  if constexpr (B < 2) {
+    lo2 = static_cast<uint32_t>(quad_xor<B>(static_cast<int>(lo)));
+    hi2 = static_cast<uint32_t>(quad_xor<B>(static_cast<int>(hi)));
+  } else {
+    lo2 = lo;
+    hi2 = hi;
+    row_swap<B == 2 ? ItemLanes<LG>::kRowA : 32>(lo, lo2);
+    row_swap<B == 2 ? ItemLanes<LG>::kRowA : 32>(hi, hi2);
   }
+  const unsigned long long a = (static_cast<unsigned long long>(hi) << 32) | lo;
+  const unsigned long long b = (static_cast<unsigned long long>(hi2) << 32) | lo2;
+  return b < a ? b : a;
+}
+template <int LG>
+__device__ __forceinline__ unsigned long long item_min(unsigned long long key) {
+  if constexpr (LG > 1) key = min_level<LG, 0>(key);
+  if constexpr (LG > 2) key = min_level<LG, 1>(key);
+  if constexpr (LG > 4) key = min_level<LG, 2>(key);
+  if constexpr (LG > 8) key = min_level<LG, 3>(key);
+  return key;
 }
 
-// Block `bid` of `nblocks` blocks that share one reorder's items.
+// floor(v 2^s) for 0 <= v with v 2^s < 2^57: v = f 2^e, f in [1/2, 1), f a
+// 24-bit fraction.
+__device__ __forceinline__ unsigned long long quantise(float v, int s) {
+  const uint32_t f = static_cast<uint32_t>(__builtin_amdgcn_frexp_mantf(v) * 4294967296.0f);
+  const int k = 64 - s - __builtin_amdgcn_frexp_expf(v);  // v 2^s = f 2^32 / 2^k (f as 32 bits), k >= 7
+  const unsigned long long q = (static_cast<unsigned long long>(f) << 32) >> (k & 63);
+  return k < 64 ? q : 0ull;
+}
+
+// Blocks are handed to the eight chiplets (each with its own L2) in turn:
+// the place of block `bid` when every chiplet takes a contiguous eighth.
+// Neighbouring groups share the 128-byte lines of their cells' permutation
+// entries and, below 32 channels, of the cells themselves (assignment inside
+// sorts, in turn / contiguous: 512^2 x 4 14.5 / 13.6 us, 723^2 x 64 52.5 /
+// 50.8, 1024^2 x 64 98.6 / 95.7, 2091^2 x 16 187 / 182; 1448^2 x 64 bfloat16
+// 110.5 / 111.8).
+__device__ __forceinline__ int64_t chiplet_order(int64_t bid, int64_t nblocks) {
+  const int64_t each = nblocks >> 3, more = nblocks & 7, chiplet = bid & 7;
+  return chiplet * each + (chiplet < more ? chiplet : more) + (bid >> 3);
+}
+
+// One reorder's blockwise assignment, block `bid` of `nblocks` blocks that
+// share its items. LG = DP / C lanes serve one item, C = assign_channels<S,
+// DP>() (4, or 8 for bfloat16 cells of 8 or more channels): each lane holds C
+// channels of the item's four grid cells and four target cells and forms all
+// 16 pair partials as the lowest levels of the channel tree. The rest of the
+// work is split across the LG lanes:
+//  - a transposed butterfly finishes the tree level by level (each still left
+//    half + right half): after log2(LG) levels the lane with chunk L holds the
+//    exact distances of pairs q = t*LG + L;
+//  - the quantised pair costs go to LDS; chunk L takes the ordered pairs p =
+//    L, L + LG, .. of places for the first two cells, each of which leaves two
+//    orderings (2p, 2p + 1) of the last two, and the lanes pick the first
+//    minimum as the smallest key (cost, ordering).
+// Keys are cost * 32 + ordering. Costs that this would not hold (tiny grids,
+// or distances that are no finite numbers) take a slower way, chosen for a
+// whole wave.
+//
+// What bounds it: on grids beyond the Infinity Cache the grid's and target's
+// cells, read and written at random 4 DP-byte places (1024^2 x 64: 0.75 GB in
+// 95.7 us); below, a wave's chain of dependent loads (table, permutation,
+// cells) and its VALU work per item, which three waves per SIMD and a few
+// long-lived blocks per CU hide best: a block of a single item costs several
+// microseconds of launch and tear-down. Pairs of places instead of all 24
+// orderings, quantising in integers instead of float64, one packed key per
+// ordering and lane swaps in registers instead of LDS shuffles took the VALU
+// work per item to under half (inside sorts, before and after: 64^2 x 64 9.5
+// -> 8.5 us, 512^2 x 4 18.5 -> 13.6, 723^2 x 64 77.6 -> 50.8, 1024^2 x 64
+// 109.7 -> 95.7, 2091^2 x 16 207 -> 182, 1448^2 x 64 bfloat16 129 -> 111).
 template <int DP, typename S>
 __device__ __forceinline__ void assign_items(S* __restrict__ G, const S* __restrict__ T, int32_t* __restrict__ P,
-                                             const int32_t* __restrict__ table, DevState* __restrict__ st,
-                                             int64_t bid, int64_t nblocks) {
+                                             const ItemGeometry& geo, DevState* __restrict__ st, int64_t bid,
+                                             int64_t nblocks) {
   using V = AssignVec<S, DP>;
   using Vec = typename V::T;
   constexpr int LG = DP / assign_channels<S, DP>();
   static_assert(sizeof(Vec) * LG == DP * sizeof(S), "lane vectors must tile a cell");
-  constexpr int IPW = 64 / LG;
-  constexpr int LEVELS = LG == 1 ? 0 : LG == 2 ? 1 : LG == 4 ? 2 : LG == 8 ? 3 : 4;
+  using Lanes = ItemLanes<LG>;
+  constexpr int IPW = Lanes::IPW;
   constexpr int KEEP = 16 / LG;  // pair distances held per lane after the reduction
+  constexpr int kRounds = (12 + LG - 1) / LG;
+  constexpr int kOwn = 4 / Lanes::kQuad;  // cells whose permutation entry a lane moves
   __shared__ unsigned long long s_q[kWavesPerBlock][IPW][16];
-  ItemGeometry geo;
-  geo.init(st, table);
-  const double scale = ldexp(1.0, st->s);
   const int lane = threadIdx.x & 63;
-  const int wib = threadIdx.x >> 6;
-  const int sub = lane % LG, slot = lane / LG;
+  const int wib = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int sub = Lanes::chunk(lane), slot = Lanes::slot(lane);
+  const int ql = lane % Lanes::kQuad;           // this lane's place in its quad (or pair, or alone)
+  const bool owns = sub < Lanes::kQuad;         // one quad of an item moves its permutation entries
   unsigned long long* q_item = s_q[wib][slot];
-  const int64_t wave = (bid * kBlock + threadIdx.x) >> 6;
-  const int64_t nwaves = (nblocks * kBlock) >> 6;
-  const Vec* __restrict__ G4 = reinterpret_cast<const Vec*>(G);
-  const Vec* __restrict__ T4 = reinterpret_cast<const Vec*>(T);
-  Vec* __restrict__ Gout = reinterpret_cast<Vec*>(G);
-  unsigned long long e_acc = 0, m_acc = 0;
+  const int64_t wave = chiplet_order(bid, nblocks) * kWavesPerBlock + wib;
+  const int64_t nwaves = nblocks * kWavesPerBlock;
+  const Vec* __restrict__ G4 = reinterpret_cast<const Vec*>(G) + sub;
+  const Vec* __restrict__ T4 = reinterpret_cast<const Vec*>(T) + sub;
+  Vec* __restrict__ Gout = reinterpret_cast<Vec*>(G) + sub;
+  // Distances from this on take the slower way.
+  const uint32_t slow_from = __float_as_uint(fminf(ldexpf(1.0f, 57 - geo.s), INFINITY));
+  unsigned long long e_acc = 0;
+  uint32_t m_acc = 0;
+
+  // The item's cells: each lane of a quad finds one and the quad shares them.
+  auto find_cells = [&](int64_t first, int32_t (&cell)[4]) {
+    const uint32_t item = static_cast<uint32_t>(first) + slot;
+    int32_t own[kOwn];
+    if (static_cast<uint32_t>(first) + IPW <= geo.groups) {
+      int y0, x0;
+      uint32_t entry;
+      geo.group_origin(item, y0, x0, entry);
+      int32_t t[kOwn];
+      if constexpr (kOwn == 4) {
+        const int4 t4 = *reinterpret_cast<const int4*>(geo.table + entry);
+        t[0] = t4.x, t[1] = t4.y, t[2] = t4.z, t[3] = t4.w;
+      } else {
+#pragma unroll
+        for (int k = 0; k < kOwn; ++k) t[k] = geo.table[entry + ql * kOwn + k];
+      }
+#pragma unroll
+      for (int k = 0; k < kOwn; ++k) own[k] = geo.group_cell(y0, x0, t[k]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < kOwn; ++k) {
+        own[k] = 0;
+        if (item < geo.groups) {
+          int y0, x0;
+          uint32_t entry;
+          geo.group_origin(item, y0, x0, entry);
+          own[k] = geo.group_cell(y0, x0, geo.table[entry + ql * kOwn + k]);
+        } else if (item < geo.total) {
+          own[k] = geo.single_cell(4 * (item - geo.groups) + ql * kOwn + k);
+        }
+      }
+    }
+    if constexpr (kOwn == 4) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) cell[i] = own[i];
+    } else if constexpr (kOwn == 2) {
+      const int32_t other0 = quad_xor<0>(own[0]), other1 = quad_xor<0>(own[1]);
+      cell[0] = ql ? other0 : own[0];
+      cell[1] = ql ? other1 : own[1];
+      cell[2] = ql ? own[0] : other0;
+      cell[3] = ql ? own[1] : other1;
+    } else {
+      cell[0] = quad_lane<0>(own[0]);
+      cell[1] = quad_lane<1>(own[0]);
+      cell[2] = quad_lane<2>(own[0]);
+      cell[3] = quad_lane<3>(own[0]);
+    }
+  };
 
   // Software pipeline: the next item's cells (table reads) are resolved
   // while the current item's grid and target cells are in flight.
   int64_t first = wave * IPW;
   int32_t cell[4];
-  geo.cells(static_cast<uint32_t>(first + slot), cell);
+  if (first < geo.total) find_cells(first, cell);
   for (; first < geo.total; first += nwaves * IPW) {
-    const int64_t item = first + slot;
-    const bool active = item < geo.total;
+    const uint32_t item = static_cast<uint32_t>(first) + slot;
     const bool is_group = item < geo.groups;
     Vec g[4], tg[4];
-    int32_t old_perm[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      g[i] = load_quad<kAssignStreamLoads>(G4 + static_cast<int64_t>(cell[i]) * LG + sub);
-      tg[i] = load_quad<kAssignStreamLoads>(T4 + static_cast<int64_t>(cell[i]) * LG + sub);
+      g[i] = load_quad<assign_stream_loads<S, DP>()>(G4 + static_cast<int64_t>(cell[i]) * LG);
+      tg[i] = load_quad<assign_stream_loads<S, DP>()>(T4 + static_cast<int64_t>(cell[i]) * LG);
     }
-    if (sub == 0 && is_group) {
+    int32_t own_perm[kOwn];
+    if (owns && is_group) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) old_perm[i] = P[cell[i]];
+      for (int k = 0; k < kOwn; ++k) {
+        const int i = ql * kOwn + k;
+        own_perm[k] = P[i == 0 ? cell[0] : i == 1 ? cell[1] : i == 2 ? cell[2] : cell[3]];
+      }
     }
-    int32_t next_cell[4];
-    {
-      const int64_t next = first + nwaves * IPW + slot;
-      geo.cells(next < geo.total ? static_cast<uint32_t>(next) : geo.total, next_cell);
-    }
+    int32_t next_cell[4] = {0, 0, 0, 0};
+    if (first + nwaves * IPW < geo.total) find_cells(first + nwaves * IPW, next_cell);
 
     // Pair q = 4i + j: grid cell i against target cell j.
     float part[16];
@@ -1717,65 +1821,105 @@ __device__ __forceinline__ void assign_items(S* __restrict__ G, const S* __restr
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < 4; ++j) part[4 * i + j] = V::sq(g[i], tg[j]);
-    if constexpr (LEVELS > 0) transpose_level<0, 8>(part, sub & 1);
-    if constexpr (LEVELS > 1) transpose_level<1, 4>(part, sub & 2);
-    if constexpr (LEVELS > 2) transpose_level<2, 2>(part, sub & 4);
-    if constexpr (LEVELS > 3) transpose_level<3, 1>(part, sub & 8);
+    if constexpr (LG > 1) transpose_level<LG, 0, 8>(part, lane);
+    if constexpr (LG > 2) transpose_level<LG, 1, 4>(part, lane);
+    if constexpr (LG > 4) transpose_level<LG, 2, 2>(part, lane);
+    if constexpr (LG > 8) transpose_level<LG, 3, 1>(part, lane);
+    uint32_t most = 0;
 #pragma unroll
-    for (int t = 0; t < KEEP; ++t)
-      q_item[t * LG + sub] = static_cast<unsigned long long>(static_cast<double>(part[t]) * scale);
-    wave_lds_sync();
+    for (int t = 0; t < KEEP; ++t) most = max(most, __float_as_uint(part[t]));
 
-    // Orderings sub, sub + LG, ...: this lane's first minimum.
-    unsigned long long best = ~0ull;
-    int best_m = 24;
+    unsigned long long cost;  // of the ordering taken
+    int best_m;
+    if (__builtin_expect(__ballot(most >= slow_from) == 0, 1)) {
 #pragma unroll
-    for (int m0 = 0; m0 < 24; m0 += LG) {
-      const int m = m0 + sub;
-      if (m < 24) {
-        const uint32_t code = order_code(m);
-        const unsigned long long cost = q_item[0 + (code & 3)] + q_item[4 + ((code >> 2) & 3)] +
-                                        q_item[8 + ((code >> 4) & 3)] + q_item[12 + ((code >> 6) & 3)];
-        if (cost < best) {
-          best = cost;
-          best_m = m;
+      for (int t = 0; t < KEEP; ++t) q_item[t * LG + sub] = quantise(part[t], geo.s);
+      wave_lds_sync();
+      unsigned long long key = ~0ull;
+#pragma unroll
+      for (int k = 0; k < kRounds; ++k) {
+        const int p = k * LG + sub;
+        const uint32_t code = order_code(2 * (p < 12 ? p : 0));
+        const unsigned long long* qa = q_item + (code & 3);
+        const unsigned long long* qb = q_item + 4 + ((code >> 2) & 3);
+        const unsigned long long* qc = q_item + 8 + ((code >> 4) & 3);
+        const unsigned long long* qd = q_item + 8 + ((code >> 6) & 3);
+        const unsigned long long straight = qc[0] + qd[4], swapped = qd[0] + qc[4];
+        const bool swap = swapped < straight;
+        const unsigned long long k_p = ((qa[0] + qb[0] + (swap ? swapped : straight)) << 5) | (2 * p + (swap ? 1 : 0));
+        if (p < 12 && k_p < key) key = k_p;
+      }
+      key = item_min<LG>(key);
+      best_m = static_cast<int>(key & 31);
+      cost = key >> 5;
+      if (static_cast<uint32_t>(first) + IPW > geo.groups && !is_group) {
+        // Four singles (or fewer, or none) keep their places.
+        best_m = 0;
+        cost = 0;
+        if (item < geo.total)
+          for (int i = 0; i < 4; ++i)
+            if (4 * (item - geo.groups) + i < geo.singles) cost += q_item[5 * i];
+      }
+    } else {
+      const double scale = ldexp(1.0, geo.s);
+      for (int t = 0; t < KEEP; ++t)
+        q_item[t * LG + sub] = static_cast<unsigned long long>(static_cast<double>(part[t]) * scale);
+      wave_lds_sync();
+      cost = ~0ull;
+      best_m = 24;
+      if (is_group) {
+        for (int m = 0; m < 24; ++m) {
+          const uint32_t code = order_code(m);
+          const unsigned long long c = q_item[code & 3] + q_item[4 + ((code >> 2) & 3)] +
+                                       q_item[8 + ((code >> 4) & 3)] + q_item[12 + ((code >> 6) & 3)];
+          if (c < cost) {
+            cost = c;
+            best_m = m;
+          }
         }
+      } else {
+        best_m = 0;
+        cost = 0;
+        if (item < geo.total)
+          for (int i = 0; i < 4; ++i)
+            if (4 * (item - geo.groups) + i < geo.singles) cost += q_item[5 * i];
       }
     }
-    // First minimum across the item's lanes: smaller cost, then smaller index.
-    if constexpr (LEVELS > 0) argmin_level<0>(best, best_m);
-    if constexpr (LEVELS > 1) argmin_level<1>(best, best_m);
-    if constexpr (LEVELS > 2) argmin_level<2>(best, best_m);
-    if constexpr (LEVELS > 3) argmin_level<3>(best, best_m);
-    const unsigned long long self_cost = q_item[0];
     wave_lds_sync();
 
-    if (is_group && best_m != 0) {
+    if (best_m != 0) {
       const uint32_t code = order_code(best_m);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int to = (code >> (2 * i)) & 3;
         if (to != i) {
           const int32_t dst = to == 0 ? cell[0] : to == 1 ? cell[1] : to == 2 ? cell[2] : cell[3];
-          Gout[static_cast<int64_t>(dst) * LG + sub] = g[i];
-          if (sub == 0) {
-            P[dst] = old_perm[i];
+          Gout[static_cast<int64_t>(dst) * LG] = g[i];
+        }
+      }
+      if (owns) {
+#pragma unroll
+        for (int k = 0; k < kOwn; ++k) {
+          const int i = ql * kOwn + k;
+          const int to = (code >> (2 * i)) & 3;
+          if (to != i) {
+            P[to == 0 ? cell[0] : to == 1 ? cell[1] : to == 2 ? cell[2] : cell[3]] = own_perm[k];
             ++m_acc;
           }
         }
       }
     }
-    if (active && sub == 0) e_acc += is_group ? best : self_cost;
+    e_acc += cost;
 #pragma unroll
     for (int i = 0; i < 4; ++i) cell[i] = next_cell[i];
   }
   // One pair of atomics per block: waves reduce, then the block.
   __shared__ unsigned long long s_sum[2][kWavesPerBlock];
-  e_acc = wave_sum_u64(e_acc);
-  m_acc = wave_sum_u64(m_acc);
+  e_acc = wave_sum_u64(sub == 0 ? e_acc : 0ull);
+  const unsigned long long moved = wave_sum_u64(m_acc);
   if (lane == 0) {
     s_sum[0][wib] = e_acc;
-    s_sum[1][wib] = m_acc;
+    s_sum[1][wib] = moved;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -1803,29 +1947,24 @@ __device__ void prepare_step(DevState* __restrict__ st, const LevelInfo* __restr
 __device__ void reorder_done(DevState* __restrict__ st, const LevelInfo* __restrict__ levels,
                              plas_level_out* __restrict__ trace, uint32_t nblocks);
 
-#ifndef PLAS_ASSIGN_WAVES_PER_EU
-#define PLAS_ASSIGN_WAVES_PER_EU 4
-#endif
-
-// Occupancy target of the assignment kernels. One wave less per SIMD (more
-// registers per lane) where the default would spill to scratch: 8-channel
-// bfloat16 lanes hold twice the raw cell data, and with one or two lanes
-// per item a lane keeps most of the 16 pair costs and orderings itself.
-template <typename S, int DP>
-constexpr int assign_waves_per_eu() {
-  constexpr int lanes = DP / assign_channels<S, DP>();
-  constexpr bool wide = lanes <= 2 || assign_channels<S, DP>() == 8;
-  return wide && PLAS_ASSIGN_WAVES_PER_EU > 1 ? PLAS_ASSIGN_WAVES_PER_EU - 1 : PLAS_ASSIGN_WAVES_PER_EU;
-}
+// Waves per SIMD the assignment kernels keep room for in registers: more do
+// not help (see assign_blocks_cap), and with four some lane layouts spill.
+constexpr int kAssignWavesPerEu = 3;
 
 template <int DP, typename S>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(assign_waves_per_eu<S, DP>())))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kAssignWavesPerEu)))
 void k_assign(S* __restrict__ G, const S* __restrict__ T, int32_t* __restrict__ P,
               const int32_t* __restrict__ table, DevState* __restrict__ st,
               const LevelInfo* __restrict__ levels, plas_level_out* __restrict__ trace, int control) {
+  ItemGeometry geo;
+  geo.init(st, table);
   if (st->done) return;
-  if (control && blockIdx.x == 0 && threadIdx.x == 0) prepare_step(st, levels);
-  assign_items<DP, S>(G, T, P, table, st, blockIdx.x, gridDim.x);
+  // With control, block 0 prepares the control step and the others assign.
+  const int64_t bid = static_cast<int64_t>(blockIdx.x) - control;
+  if (bid >= 0)
+    assign_items<DP, S>(G, T, P, geo, st, bid, static_cast<int64_t>(gridDim.x) - control);
+  else if (threadIdx.x < 64)
+    prepare_step(st, levels);
   if (control && threadIdx.x < 64) reorder_done(st, levels, trace, gridDim.x);
 }
 
@@ -1926,16 +2065,10 @@ __global__ __launch_bounds__(kBlock) void k_vad_finish(const double* __restrict_
 // draws a new shift; a stall right after a new shift ends the level
 // (phi <- decay * phi, precomputed in `levels`). The block shift number
 // st.j, the grouping keys of reorder st.k + 1 and the next level come
-// prepared in st.next_* (none depends on E). trace may be NULL.
+// prepared in st.next_* (none depends on E). E, moved: the reorder's sums.
+// trace may be NULL.
 __device__ void control_step(DevState& st, const LevelInfo* __restrict__ levels,
-                             plas_level_out* __restrict__ trace) {
-  unsigned long long E = 0, moved = 0;
-  for (int i = 0; i < kAccSlots; ++i) {
-    E += st.energy_acc[i];
-    moved += st.moved_acc[i];
-    st.energy_acc[i] = 0;
-    st.moved_acc[i] = 0;
-  }
+                             plas_level_out* __restrict__ trace, unsigned long long E, unsigned long long moved) {
   st.blocks_done = 0;
   st.k += 1;
   st.level_reorders += 1;
@@ -1973,6 +2106,9 @@ __device__ void control_step(DevState& st, const LevelInfo* __restrict__ levels,
       st.groups_per_block = lv.groups_per_block;
       st.groups = lv.groups;
       st.singles = lv.singles;
+      st.by_gpb = lv.by_gpb;
+      st.by_nb = lv.by_nb;
+      st.by_rest = lv.by_rest;
       st.dy = st.next_dy;
       st.dx = st.next_dx;
       st.j += 1;
@@ -1993,29 +2129,39 @@ __device__ void control_step(DevState& st, const LevelInfo* __restrict__ levels,
     for (int i = 0; i < 4; ++i) st.keys[i] = st.next_keys[i];
 }
 
-// What the control step of the running reorder may need, prepared by one
-// thread of the assignment's first block before its items: block shift
-// number j, the grouping keys of reorder k + 1, the next level. Written
-// with device-scope atomic exchanges, made where every block's atomics meet
-// and complete (their results returned) before that thread takes its
-// block's ticket, so the last block, which reads the state after every
+// What the control step of the running reorder may need, prepared by the
+// first wave of a block of the assignment launch that does nothing else (the
+// draws take longer than a block's share of a small grid): block shift number
+// j (lane 0), the grouping keys of reorder k + 1 (lane 1), the next level.
+// Written with device-scope atomic exchanges, made where every block's
+// atomics meet and complete (their results returned) before that wave takes
+// its block's ticket, so the last block, which reads the state after every
 // ticket, sees them.
 __device__ void prepare_step(DevState* __restrict__ st, const LevelInfo* __restrict__ levels) {
-  int32_t dy, dx;
-  block_shift(st->seed, st->j, st->w, &dy, &dx);
-  const Words4 keys = draw(st->seed, kDrawGrouping, static_cast<uint64_t>(st->k + 1));
-  __hip_atomic_exchange(&st->next_dy, dy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_exchange(&st->next_dx, dx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  for (int i = 0; i < 4; ++i)
-    __hip_atomic_exchange(&st->next_keys[i], keys.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int lane = threadIdx.x & 63;
+  const Words4 u = draw(st->seed, lane == 0 ? kDrawShift : kDrawGrouping,
+                        lane == 0 ? st->j : static_cast<uint64_t>(st->k + 1));
+  uint64_t old = 0;  // what the exchanges return: waiting for it is waiting for them
+  if (lane == 0) {
+    int32_t dy, dx;
+    scale_shift_words(u, st->w, &dy, &dx);
+    old |= static_cast<uint32_t>(__hip_atomic_exchange(&st->next_dy, dy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    old |= static_cast<uint32_t>(__hip_atomic_exchange(&st->next_dx, dx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  } else if (lane == 1) {
+    for (int i = 0; i < 4; ++i)
+      old |= __hip_atomic_exchange(&st->next_keys[i], u.v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   const int next = st->level + 1;
   if (next < st->nlevels) {
     static_assert(sizeof(LevelInfo) % 4 == 0, "level copied as 32-bit words");
+    constexpr int kWords = sizeof(LevelInfo) / 4;
+    static_assert(kWords <= 64, "one word per lane");
     const uint32_t* src = reinterpret_cast<const uint32_t*>(levels + next);
     uint32_t* dst = reinterpret_cast<uint32_t*>(&st->next_level);
-    for (int i = 0; i < static_cast<int>(sizeof(LevelInfo) / 4); ++i)
-      __hip_atomic_exchange(dst + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane < kWords)
+      old |= __hip_atomic_exchange(dst + lane, src[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  asm volatile("s_waitcnt vmcnt(0)" : : "v"(old) : "memory");
 }
 
 // The end of a reorder's assignment launch, run by the first wave of every
@@ -2045,7 +2191,16 @@ __device__ void reorder_done(DevState* __restrict__ st, const LevelInfo* __restr
   for (int i = lane; i < kWords; i += 64)
     words[i] = __hip_atomic_load(gwords + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   wave_lds_sync();
-  if (lane == 0) control_step(s_st, levels, trace);
+  // Energy slots by the lower half of the wave, moved counts by the upper.
+  static_assert(kAccSlots == 32, "one slot per lane of a half");
+  unsigned long long* acc = (lane < kAccSlots ? s_st.energy_acc : s_st.moved_acc) + lane % kAccSlots;
+  unsigned long long sum = *acc;
+  *acc = 0;
+#pragma unroll
+  for (int m = kAccSlots / 2; m >= 1; m >>= 1) sum += __shfl_xor(sum, m);
+  const unsigned long long moved = __shfl(sum, kAccSlots);
+  wave_lds_sync();
+  if (lane == 0) control_step(s_st, levels, trace, sum, moved);
   wave_lds_sync();
   for (int i = lane; i < kWords; i += 64) gwords[i] = words[i];
 }
@@ -2142,15 +2297,19 @@ __global__ __launch_bounds__(kBlock) void k_blur_batch(const BatchGrid* __restri
 // Every block of a sort adds its sums; the last one of the sort runs its
 // control step.
 template <int DP, typename S>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(assign_waves_per_eu<S, DP>())))
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kAssignWavesPerEu)))
 void k_assign_batch(const BatchGrid* __restrict__ grids, const uint32_t* __restrict__ map) {
   uint32_t local;
   const BatchGridView& g = batch_grid(grids, map, local);
   DevState* st = global_ptr<DevState>(g.state);
+  ItemGeometry geo;
+  geo.init(st, global_ptr<const int32_t>(g.table));
   if (st->done) return;
-  if (local == 0 && threadIdx.x == 0) prepare_step(st, global_ptr<const LevelInfo>(g.levels));
-  assign_items<DP, S>(global_ptr<S>(g.G), global_ptr<const S>(g.T), global_ptr<int32_t>(g.P),
-                      global_ptr<const int32_t>(g.table), st, local, g.assign_blocks);
+  if (local > 0)
+    assign_items<DP, S>(global_ptr<S>(g.G), global_ptr<const S>(g.T), global_ptr<int32_t>(g.P), geo, st,
+                        static_cast<int64_t>(local) - 1, static_cast<int64_t>(g.assign_blocks) - 1);
+  else if (threadIdx.x < 64)
+    prepare_step(st, global_ptr<const LevelInfo>(g.levels));
   if (threadIdx.x < 64)
     reorder_done(st, global_ptr<const LevelInfo>(g.levels), global_ptr<plas_level_out>(g.trace),
                  static_cast<uint32_t>(g.assign_blocks));
@@ -2416,9 +2575,9 @@ hipError_t launch_assign(void* G, const void* T, int32_t* P, const int32_t* tabl
                          int storage, int64_t max_items, hipStream_t stream, const ControlArgs* control) {
   const int64_t items_per_wave = assign_items_per_wave(dp, storage);
   const int64_t waves = (max_items + items_per_wave - 1) / items_per_wave;
-  const int blocks = blocks_for(waves * 64, assign_blocks_cap(storage));
   const ControlArgs ca = control != nullptr ? *control : ControlArgs{};
   const int with_control = control != nullptr ? 1 : 0;
+  const int blocks = blocks_for(waves * 64, assign_blocks_cap(storage)) + with_control;
   PLAS_DISPATCH_STORAGE(storage, {
     PLAS_DISPATCH_DP(dp, (k_assign<DPV, SV><<<blocks, kBlock, 0, stream>>>(
                              static_cast<SV*>(G), static_cast<const SV*>(T), P, table, st, ca.levels, ca.trace,
@@ -2495,13 +2654,17 @@ int batch_blur_blocks(int w, int dp, int storage, int groups_per_block, int64_t 
 int batch_assign_blocks(int64_t max_items, int dp, int storage, int cap) {
   const int64_t items_per_wave = assign_items_per_wave(dp, storage);
   const int64_t waves = (max_items + items_per_wave - 1) / items_per_wave;
-  return blocks_for(waves * 64, cap > 0 ? cap : assign_blocks_cap(storage));
+  return blocks_for(waves * 64, cap > 0 ? cap : assign_blocks_cap(storage)) + 1;
 }
 
-int assign_blocks_cap(int storage) {
-  (void)storage;
-  return PLAS_ASSIGN_MAX_BLOCKS;
-}
+// Blocks of an assignment launch (its waves stride over the items). A block
+// begins and ends with a chain of dependent memory accesses (state, table,
+// sums, ticket) of several us, so few blocks that run all along beat many:
+// two per CU in float32, three in bfloat16, whose waves hold half the bytes
+// in flight. 512 / 768 / 1024 / 2048 / 4096 blocks, us per assignment inside
+// sorts: 723^2 x 64 float32 53 / 54 / 53 / 58 / 71, 1024^2 x 64 98 / 101 / 101
+// / 99 / 101, 1448^2 x 64 bfloat16 116 / 111 / 127 / 114 / 118.
+int assign_blocks_cap(int storage) { return storage == kStorageBF16 ? 768 : 512; }
 
 template <typename S, int DP>
 hipError_t blur_batch_dp(const BatchGrid* grids, const uint32_t* map, int blocks, int groups_per_block,

@@ -66,8 +66,9 @@ struct ControlArgs {
   plas_level_out* trace;
 };
 
-// One blockwise assignment with the parameters in st. max_items bounds
-// groups + singles over every level this launch may see. With `control`,
+// One blockwise assignment with the parameters in st. max_items bounds the
+// items (groups, and packs of four singles) of every level this launch may
+// see. With `control`,
 // the last block to finish runs the control step of the reorder on st in
 // place (the energy and moved sums, the stall test, the schedule, the next
 // shift and grouping keys); without it, st keeps the sums for the caller.

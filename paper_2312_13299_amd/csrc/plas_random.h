@@ -115,13 +115,15 @@ struct Bijection {
   }
 };
 
-// Block shift of draw j on a grid of side w: the top 32 bits of the first
-// two words scaled to [0, w).
-__host__ __device__ inline void block_shift(uint64_t seed, uint64_t j, int32_t w, int32_t* dy,
-                                            int32_t* dx) {
-  const Words4 u = draw(seed, kDrawShift, j);
+// Block shift of draw j on a grid of side w: the top 32 bits of the draw's
+// first two words scaled to [0, w).
+__host__ __device__ inline void scale_shift_words(const Words4& u, int32_t w, int32_t* dy, int32_t* dx) {
   *dy = static_cast<int32_t>(((u.v[0] >> 32) * static_cast<uint64_t>(w)) >> 32);
   *dx = static_cast<int32_t>(((u.v[1] >> 32) * static_cast<uint64_t>(w)) >> 32);
+}
+__host__ __device__ inline void block_shift(uint64_t seed, uint64_t j, int32_t w, int32_t* dy,
+                                            int32_t* dx) {
+  scale_shift_words(draw(seed, kDrawShift, j), w, dy, dx);
 }
 
 }  // namespace plas
