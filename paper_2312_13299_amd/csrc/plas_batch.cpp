@@ -286,23 +286,16 @@ class BatchRun {
     g.blur_blocks = plas::batch_blur_blocks(s.w, s.dp, s.storage, s.wpb, s.max_cells);
     // The assignment's share is set with the plan (rebuild).
 
-    // Features -> X in T, the start arrangement, G = X[P] (as plas_sort).
+    // The start arrangement and the features in its order (as plas_sort).
     hipStream_t stream = b_->stream;
-    st = ingest_features(h_, it.features, it.dtype, s.n, s.d, it.layout, s.dp, s.storage, g.T, &s.s);
+    st = reserve_query(h_, s.dp);
     if (st != PLAS_OK) return finish_failed(s, st);
-    if (it.init_perm != nullptr) {
-      st = check_permutation(h_, it.init_perm, s.n, static_cast<int32_t*>(g.H));
-      if (st != PLAS_OK) return finish_failed(s, st);
-      PLAS_HIP(h_, hipMemcpyAsync(g.P, it.init_perm, static_cast<size_t>(s.n) * sizeof(int32_t),
-                                  hipMemcpyDeviceToDevice, stream));
-    } else {
-      const plas::Words4 k0 = plas::draw(it.seed, plas::kDrawStart, 0);
-      PLAS_HIP(h_, plas::launch_start_perm(g.P, s.n, k0.v, stream));
-    }
-    PLAS_HIP(h_, plas::launch_gather(g.T, g.P, g.G, s.n, s.dp, s.storage, stream));
-    const std::vector<float> inv = inverse_counts(s.w);
-    PLAS_HIP(h_, hipMemcpyAsync(base + o_inv, inv.data(), inv.size() * sizeof(float), hipMemcpyHostToDevice,
-                                stream));
+    const IngestPlan plan{g.G, static_cast<int32_t*>(g.H), as<float>(h_->range_part), as<plas::QueryOut>(h_->query)};
+    st = queue_start(h_, it.features, it.dtype, s.n, s.d, s.w, it.layout, s.dp, s.storage, it.init_perm, it.seed,
+                     g.P, plan, reinterpret_cast<float*>(base + o_inv));
+    if (st == PLAS_OK) st = read_query(h_, plan.out);
+    if (st != PLAS_OK) return finish_failed(s, st);
+    s.s = h_->query_host->s;
     PLAS_HIP(h_, hipMemcpyAsync(base + o_levels, s.levels.data(), nl * sizeof(LevelInfo), hipMemcpyHostToDevice,
                                 stream));
     PLAS_HIP(h_, hipMemsetAsync(base + o_trace, 0, nl * sizeof(plas_level_out), stream));

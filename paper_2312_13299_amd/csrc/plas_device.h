@@ -1,6 +1,8 @@
 // plas_device.h -- data shared by the PLAS kernels and the host engine.
 #pragma once
 
+#include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace plas {
@@ -8,6 +10,20 @@ namespace plas {
 // Number of separate energy accumulators the assignment kernel spreads its
 // atomics over (the controller adds them up).
 constexpr int kAccSlots = 32;
+
+// The energy's fixed-point scale 2^s from the features' ranges: the largest s
+// for which n times the largest possible squared distance stays below 2^61.
+__host__ __device__ inline int32_t scale_shift(const float* mins, const float* maxs, int32_t d, int64_t n) {
+  double dmax = 0.0;
+  for (int32_t c = 0; c < d; ++c) {
+    const double span = static_cast<double>(maxs[c]) - static_cast<double>(mins[c]);
+    dmax += span * span;
+  }
+  if (!(dmax > 0.0)) return 0;
+  int e = 0;
+  (void)frexp(static_cast<double>(n) * dmax, &e);
+  return 61 - e;
+}
 
 // Division by a fixed 1 <= d < 2^31: a / d = (2 a mul) / 2^32 >> shift for 0 <=
 // a < 2^31, with shift = ceil(log2 d) and mul = ceil(2^(31 + shift) / d) (the

@@ -81,7 +81,7 @@ int32_t plas_create(plas_handle* out, int32_t device) {
     delete h;
     return PLAS_ERR_HIP;
   }
-  bool ok = hipHostMalloc(reinterpret_cast<void**>(&h->range_host), (2 * 64 + 1) * sizeof(float)) == hipSuccess &&
+  bool ok = hipHostMalloc(reinterpret_cast<void**>(&h->query_host), sizeof(plas::QueryOut)) == hipSuccess &&
             hipHostMalloc(reinterpret_cast<void**>(&h->u64_host), 16 * sizeof(unsigned long long)) == hipSuccess &&
             hipHostMalloc(reinterpret_cast<void**>(&h->state_host), sizeof(DevState)) == hipSuccess &&
             reserve(h->state, sizeof(DevState)) == hipSuccess &&
@@ -109,10 +109,10 @@ int32_t plas_destroy(plas_handle h) {
   for (hipEvent_t e : h->events) (void)hipEventDestroy(e);
   release_batch_state(h);
   DeviceBuffer* bufs[] = {&h->grid_g, &h->grid_h, &h->grid_t, &h->perm, &h->table, &h->inv,
-                          &h->range_part, &h->range_out, &h->levels, &h->trace, &h->state,
+                          &h->range_part, &h->query, &h->levels, &h->trace, &h->state,
                           &h->stage_state, &h->scratch, &h->vad};
   for (DeviceBuffer* b : bufs) release(*b);
-  if (h->range_host) (void)hipHostFree(h->range_host);
+  if (h->query_host) (void)hipHostFree(h->query_host);
   if (h->u64_host) (void)hipHostFree(h->u64_host);
   if (h->state_host) (void)hipHostFree(h->state_host);
   delete h;
@@ -156,35 +156,33 @@ int32_t plas_sort(plas_handle h, const void* features, int64_t n, int32_t d, int
   // Workspace.
   int32_t s = 0;
   const int32_t storage = prm.storage;
-  st = prepare_features(h, features, dtype, n, d, layout, dp, storage, &s);
-  if (st != PLAS_OK) return st;
+  const size_t grid_bytes = static_cast<size_t>(n) * dp * storage_bytes(storage);
+  PLAS_HIP(h, reserve(h->grid_g, grid_bytes));
+  PLAS_HIP(h, reserve(h->grid_h, grid_bytes));
+  PLAS_HIP(h, reserve(h->grid_t, grid_bytes));
   PLAS_HIP(h, reserve(h->perm, static_cast<size_t>(n) * sizeof(int32_t)));
   PLAS_HIP(h, reserve(h->table, static_cast<size_t>(max_cells) * sizeof(int32_t)));
   PLAS_HIP(h, reserve(h->levels, levels.size() * sizeof(LevelInfo)));
   PLAS_HIP(h, reserve(h->trace, levels.size() * sizeof(plas_level_out)));
-  st = upload_inverse_counts(h, w);
+  PLAS_HIP(h, reserve(h->inv, static_cast<size_t>(w + 1) * sizeof(float)));
+  st = reserve_query(h, dp);
+  if (st != PLAS_OK) return st;
+  void* G = h->grid_g.ptr;
+  void* H = h->grid_h.ptr;
+  void* T = h->grid_t.ptr;
+  int32_t* P = as<int32_t>(h->perm);
+
+  // The start arrangement and the features in its order.
+  const IngestPlan plan{G, static_cast<int32_t*>(H), as<float>(h->range_part), as<plas::QueryOut>(h->query)};
+  st = queue_start(h, features, dtype, n, d, w, layout, dp, storage, prm.init_perm, prm.seed, P, plan,
+                   as<float>(h->inv));
   if (st != PLAS_OK) return st;
   PLAS_HIP(h, hipMemcpyAsync(h->levels.ptr, levels.data(), levels.size() * sizeof(LevelInfo),
                              hipMemcpyHostToDevice, h->stream));
   PLAS_HIP(h, hipMemsetAsync(h->trace.ptr, 0, levels.size() * sizeof(plas_level_out), h->stream));
-
-  void* G = h->grid_g.ptr;
-  void* H = h->grid_h.ptr;
-  void* T = h->grid_t.ptr;  // holds X until the gather
-  int32_t* P = as<int32_t>(h->perm);
-
-  // Start arrangement: the caller's, or the keyed bijection of draw
-  // (seed, 0, 0) (random positions, Sec. 3.1).
-  if (prm.init_perm != nullptr) {
-    st = check_permutation(h, prm.init_perm, n, as<int32_t>(h->grid_h));
-    if (st != PLAS_OK) return st;
-    PLAS_HIP(h, hipMemcpyAsync(P, prm.init_perm, static_cast<size_t>(n) * sizeof(int32_t),
-                               hipMemcpyDeviceToDevice, h->stream));
-  } else {
-    const plas::Words4 k0 = plas::draw(prm.seed, plas::kDrawStart, 0);
-    PLAS_HIP(h, plas::launch_start_perm(P, n, k0.v, h->stream));
-  }
-  PLAS_HIP(h, plas::launch_gather(T, P, G, n, dp, storage, h->stream));
+  st = read_query(h, plan.out);
+  if (st != PLAS_OK) return st;
+  s = h->query_host->s;
 
   // First reorder's state.
   DevState* S = h->state_host;
@@ -298,6 +296,31 @@ int32_t plas_sort(plas_handle h, const void* features, int64_t n, int32_t d, int
   return PLAS_OK;
 }
 
+// An energy query on grids plan.G, H and T: everything is queued before the
+// one wait, so a permutation that is none and features that are not finite
+// run through the passes (every place they lead to is inside the grids) and
+// are reported from the flags at the end.
+static int32_t query_energy(plas_handle h, const void* features, const int32_t* perm, int64_t n, int32_t d,
+                            int32_t side, int32_t layout, int32_t dtype, int32_t storage, int32_t radius,
+                            const IngestPlan& plan, void* H, void* T, float* inv, uint64_t* energy_fixed,
+                            int32_t* scale_shift_out, double* energy_mean) {
+  const int dp = padded_channels(d);
+  void* G = plan.G;
+  int32_t st = queue_arranged(h, features, dtype, n, d, side, layout, dp, storage, perm, plan, inv);
+  if (st != PLAS_OK) return st;
+  PLAS_HIP(h, plas::launch_blur_pass(G, H, side, dp, storage, nullptr, radius, 0, inv, h->stream));
+  PLAS_HIP(h, plas::launch_blur_pass(H, T, side, dp, storage, nullptr, radius, 1, inv, h->stream));
+  PLAS_HIP(h, plas::launch_energy(G, T, n, dp, storage, 0, &plan.out->s, &plan.out->energy, h->stream));
+  st = read_query(h, plan.out);
+  if (st != PLAS_OK) return st;
+  const uint64_t E = h->query_host->energy;
+  const int32_t s = h->query_host->s;
+  if (energy_fixed) *energy_fixed = E;
+  if (scale_shift_out) *scale_shift_out = s;
+  if (energy_mean) *energy_mean = std::ldexp(static_cast<double>(E), -s) / static_cast<double>(n);
+  return PLAS_OK;
+}
+
 int32_t plas_grid_energy(plas_handle h, const void* features, const int32_t* perm, int64_t n, int32_t d,
                          int32_t side, int32_t layout, int32_t dtype, int32_t storage, int32_t radius,
                          uint64_t* energy_fixed, int32_t* scale_shift_out, double* energy_mean) {
@@ -309,39 +332,24 @@ int32_t plas_grid_energy(plas_handle h, const void* features, const int32_t* per
   DeviceScope scope(h->device);
   if (!scope.ok()) return fail(h, PLAS_ERR_HIP, "hipSetDevice failed");
   const int dp = padded_channels(d);
-  int32_t s = 0;
-  st = prepare_features(h, features, dtype, n, d, layout, dp, storage, &s);
+  const size_t grid_bytes = static_cast<size_t>(n) * dp * storage_bytes(storage);
+  PLAS_HIP(h, reserve(h->grid_g, grid_bytes));
+  PLAS_HIP(h, reserve(h->grid_h, grid_bytes));
+  PLAS_HIP(h, reserve(h->grid_t, grid_bytes));
+  PLAS_HIP(h, reserve(h->inv, static_cast<size_t>(side + 1) * sizeof(float)));
+  st = reserve_query(h, dp);
   if (st != PLAS_OK) return st;
-  if (perm != nullptr) {
-    st = check_permutation(h, perm, n, as<int32_t>(h->grid_h));
-    if (st != PLAS_OK) return st;
-  }
-  st = upload_inverse_counts(h, side);
-  if (st != PLAS_OK) return st;
-  void* G = h->grid_g.ptr;
-  void* H = h->grid_h.ptr;
-  void* T = h->grid_t.ptr;
-  PLAS_HIP(h, plas::launch_gather(T, perm, G, n, dp, storage, h->stream));
-  PLAS_HIP(h, plas::launch_blur_pass(G, H, side, dp, storage, nullptr, radius, 0, as<float>(h->inv), h->stream));
-  PLAS_HIP(h, plas::launch_blur_pass(H, T, side, dp, storage, nullptr, radius, 1, as<float>(h->inv), h->stream));
-  unsigned long long* acc = as<unsigned long long>(h->scratch);
-  PLAS_HIP(h, hipMemsetAsync(acc, 0, sizeof(unsigned long long), h->stream));
-  PLAS_HIP(h, plas::launch_energy(G, T, n, dp, storage, s, acc, h->stream));
-  PLAS_HIP(h, hipMemcpyAsync(h->u64_host, acc, sizeof(unsigned long long), hipMemcpyDeviceToHost, h->stream));
-  PLAS_HIP(h, hipStreamSynchronize(h->stream));
-  const uint64_t E = h->u64_host[0];
-  if (energy_fixed) *energy_fixed = E;
-  if (scale_shift_out) *scale_shift_out = s;
-  if (energy_mean) *energy_mean = std::ldexp(static_cast<double>(E), -s) / static_cast<double>(n);
-  return PLAS_OK;
+  const IngestPlan plan{h->grid_g.ptr, as<int32_t>(h->grid_h), as<float>(h->range_part),
+                        as<plas::QueryOut>(h->query)};
+  return query_energy(h, features, perm, n, d, side, layout, dtype, storage, radius, plan, h->grid_h.ptr,
+                      h->grid_t.ptr, as<float>(h->inv), energy_fixed, scale_shift_out, energy_mean);
 }
 
 int32_t plas_grid_energy_noalloc(plas_handle h, const void* features, const int32_t* perm, int64_t n, int32_t d,
                                  int32_t side, int32_t layout, int32_t dtype, int32_t storage, int32_t radius,
                                  uint64_t* energy_fixed, int32_t* scale_shift_out, double* energy_mean) {
   // plas_grid_energy's steps on the device's static scratch (no allocation,
-  // no memset): ingest into T, range and scale, permutation check (counts in
-  // H), 1/c table, gather into G, rows into H, columns into T, energy.
+  // no memset).
   using L = plas::NoAllocLayout;
   int32_t st = check_features(h, features, n, d, side, layout, dtype);
   if (st != PLAS_OK) return st;
@@ -353,47 +361,12 @@ int32_t plas_grid_energy_noalloc(plas_handle h, const void* features, const int3
   DeviceScope scope(h->device);
   if (!scope.ok()) return fail(h, PLAS_ERR_HIP, "hipSetDevice failed");
   char* base = static_cast<char*>(h->noalloc);
-  void* G = base + L::kG;
-  void* H = base + L::kH;
-  void* T = base + L::kT;
-  float* range_part = reinterpret_cast<float*>(base + L::kRangePart);
-  float* range_out = reinterpret_cast<float*>(base + L::kRangeOut);
-  unsigned long long* acc = reinterpret_cast<unsigned long long*>(base + L::kFlags);
-  int32_t* flag = reinterpret_cast<int32_t*>(base + L::kFlags + 8);
-  float* inv = reinterpret_cast<float*>(base + L::kInv);
-  const int dp = padded_channels(d);
-
-  PLAS_HIP(h, plas::launch_ingest(features, dtype == PLAS_DTYPE_BF16, n, d, layout, dp, storage, T, h->stream));
-  PLAS_HIP(h, plas::launch_range(T, n, d, dp, storage, range_part, range_out, h->stream));
-  PLAS_HIP(h, hipMemcpyAsync(h->range_host, range_out, (2 * dp + 1) * sizeof(float), hipMemcpyDeviceToHost,
-                             h->stream));
-  PLAS_HIP(h, hipStreamSynchronize(h->stream));
-  if (h->range_host[2 * dp] != 0.0f) return fail(h, PLAS_ERR_NONFINITE, "features contain NaN or infinity");
-  const int32_t s = scale_shift(h->range_host, h->range_host + dp, d, n);
-  if (perm != nullptr) {
-    int32_t* counts = static_cast<int32_t*>(H);
-    PLAS_HIP(h, plas::launch_fill_u32(reinterpret_cast<uint32_t*>(counts), n, 0u, h->stream));
-    PLAS_HIP(h, plas::launch_fill_u32(reinterpret_cast<uint32_t*>(flag), 1, 0u, h->stream));
-    PLAS_HIP(h, plas::launch_check_perm(perm, n, counts, flag, h->stream));
-    PLAS_HIP(h, hipMemcpyAsync(h->u64_host, flag, sizeof(int32_t), hipMemcpyDeviceToHost, h->stream));
-    PLAS_HIP(h, hipStreamSynchronize(h->stream));
-    int32_t bad = 0;
-    std::memcpy(&bad, h->u64_host, sizeof(int32_t));
-    if (bad != 0) return fail(h, PLAS_ERR_INVALID_ARGUMENT, "permutation is not a bijection of [0, n)");
-  }
-  PLAS_HIP(h, plas::launch_inverse_counts(inv, side, h->stream));
-  PLAS_HIP(h, plas::launch_gather(T, perm, G, n, dp, storage, h->stream));
-  PLAS_HIP(h, plas::launch_blur_pass(G, H, side, dp, storage, nullptr, radius, 0, inv, h->stream));
-  PLAS_HIP(h, plas::launch_blur_pass(H, T, side, dp, storage, nullptr, radius, 1, inv, h->stream));
-  PLAS_HIP(h, plas::launch_fill_u32(reinterpret_cast<uint32_t*>(acc), 2, 0u, h->stream));
-  PLAS_HIP(h, plas::launch_energy(G, T, n, dp, storage, s, acc, h->stream));
-  PLAS_HIP(h, hipMemcpyAsync(h->u64_host, acc, sizeof(unsigned long long), hipMemcpyDeviceToHost, h->stream));
-  PLAS_HIP(h, hipStreamSynchronize(h->stream));
-  const uint64_t E = h->u64_host[0];
-  if (energy_fixed) *energy_fixed = E;
-  if (scale_shift_out) *scale_shift_out = s;
-  if (energy_mean) *energy_mean = std::ldexp(static_cast<double>(E), -s) / static_cast<double>(n);
-  return PLAS_OK;
+  const IngestPlan plan{base + L::kG, reinterpret_cast<int32_t*>(base + L::kH),
+                        reinterpret_cast<float*>(base + L::kRangePart),
+                        reinterpret_cast<plas::QueryOut*>(base + L::kOut)};
+  return query_energy(h, features, perm, n, d, side, layout, dtype, storage, radius, plan, base + L::kH,
+                      base + L::kT, reinterpret_cast<float*>(base + L::kInv), energy_fixed, scale_shift_out,
+                      energy_mean);
 }
 
 int32_t plas_vad(plas_handle h, const void* features, const int32_t* perm, int64_t n, int32_t d, int32_t side,
@@ -406,8 +379,14 @@ int32_t plas_vad(plas_handle h, const void* features, const int32_t* perm, int64
   if (!scope.ok()) return fail(h, PLAS_ERR_HIP, "hipSetDevice failed");
   if (perm != nullptr) {
     PLAS_HIP(h, reserve(h->grid_h, static_cast<size_t>(n) * sizeof(int32_t)));
-    st = check_permutation(h, perm, n, as<int32_t>(h->grid_h));
-    if (st != PLAS_OK) return st;
+    PLAS_HIP(h, reserve(h->query, sizeof(plas::QueryOut)));
+    plas::QueryOut* out = as<plas::QueryOut>(h->query);
+    PLAS_HIP(h, plas::launch_check_perm(perm, n, as<int32_t>(h->grid_h), out, h->stream));
+    PLAS_HIP(h, hipMemcpyAsync(&h->query_host->bad_perm, &out->bad_perm, sizeof(int32_t), hipMemcpyDeviceToHost,
+                               h->stream));
+    PLAS_HIP(h, hipStreamSynchronize(h->stream));
+    if (h->query_host->bad_perm != 0)
+      return fail(h, PLAS_ERR_INVALID_ARGUMENT, "permutation is not a bijection of [0, n)");
   }
   const size_t parts = plas::vad_partial_doubles();
   PLAS_HIP(h, reserve(h->vad, (parts + 2) * sizeof(double)));
@@ -516,8 +495,8 @@ int32_t plas_stage_energy(plas_handle h, const void* grid, const void* target, i
   DeviceScope scope(h->device);
   unsigned long long* acc = as<unsigned long long>(h->scratch);
   PLAS_HIP(h, hipMemsetAsync(acc, 0, sizeof(unsigned long long), h->stream));
-  PLAS_HIP(h, plas::launch_energy(grid, target, static_cast<int64_t>(side) * side, dp, storage, scale_shift_in, acc,
-                                  h->stream));
+  PLAS_HIP(h, plas::launch_energy(grid, target, static_cast<int64_t>(side) * side, dp, storage, scale_shift_in,
+                                  nullptr, acc, h->stream));
   PLAS_HIP(h, hipMemcpyAsync(h->u64_host, acc, sizeof(unsigned long long), hipMemcpyDeviceToHost, h->stream));
   PLAS_HIP(h, hipStreamSynchronize(h->stream));
   if (energy) *energy = h->u64_host[0];
@@ -529,7 +508,7 @@ int32_t plas_stage_bijection(plas_handle h, int64_t n, const uint64_t round_keys
   if (out == nullptr || round_keys == nullptr || n < 1 || n > 2147483647LL)
     return fail(h, PLAS_ERR_INVALID_ARGUMENT, "bad bijection arguments");
   DeviceScope scope(h->device);
-  PLAS_HIP(h, plas::launch_start_perm(out, n, round_keys, h->stream));
+  PLAS_HIP(h, plas::launch_start_perm(out, nullptr, n, round_keys, h->stream));
   PLAS_HIP(h, hipStreamSynchronize(h->stream));
   return PLAS_OK;
 }
@@ -563,7 +542,7 @@ int32_t plas_scale_shift_from_ranges(const float* mins, const float* maxs, int32
                                      int32_t* scale_shift_out) {
   if (mins == nullptr || maxs == nullptr || d < 1 || n < 1 || scale_shift_out == nullptr)
     return PLAS_ERR_INVALID_ARGUMENT;
-  *scale_shift_out = scale_shift(mins, maxs, d, n);
+  *scale_shift_out = plas::scale_shift(mins, maxs, d, n);
   return PLAS_OK;
 }
 

@@ -53,7 +53,8 @@ struct plas_context {
   plas_host::DeviceBuffer perm;                    // int32[n]
   plas_host::DeviceBuffer table;                   // int32[beta^2]
   plas_host::DeviceBuffer inv;                     // float32 1/c, c = 0..w
-  plas_host::DeviceBuffer range_part, range_out;   // range pass scratch and result
+  plas_host::DeviceBuffer range_part;              // ingest scratch: range partials
+  plas_host::DeviceBuffer query;                   // QueryOut of an ingest or energy query
   plas_host::DeviceBuffer levels;                  // LevelInfo[levels]
   plas_host::DeviceBuffer trace;                   // plas_level_out[levels]
   plas_host::DeviceBuffer state;                   // DevState of a sort
@@ -62,7 +63,7 @@ struct plas_context {
   plas_host::DeviceBuffer vad;                     // VAD partial sums and results
   void* noalloc = nullptr;                         // the device's scratch of plas_grid_energy_noalloc
   // Pinned host memory for small read-backs.
-  float* range_host = nullptr;
+  plas::QueryOut* query_host = nullptr;
   unsigned long long* u64_host = nullptr;
   DevState* state_host = nullptr;
   std::vector<hipEvent_t> events;
@@ -198,18 +199,6 @@ inline int32_t build_schedule(int32_t w, double decay, int32_t min_block, double
   return PLAS_OK;
 }
 
-inline int32_t scale_shift(const float* mins, const float* maxs, int32_t d, int64_t n) {
-  double dmax = 0.0;
-  for (int32_t c = 0; c < d; ++c) {
-    const double span = static_cast<double>(maxs[c]) - static_cast<double>(mins[c]);
-    dmax += span * span;
-  }
-  if (!(dmax > 0.0)) return 0;
-  int e = 0;
-  (void)std::frexp(static_cast<double>(n) * dmax, &e);
-  return 61 - e;
-}
-
 inline bool valid_layout(int32_t layout) { return layout == PLAS_LAYOUT_CN || layout == PLAS_LAYOUT_NC; }
 
 // Shared argument checks of plas_sort and plas_grid_energy.
@@ -228,46 +217,63 @@ inline int32_t check_features(plas_context* h, const void* features, int64_t n, 
   return PLAS_OK;
 }
 
-// Ingest + range + scale shift into X (device [n][dp] in `storage`, cell-major
-// padded features). Returns NONFINITE if a value is not finite.
-inline int32_t ingest_features(plas_context* h, const void* features, int32_t dtype, int64_t n, int32_t d,
-                               int32_t layout, int dp, int32_t storage, void* X, int32_t* s_out) {
-  PLAS_HIP(h, reserve(h->range_part, plas::range_partial_floats(dp) * sizeof(float)));
-  PLAS_HIP(h, reserve(h->range_out, (2 * 64 + 1) * sizeof(float)));
-  PLAS_HIP(h, plas::launch_ingest(features, dtype == PLAS_DTYPE_BF16, n, d, layout, dp, storage, X, h->stream));
-  PLAS_HIP(h, plas::launch_range(X, n, d, dp, storage, as<float>(h->range_part), as<float>(h->range_out),
-                                 h->stream));
-  PLAS_HIP(h, hipMemcpyAsync(h->range_host, h->range_out.ptr, (2 * dp + 1) * sizeof(float),
-                             hipMemcpyDeviceToHost, h->stream));
-  PLAS_HIP(h, hipStreamSynchronize(h->stream));
-  if (h->range_host[2 * dp] != 0.0f)
-    return fail(h, PLAS_ERR_NONFINITE, "features contain NaN or infinity");
-  *s_out = scale_shift(h->range_host, h->range_host + dp, d, n);
+// Where an ingest works: the arranged grid, the inverse permutation's scratch
+// (int32[n]; may be a grid that is written later), the range partials and the
+// results.
+struct IngestPlan {
+  void* G;
+  int32_t* inv;
+  float* part;
+  plas::QueryOut* out;
+};
+
+// The context's range scratch and query results.
+inline int32_t reserve_query(plas_context* h, int dp) {
+  PLAS_HIP(h, reserve(h->range_part, plas::ingest_partial_floats(dp) * sizeof(float)));
+  PLAS_HIP(h, reserve(h->query, sizeof(plas::QueryOut)));
   return PLAS_OK;
 }
 
-// The context's three working grids, with X in grid_t.
-inline int32_t prepare_features(plas_context* h, const void* features, int32_t dtype, int64_t n, int32_t d,
-                                int32_t layout, int dp, int32_t storage, int32_t* s_out) {
-  const size_t grid_bytes = static_cast<size_t>(n) * dp * storage_bytes(storage);
-  PLAS_HIP(h, reserve(h->grid_g, grid_bytes));
-  PLAS_HIP(h, reserve(h->grid_h, grid_bytes));
-  PLAS_HIP(h, reserve(h->grid_t, grid_bytes));
-  return ingest_features(h, features, dtype, n, d, layout, dp, storage, h->grid_t.ptr, s_out);
+// Queues: features arranged by perm (device int32[n], checked; NULL: in
+// order) into the plan's grid in `storage`, with their range, scale and flags.
+// counts: the register blur kernel's 1/c table to fill (NULL: none).
+inline int32_t queue_arranged(plas_context* h, const void* features, int32_t dtype, int64_t n, int32_t d,
+                              int32_t side, int32_t layout, int dp, int32_t storage, const int32_t* perm,
+                              const IngestPlan& plan, float* counts) {
+  PLAS_HIP(h, plas::launch_begin(plan.out, perm, n, plan.inv, counts, side, h->stream));
+  PLAS_HIP(h, plas::launch_ingest(features, dtype == PLAS_DTYPE_BF16, n, d, layout, dp, storage,
+                                  perm != nullptr ? plan.inv : nullptr, perm, plan.G, plan.part, plan.out,
+                                  h->stream));
+  return PLAS_OK;
 }
 
-// Validate a caller permutation (device int32[n]); counts: device scratch of
-// n int32.
-inline int32_t check_permutation(plas_context* h, const int32_t* perm, int64_t n, int32_t* counts) {
-  int32_t* flag = reinterpret_cast<int32_t*>(as<unsigned long long>(h->scratch) + 8);
-  PLAS_HIP(h, hipMemsetAsync(counts, 0, static_cast<size_t>(n) * sizeof(int32_t), h->stream));
-  PLAS_HIP(h, hipMemsetAsync(flag, 0, sizeof(int32_t), h->stream));
-  PLAS_HIP(h, plas::launch_check_perm(perm, n, counts, flag, h->stream));
-  PLAS_HIP(h, hipMemcpyAsync(h->u64_host, flag, sizeof(int32_t), hipMemcpyDeviceToHost, h->stream));
+// As queue_arranged for a sort's start, and P: the caller's arrangement (init,
+// checked), or if that is NULL the keyed bijection of draw (seed, 0, 0)
+// (random positions, Sec. 3.1).
+inline int32_t queue_start(plas_context* h, const void* features, int32_t dtype, int64_t n, int32_t d, int32_t side,
+                           int32_t layout, int dp, int32_t storage, const int32_t* init, uint64_t seed, int32_t* P,
+                           const IngestPlan& plan, float* counts) {
+  if (init != nullptr) {
+    PLAS_HIP(h, hipMemcpyAsync(P, init, static_cast<size_t>(n) * sizeof(int32_t), hipMemcpyDeviceToDevice,
+                               h->stream));
+    return queue_arranged(h, features, dtype, n, d, side, layout, dp, storage, P, plan, counts);
+  }
+  PLAS_HIP(h, plas::launch_begin(plan.out, nullptr, n, nullptr, counts, side, h->stream));
+  const plas::Words4 k0 = plas::draw(seed, plas::kDrawStart, 0);
+  PLAS_HIP(h, plas::launch_start_perm(P, plan.inv, n, k0.v, h->stream));
+  PLAS_HIP(h, plas::launch_ingest(features, dtype == PLAS_DTYPE_BF16, n, d, layout, dp, storage, plan.inv, nullptr,
+                                  plan.G, plan.part, plan.out, h->stream));
+  return PLAS_OK;
+}
+
+// Reads the results of what is queued (to h->query_host) and reports features
+// that are not finite and permutations that are none.
+inline int32_t read_query(plas_context* h, const plas::QueryOut* out) {
+  PLAS_HIP(h, hipMemcpyAsync(h->query_host, out, sizeof(plas::QueryOut), hipMemcpyDeviceToHost, h->stream));
   PLAS_HIP(h, hipStreamSynchronize(h->stream));
-  int32_t bad = 0;
-  std::memcpy(&bad, h->u64_host, sizeof(int32_t));
-  if (bad != 0) return fail(h, PLAS_ERR_INVALID_ARGUMENT, "permutation is not a bijection of [0, n)");
+  if (h->query_host->bad_value != 0) return fail(h, PLAS_ERR_NONFINITE, "features contain NaN or infinity");
+  if (h->query_host->bad_perm != 0)
+    return fail(h, PLAS_ERR_INVALID_ARGUMENT, "permutation is not a bijection of [0, n)");
   return PLAS_OK;
 }
 

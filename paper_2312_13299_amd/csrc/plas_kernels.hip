@@ -1,5 +1,5 @@
 // plas_kernels.hip -- gfx950 kernels of one PLAS sort (Sec. 3.1 of arXiv
-// 2312.13299): ingest, range, start arrangement, gather, separable box blur,
+// 2312.13299): start arrangement, ingest with the range, separable box blur,
 // grouping table, blockwise assignment with its energy, and the controller.
 //
 // Working layout: a grid is [n][DP], cell-major, DP a power of two (4..64)
@@ -29,8 +29,11 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kWavesPerBlock = kBlock / 64;
-constexpr int kRangeBlocks = 256;
+constexpr int kIngestTile = 4096;   // values of an ingest tile
+constexpr int kFinishBlock = 1024;  // threads of the ingest's last fold
 constexpr int kMaxGridBlocks = 4096;
+constexpr int kEnergyBlocks = 512;  // blocks of an energy sum
+constexpr int kEnergyFlight = 4;    // cells in flight per lane there
 
 inline int blocks_for(int64_t threads, int64_t cap = kMaxGridBlocks) {
   int64_t b = (threads + kBlock - 1) / kBlock;
@@ -75,152 +78,221 @@ struct Storage<uint16_t> {
   }
 };
 
-// ----------------------------------------------------------------- ingest
+// ------------------------------------------------- arrangement and ingest
 
-// Channel-major [d][n] -> [n][DP]: a 64-cell tile goes through LDS so that
-// both the reads (64 consecutive cells of one channel) and the writes
-// (64 consecutive cells of DP channels) are contiguous.
-template <int DP, typename SI, typename SO>
-__global__ __launch_bounds__(kBlock) void k_ingest_cn(const SI* __restrict__ F, int64_t n, int d,
-                                                      SO* __restrict__ X) {
-  __shared__ float tile[DP][65];
-  const int64_t n0 = static_cast<int64_t>(blockIdx.x) * 64;
-  for (int e = threadIdx.x; e < DP * 64; e += kBlock) {
-    const int c = e >> 6, i = e & 63;
-    const int64_t cell = n0 + i;
-    tile[c][i] = (c < d && cell < n) ? Storage<SI>::widen(F[static_cast<int64_t>(c) * n + cell]) : 0.0f;
-  }
-  __syncthreads();
-  for (int e = threadIdx.x; e < DP * 64; e += kBlock) {
-    const int i = e / DP, c = e % DP;
-    const int64_t cell = n0 + i;
-    if (cell < n) X[cell * DP + c] = Storage<SO>::narrow(tile[c][i]);
-  }
-}
-
-template <int DP, typename SI, typename SO>
-__global__ __launch_bounds__(kBlock) void k_ingest_nc(const SI* __restrict__ F, int64_t n, int d,
-                                                      SO* __restrict__ X) {
-  const int64_t total = n * DP;
+// Before an ingest: clears the query's results, fills the 1/c table (if
+// `counts` is given: c = 0..w) and inverts a caller's permutation (if given).
+// Entries that no in-range value of perm names keep what inv held before;
+// the ingest finds them (arranged_place).
+__global__ __launch_bounds__(kBlock) void k_begin(QueryOut* __restrict__ out, const int32_t* __restrict__ perm,
+                                                  int64_t n, int32_t* __restrict__ inv, float* __restrict__ counts,
+                                                  int w) {
   const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-  for (int64_t e = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; e < total; e += stride) {
-    const int64_t cell = e / DP;
-    const int c = static_cast<int>(e % DP);
-    X[e] = Storage<SO>::narrow(c < d ? Storage<SI>::widen(F[cell * d + c]) : 0.0f);
+  const int64_t first = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+  if (first == 0) {
+    out->bad_value = 0;
+    out->bad_perm = 0;
+    out->energy = 0;
+  }
+  if (counts != nullptr)
+    for (int64_t c = first; c <= w; c += stride) counts[c] = c == 0 ? 0.0f : 1.0f / static_cast<float>(c);
+  if (perm != nullptr)
+    for (int64_t p = first; p < n; p += stride) {
+      const int32_t v = perm[p];
+      if (v >= 0 && v < n) inv[v] = static_cast<int32_t>(p);
+    }
+}
+
+// P[p] = f(p), the keyed bijection of the start arrangement, and its inverse
+// (inv NULL: not).
+__global__ __launch_bounds__(kBlock) void k_start_perm(int32_t* __restrict__ P, int32_t* __restrict__ inv, int64_t n,
+                                                       Words4 keys) {
+  const Bijection f(static_cast<uint64_t>(n), keys.v);
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
+  for (int64_t p = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; p < n; p += stride) {
+    const int32_t v = static_cast<int32_t>(f(static_cast<uint64_t>(p)));
+    P[p] = v;
+    if (inv != nullptr) inv[v] = static_cast<int32_t>(p);
   }
 }
 
-// ------------------------------------------------------------------ range
+// Cell i's place under perm, from the inverse k_begin wrote: `at` = inv[i] if
+// perm really holds i there, else -1. If that succeeds for all n cells, perm
+// takes all n values, so it is a bijection; if perm is one, k_begin wrote
+// every entry and it succeeds for all. No counting, no atomics (1024^2 cells:
+// 41 us of counters alone before).
+__device__ __forceinline__ int32_t arranged_place(const int32_t* __restrict__ perm, int64_t n, int64_t i,
+                                                  int32_t at) {
+  return at >= 0 && at < n && perm[at] == i ? at : -1;
+}
 
-// Each thread owns one channel (the grid stride is a multiple of DP), so a
-// block reduces to DP partial min/max values in LDS.
-template <int DP, typename S>
-__global__ __launch_bounds__(kBlock) void k_range_partial(const S* __restrict__ X, int64_t n,
-                                                          float* __restrict__ part) {
-  __shared__ float s_lo[kBlock], s_hi[kBlock], s_bad[kBlock];
+// The check alone: sets *bad if perm is not a bijection.
+__global__ __launch_bounds__(kBlock) void k_check_inverse(const int32_t* __restrict__ perm,
+                                                          const int32_t* __restrict__ inv, int64_t n,
+                                                          int32_t* __restrict__ bad) {
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
+  bool wrong = false;
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < n; i += stride)
+    wrong |= arranged_place(perm, n, i, inv[i]) < 0;
+  if (__any(wrong) && (threadIdx.x & 63) == 0) atomicOr(bad, 1);
+}
+
+// features -> G: G[inv[i]] = features[i] (inv NULL: G[i]), padded to DP
+// channels and rounded to the storage, with the range of the stored values
+// per channel and the check of perm (NULL: not checked) on the way. Tiles of
+// 4096 / DP cells go through LDS, so that the reads (64 consecutive cells of
+// one channel, or whole cells one after the other) and the writes (whole
+// cells) are both contiguous; a block loads its next tile while it stores
+// this one. A thread stores one channel, so a block's range reduces over
+// every DP-th thread; a NaN counts as an infinite maximum.
+//
+// Bound by memory: each value is read once and written once, at its place in
+// the arranged grid, and the check's random reads ride along (1024^2 x 59
+// float32 under a permutation: 112 us and 6 for the fold of the ranges, 4.6
+// TB/s; ingest, range, its fold, permutation check and gather took 130, 380,
+// 65, 41 and more, and 83 us as passes of their own).
+template <int DP, typename SI, typename SO, int LAYOUT>
+__global__ __launch_bounds__(kBlock) void k_ingest(const SI* __restrict__ F, int64_t n, int d,
+                                                   const int32_t* __restrict__ inv, const int32_t* __restrict__ perm,
+                                                   SO* __restrict__ G, float* __restrict__ part,
+                                                   QueryOut* __restrict__ out) {
+  constexpr int kTile = kIngestTile / DP;             // cells
+  constexpr int kEach = kIngestTile / kBlock;         // values per thread
+  constexpr int kPlaces = (kTile + kBlock - 1) / kBlock;
+  constexpr int kPitch = LAYOUT == 0 ? kTile + 1 : DP;
+  __shared__ float tile[LAYOUT == 0 ? DP * kPitch : kIngestTile];
+  __shared__ int32_t s_at[kTile];
+  __shared__ float s_lo[kBlock], s_hi[kBlock];
   const int t = threadIdx.x;
-  float lo = INFINITY, hi = -INFINITY, bad = 0.0f;
-  const int64_t total = n * DP;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-  for (int64_t e = static_cast<int64_t>(blockIdx.x) * kBlock + t; e < total; e += stride) {
-    const float v = Storage<S>::widen(X[e]);
-    if (!__builtin_isfinite(v)) bad = 1.0f;
-    lo = fminf(lo, v);
-    hi = fmaxf(hi, v);
-  }
-  s_lo[t] = lo;
-  s_hi[t] = hi;
-  s_bad[t] = bad;
-  __syncthreads();
-  for (int s = kBlock / 2; s >= DP; s >>= 1) {
-    if (t < s) {
-      s_lo[t] = fminf(s_lo[t], s_lo[t + s]);
-      s_hi[t] = fmaxf(s_hi[t], s_hi[t + s]);
-      s_bad[t] = fmaxf(s_bad[t], s_bad[t + s]);
+  const int64_t tiles = (n + kTile - 1) / kTile;
+  SI value[kEach];
+  int32_t at[kPlaces];
+  // CN: thread t loads cells t % kTile of channels t / kTile + ..; NC: the
+  // tile's d values per cell are one run.
+  auto load = [&](int64_t index) {
+    const int64_t n0 = index * kTile;
+    const int cells = static_cast<int>(n - n0 < kTile ? n - n0 : kTile);
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+      const int e = k * kBlock + t;
+      value[k] = SI(0);
+      if constexpr (LAYOUT == 0) {
+        const int c = e / kTile, i = e % kTile;
+        if (c < d && i < cells) value[k] = F[static_cast<int64_t>(c) * n + n0 + i];
+      } else {
+        if (e < cells * d) value[k] = F[n0 * d + e];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kPlaces; ++k) {
+      const int i = k * kBlock + t;
+      at[k] = -1;
+      if (i < cells) at[k] = inv != nullptr ? inv[n0 + i] : static_cast<int32_t>(n0 + i);
+    }
+  };
+  const int c = t % DP;
+  float lo = INFINITY, hi = -INFINITY;
+  bool wrong = false;
+  int64_t index = blockIdx.x;
+  if (index < tiles) load(index);
+  for (; index < tiles; index += gridDim.x) {
+    const int64_t n0 = index * kTile;
+    const int cells = static_cast<int>(n - n0 < kTile ? n - n0 : kTile);
+    if (perm != nullptr) {
+#pragma unroll
+      for (int k = 0; k < kPlaces; ++k) {
+        const int i = k * kBlock + t;
+        if (i < cells) {
+          at[k] = arranged_place(perm, n, n0 + i, at[k]);
+          wrong |= at[k] < 0;
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+      const int e = k * kBlock + t;
+      const float v = Storage<SI>::widen(value[k]);
+      if constexpr (LAYOUT == 0)
+        tile[(e / kTile) * kPitch + e % kTile] = v;
+      else
+        tile[e] = v;
+    }
+#pragma unroll
+    for (int k = 0; k < kPlaces; ++k)
+      if (k * kBlock + t < kTile) s_at[k * kBlock + t] = at[k];
+    __syncthreads();
+    if (index + gridDim.x < tiles) load(index + gridDim.x);
+#pragma unroll
+    for (int k = 0; k < kEach; ++k) {
+      const int i = k * (kBlock / DP) + t / DP;
+      if (i < cells) {
+        float v;
+        if constexpr (LAYOUT == 0)
+          v = tile[c * kPitch + i];
+        else
+          v = c < d ? tile[i * d + c] : 0.0f;
+        const SO stored = Storage<SO>::narrow(v);
+        const float r = Storage<SO>::widen(stored);
+        lo = fminf(lo, r);
+        hi = r == r ? fmaxf(hi, r) : INFINITY;
+        const int32_t place = s_at[i];
+        if (place >= 0) G[static_cast<int64_t>(place) * DP + c] = stored;
+      }
     }
     __syncthreads();
   }
-  if (t < DP) {
-    float* out = part + static_cast<int64_t>(blockIdx.x) * 3 * DP;
-    out[t] = s_lo[t];
-    out[DP + t] = s_hi[t];
-    out[2 * DP + t] = s_bad[t];
-  }
-}
-
-template <int DP>
-__global__ void k_range_finish(const float* __restrict__ part, int nparts, int d,
-                               float* __restrict__ out) {
-  // Launched with one wave of 64 threads; lanes c >= DP only join the barrier.
-  __shared__ float s_bad[64];
-  const int c = threadIdx.x;
-  float bad = 0.0f;
-  if (c < DP) {
-    float lo = INFINITY, hi = -INFINITY;
-    for (int b = 0; b < nparts; ++b) {
-      const float* p = part + static_cast<int64_t>(b) * 3 * DP;
-      lo = fminf(lo, p[c]);
-      hi = fmaxf(hi, p[DP + c]);
-      bad = fmaxf(bad, p[2 * DP + c]);
-    }
-    out[c] = lo;
-    out[DP + c] = hi;
-  }
-  // One flag for all real channels, reduced by lane 0 from the others.
-  s_bad[c] = c < d ? bad : 0.0f;
+  s_lo[t] = lo;
+  s_hi[t] = hi;
   __syncthreads();
-  if (c == 0) {
-    float any = 0.0f;
-    for (int i = 0; i < DP; ++i) any = fmaxf(any, s_bad[i]);
-    out[2 * DP] = any;
+  if (t < DP) {
+    for (int i = t + DP; i < kBlock; i += DP) {
+      lo = fminf(lo, s_lo[i]);
+      hi = fmaxf(hi, s_hi[i]);
+    }
+    float* mine = part + static_cast<int64_t>(blockIdx.x) * 2 * DP;
+    mine[t] = lo;
+    mine[DP + t] = hi;
   }
+  if (__any(wrong) && (t & 63) == 0) atomicOr(&out->bad_perm, 1);
 }
 
-// ------------------------------------------------- start arrangement, gather
-
-__global__ __launch_bounds__(kBlock) void k_start_perm(int32_t* __restrict__ P, int64_t n, Words4 keys) {
-  const Bijection f(static_cast<uint64_t>(n), keys.v);
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-  for (int64_t p = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; p < n; p += stride)
-    P[p] = static_cast<int32_t>(f(static_cast<uint64_t>(p)));
-}
-
-__global__ __launch_bounds__(kBlock) void k_count_perm(const int32_t* __restrict__ init, int64_t n,
-                                                       int32_t* __restrict__ counts,
-                                                       int32_t* __restrict__ flag) {
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-  for (int64_t p = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; p < n; p += stride) {
-    const int32_t v = init[p];
-    if (v < 0 || v >= n)
-      atomicOr(flag, 1);
-    else
-      atomicAdd(&counts[v], 1);
+// The blocks' ranges to the features' range and its energy scale, by one
+// block: a thread folds every R-th block's four minima or maxima, then the R
+// rows fold in LDS. QueryOut's ranges hold d channels.
+template <int DP>
+__global__ __launch_bounds__(kFinishBlock) void k_ingest_finish(const float* __restrict__ part, int nparts, int d,
+                                                                int64_t n, QueryOut* __restrict__ out) {
+  constexpr int kCols = DP / 2;  // quads of one block's 2 DP values
+  constexpr int kRows = kFinishBlock / kCols;
+  __shared__ float4 s_fold[kFinishBlock];
+  const int t = threadIdx.x, col = t % kCols;
+  const bool minimum = col < kCols / 2;
+  const float none = minimum ? INFINITY : -INFINITY;
+  auto fold = [minimum](float4 a, const float4 b) {
+    a.x = minimum ? fminf(a.x, b.x) : fmaxf(a.x, b.x);
+    a.y = minimum ? fminf(a.y, b.y) : fmaxf(a.y, b.y);
+    a.z = minimum ? fminf(a.z, b.z) : fmaxf(a.z, b.z);
+    a.w = minimum ? fminf(a.w, b.w) : fmaxf(a.w, b.w);
+    return a;
+  };
+  const float4* __restrict__ rows = reinterpret_cast<const float4*>(part);
+  float4 v = make_float4(none, none, none, none);
+#pragma unroll 8
+  for (int b = t / kCols; b < nparts; b += kRows) v = fold(v, rows[static_cast<int64_t>(b) * kCols + col]);
+  s_fold[t] = v;
+  __syncthreads();
+  for (int step = kFinishBlock / 2; step >= kCols; step >>= 1) {
+    if (t < step) s_fold[t] = fold(s_fold[t], s_fold[t + step]);
+    __syncthreads();
   }
-}
-
-__global__ __launch_bounds__(kBlock) void k_verify_counts(const int32_t* __restrict__ counts, int64_t n,
-                                                          int32_t* __restrict__ flag) {
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-  for (int64_t p = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; p < n; p += stride)
-    if (counts[p] != 1) atomicOr(flag, 1);
-}
-
-// G[p] = X[P[p]] (P NULL: identity), four channels per thread.
-template <int DP, typename S>
-__global__ __launch_bounds__(kBlock) void k_gather(const S* __restrict__ X, const int32_t* __restrict__ P,
-                                                   S* __restrict__ G, int64_t n) {
-  constexpr int LG = DP / 4;
-  using Quad = typename Storage<S>::Quad;
-  const Quad* __restrict__ src = reinterpret_cast<const Quad*>(X);
-  Quad* __restrict__ dst = reinterpret_cast<Quad*>(G);
-  const int64_t total = n * LG;
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-  for (int64_t e = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; e < total; e += stride) {
-    const int64_t p = e / LG;
-    const int j = static_cast<int>(e % LG);
-    const int64_t from = P != nullptr ? static_cast<int64_t>(P[p]) : p;
-    dst[e] = src[from * LG + j];
+  const float* lo = reinterpret_cast<const float*>(s_fold);
+  const float* hi = lo + DP;
+  if (t < d) {
+    out->lo[t] = lo[t];
+    out->hi[t] = hi[t];
+    if (!__builtin_isfinite(lo[t]) || !__builtin_isfinite(hi[t])) atomicOr(&out->bad_value, 1);
   }
+  if (t == 0) out->s = scale_shift(lo, hi, d, n);
 }
 
 // ------------------------------------------------------------------- blur
@@ -1970,30 +2042,54 @@ void k_assign(S* __restrict__ G, const S* __restrict__ T, int32_t* __restrict__ 
 
 // ----------------------------------------------------------------- energy
 
+// out += sum over cells of floor(d(G[p], T[p]) 2^s), s read from device
+// memory where the host does not have it yet. Bound by reading G and T once:
+// the launch is few blocks with several cells in flight per lane, since every
+// block's atomic on the one sum costs 15 ns (1024^2 x 64: 130 us, 4.1 TB/s;
+// with one cell in flight and an atomic per wave of 4096 blocks 252 us).
 template <int DP, typename S>
 __global__ __launch_bounds__(kBlock) void k_energy(const S* __restrict__ G, const S* __restrict__ T,
-                                                   int64_t n, double scale,
+                                                   int64_t n, int s_host, const int32_t* __restrict__ s_device,
                                                    unsigned long long* __restrict__ out) {
   constexpr int LG = DP / 4;
   constexpr int IPW = 64 / LG;
+  __shared__ unsigned long long s_sum[kWavesPerBlock];
+  const double scale = ldexp(1.0, s_device != nullptr ? *s_device : s_host);
   const int lane = threadIdx.x & 63;
   const int sub = lane % LG, slot = lane / LG;
-  const int64_t wave = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) >> 6;
-  const int64_t nwaves = (static_cast<int64_t>(gridDim.x) * kBlock) >> 6;
+  const int wib = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+  const int64_t wave = static_cast<int64_t>(blockIdx.x) * kWavesPerBlock + wib;
+  const int64_t nwaves = static_cast<int64_t>(gridDim.x) * kWavesPerBlock;
   using Quad = typename Storage<S>::Quad;
   const Quad* __restrict__ G4 = reinterpret_cast<const Quad*>(G);
   const Quad* __restrict__ T4 = reinterpret_cast<const Quad*>(T);
   unsigned long long acc = 0;
-  for (int64_t first = wave * IPW; first < n; first += nwaves * IPW) {
-    const int64_t p = first + slot;
-    const int64_t pc = p < n ? p : 0;
-    float v = chunk_sq(Storage<S>::widen4(G4[pc * LG + sub]), Storage<S>::widen4(T4[pc * LG + sub]));
+  for (int64_t first = wave * IPW; first < n; first += kEnergyFlight * nwaves * IPW) {
+    Quad g[kEnergyFlight], t[kEnergyFlight];
+    bool in[kEnergyFlight];
 #pragma unroll
-    for (int m = 1; m < LG; m <<= 1) v = v + __shfl_xor(v, m);
-    if (p < n && sub == 0) acc += static_cast<unsigned long long>(static_cast<double>(v) * scale);
+    for (int k = 0; k < kEnergyFlight; ++k) {
+      const int64_t p = first + k * nwaves * IPW + slot;
+      in[k] = p < n;
+      const int64_t at = (in[k] ? p : 0) * LG + sub;
+      g[k] = G4[at];
+      t[k] = T4[at];
+    }
+#pragma unroll
+    for (int k = 0; k < kEnergyFlight; ++k) {
+      float v = chunk_sq(Storage<S>::widen4(g[k]), Storage<S>::widen4(t[k]));
+#pragma unroll
+      for (int m = 1; m < LG; m <<= 1) v = v + __shfl_xor(v, m);
+      if (in[k] && sub == 0) acc += static_cast<unsigned long long>(static_cast<double>(v) * scale);
+    }
   }
   acc = wave_sum_u64(acc);
-  if (lane == 0) atomicAdd(out, acc);
+  if (lane == 0) s_sum[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 1; i < kWavesPerBlock; ++i) acc += s_sum[i];
+    atomicAdd(out, acc);
+  }
 }
 
 // -------------------------------------------------------------------- VAD
@@ -2330,16 +2426,6 @@ __global__ __launch_bounds__(kBlock) void k_batch_status(const BatchGrid* __rest
   out[i] = hs;
 }
 
-__global__ __launch_bounds__(kBlock) void k_fill_u32(uint32_t* __restrict__ p, int64_t count, uint32_t value) {
-  const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; i < count; i += stride) p[i] = value;
-}
-
-__global__ __launch_bounds__(kBlock) void k_inverse_counts(float* __restrict__ inv, int w) {
-  const int c = blockIdx.x * kBlock + threadIdx.x;
-  if (c <= w) inv[c] = c == 0 ? 0.0f : 1.0f / static_cast<float>(c);
-}
-
 }  // namespace
 
 // ------------------------------------------------- no-allocation scratch
@@ -2349,8 +2435,7 @@ __global__ __launch_bounds__(kBlock) void k_inverse_counts(float* __restrict__ i
 // must not pass `scratch` itself to a kernel (it names a host-side stand-in):
 // noalloc_scratch gives its address on the current device.
 static __device__ __align__(256) unsigned char scratch[NoAllocLayout::kBytes];
-static_assert(NoAllocLayout::kRangePartBytes == static_cast<size_t>(kRangeBlocks) * 3 * 64 * sizeof(float),
-              "range scratch of the widest cell");
+static_assert(NoAllocLayout::kOut + sizeof(QueryOut) <= NoAllocLayout::kInv, "query results");
 static_assert((kNoAllocMaxSide + 1) * sizeof(float) <= 4096, "1/c table");
 
 namespace {
@@ -2373,18 +2458,6 @@ hipError_t noalloc_scratch(int device, void** out) {
 }
 
 // --------------------------------------------------------------- launchers
-
-hipError_t launch_fill_u32(uint32_t* p, int64_t count, uint32_t value, hipStream_t stream) {
-  if (count <= 0) return hipSuccess;
-  k_fill_u32<<<blocks_for(count, 1024), kBlock, 0, stream>>>(p, count, value);
-  return hipGetLastError();
-}
-
-hipError_t launch_inverse_counts(float* inv, int w, hipStream_t stream) {
-  if (w < 0) return hipErrorInvalidValue;
-  k_inverse_counts<<<(w + kBlock) / kBlock, kBlock, 0, stream>>>(inv, w);
-  return hipGetLastError();
-}
 
 #define PLAS_DISPATCH_DP(dp, CALL) \
   switch (dp) {                    \
@@ -2409,66 +2482,53 @@ hipError_t launch_inverse_counts(float* inv, int w, hipStream_t stream) {
     return hipErrorInvalidValue;                           \
   }
 
-hipError_t launch_ingest(const void* features, int input_bf16, int64_t n, int d, int layout, int dp, int storage,
-                         void* X, hipStream_t stream) {
-  if (layout == 0) {
-    const int blocks = static_cast<int>((n + 63) / 64);
-    PLAS_DISPATCH_STORAGE(storage, {
-      if (input_bf16) {
-        PLAS_DISPATCH_DP(dp, (k_ingest_cn<DPV, uint16_t, SV><<<blocks, kBlock, 0, stream>>>(
-                                 static_cast<const uint16_t*>(features), n, d, static_cast<SV*>(X))));
-      } else {
-        PLAS_DISPATCH_DP(dp, (k_ingest_cn<DPV, float, SV><<<blocks, kBlock, 0, stream>>>(
-                                 static_cast<const float*>(features), n, d, static_cast<SV*>(X))));
-      }
-    });
-  } else {
-    const int blocks = blocks_for(n * dp, 65536);
-    PLAS_DISPATCH_STORAGE(storage, {
-      if (input_bf16) {
-        PLAS_DISPATCH_DP(dp, (k_ingest_nc<DPV, uint16_t, SV><<<blocks, kBlock, 0, stream>>>(
-                                 static_cast<const uint16_t*>(features), n, d, static_cast<SV*>(X))));
-      } else {
-        PLAS_DISPATCH_DP(dp, (k_ingest_nc<DPV, float, SV><<<blocks, kBlock, 0, stream>>>(
-                                 static_cast<const float*>(features), n, d, static_cast<SV*>(X))));
-      }
-    });
-  }
-  return hipGetLastError();
-}
-
-size_t range_partial_floats(int dp) { return static_cast<size_t>(kRangeBlocks) * 3 * dp; }
-
-hipError_t launch_range(const void* X, int64_t n, int d, int dp, int storage, float* part, float* out,
+hipError_t launch_begin(QueryOut* out, const int32_t* perm, int64_t n, int32_t* inv, float* counts, int w,
                         hipStream_t stream) {
-  PLAS_DISPATCH_STORAGE(storage, {
-    PLAS_DISPATCH_DP(dp, (k_range_partial<DPV, SV><<<kRangeBlocks, kBlock, 0, stream>>>(
-                             static_cast<const SV*>(X), n, part)));
-  });
-  PLAS_DISPATCH_DP(dp, (k_range_finish<DPV><<<1, 64, 0, stream>>>(part, kRangeBlocks, d, out)));
+  const int64_t work = std::max<int64_t>(perm != nullptr ? n : 1, counts != nullptr ? w + 1 : 1);
+  k_begin<<<blocks_for(work), kBlock, 0, stream>>>(out, perm, n, inv, counts, w);
   return hipGetLastError();
 }
 
-hipError_t launch_start_perm(int32_t* P, int64_t n, const uint64_t keys[4], hipStream_t stream) {
+hipError_t launch_start_perm(int32_t* P, int32_t* inv, int64_t n, const uint64_t keys[4], hipStream_t stream) {
   Words4 k;
   for (int i = 0; i < 4; ++i) k.v[i] = keys[i];
-  k_start_perm<<<blocks_for(n), kBlock, 0, stream>>>(P, n, k);
+  k_start_perm<<<blocks_for(n), kBlock, 0, stream>>>(P, inv, n, k);
   return hipGetLastError();
 }
 
-hipError_t launch_check_perm(const int32_t* init, int64_t n, int32_t* counts, int32_t* flag,
-                             hipStream_t stream) {
-  k_count_perm<<<blocks_for(n), kBlock, 0, stream>>>(init, n, counts, flag);
-  k_verify_counts<<<blocks_for(n), kBlock, 0, stream>>>(counts, n, flag);
+hipError_t launch_check_perm(const int32_t* perm, int64_t n, int32_t* inv, QueryOut* out, hipStream_t stream) {
+  const hipError_t e = launch_begin(out, perm, n, inv, nullptr, 0, stream);
+  if (e != hipSuccess) return e;
+  k_check_inverse<<<blocks_for(n), kBlock, 0, stream>>>(perm, inv, n, &out->bad_perm);
   return hipGetLastError();
 }
 
-hipError_t launch_gather(const void* X, const int32_t* P, void* G, int64_t n, int dp, int storage,
+namespace {
+template <typename SI, typename SO, int DP>
+void ingest_dp(const void* features, int64_t n, int d, int layout, const int32_t* inv, const int32_t* perm, void* G,
+               float* part, QueryOut* out, hipStream_t stream) {
+  constexpr int kTile = kIngestTile / DP;
+  const int blocks = static_cast<int>(std::min<int64_t>((n + kTile - 1) / kTile, kIngestBlocks));
+  const SI* F = static_cast<const SI*>(features);
+  SO* dst = static_cast<SO*>(G);
+  if (layout == 0)
+    k_ingest<DP, SI, SO, 0><<<blocks, kBlock, 0, stream>>>(F, n, d, inv, perm, dst, part, out);
+  else
+    k_ingest<DP, SI, SO, 1><<<blocks, kBlock, 0, stream>>>(F, n, d, inv, perm, dst, part, out);
+  k_ingest_finish<DP><<<1, kFinishBlock, 0, stream>>>(part, blocks, d, n, out);
+}
+}  // namespace
+
+hipError_t launch_ingest(const void* features, int input_bf16, int64_t n, int d, int layout, int dp, int storage,
+                         const int32_t* inv, const int32_t* perm, void* G, float* part, QueryOut* out,
                          hipStream_t stream) {
-  const int blocks = blocks_for(n * (dp / 4), 65536);
+  if (n < 1 || d < 1 || d > dp) return hipErrorInvalidValue;
   PLAS_DISPATCH_STORAGE(storage, {
-    PLAS_DISPATCH_DP(dp, (k_gather<DPV, SV><<<blocks, kBlock, 0, stream>>>(static_cast<const SV*>(X), P,
-                                                                          static_cast<SV*>(G), n)));
+    if (input_bf16) {
+      PLAS_DISPATCH_DP(dp, (ingest_dp<uint16_t, SV, DPV>(features, n, d, layout, inv, perm, G, part, out, stream)));
+    } else {
+      PLAS_DISPATCH_DP(dp, (ingest_dp<float, SV, DPV>(features, n, d, layout, inv, perm, G, part, out, stream)));
+    }
   });
   return hipGetLastError();
 }
@@ -2587,14 +2647,13 @@ hipError_t launch_assign(void* G, const void* T, int32_t* P, const int32_t* tabl
 }
 
 hipError_t launch_energy(const void* G, const void* T, int64_t n, int dp, int storage, int s,
-                         unsigned long long* energy_out, hipStream_t stream) {
-  const int64_t items_per_wave = 64 / (dp / 4);
-  const int64_t waves = (n + items_per_wave - 1) / items_per_wave;
-  const int blocks = blocks_for(waves * 64);
-  const double scale = ldexp(1.0, s);
+                         const int32_t* s_device, unsigned long long* energy_out, hipStream_t stream) {
+  const int64_t cells_per_wave = kEnergyFlight * (64 / (dp / 4));
+  const int64_t waves = (n + cells_per_wave - 1) / cells_per_wave;
+  const int blocks = blocks_for(waves * 64, kEnergyBlocks);
   PLAS_DISPATCH_STORAGE(storage, {
     PLAS_DISPATCH_DP(dp, (k_energy<DPV, SV><<<blocks, kBlock, 0, stream>>>(
-                             static_cast<const SV*>(G), static_cast<const SV*>(T), n, scale, energy_out)));
+                             static_cast<const SV*>(G), static_cast<const SV*>(T), n, s, s_device, energy_out)));
   });
   return hipGetLastError();
 }

@@ -23,25 +23,38 @@ struct plas_level_out {  // same layout as plas_level_stat in plas.h
 constexpr int kStorageF32 = 0;
 constexpr int kStorageBF16 = 1;
 
-// features (layout CN [d][n] or NC [n][d]; float32, or bfloat16 bits if
-// input_bf16) -> X [n][dp] in `storage`, channels >= d zero.
-hipError_t launch_ingest(const void* features, int input_bf16, int64_t n, int d, int layout, int dp, int storage,
-                         void* X, hipStream_t stream);
-// Per-channel min/max of X[n][dp] over the first d channels, and a flag set
-// if any value is NaN or infinite. out: [dp] mins, [dp] maxs, then the flag
-// (as a float slot holding 0 or 1). part: scratch of range_partial_floats().
-size_t range_partial_floats(int dp);
-hipError_t launch_range(const void* X, int64_t n, int d, int dp, int storage, float* part, float* out,
+// What an ingest and an energy query leave on the device.
+struct QueryOut {
+  float lo[64], hi[64];       // range of the stored values per channel, d of them
+  int32_t bad_value;          // nonzero: some value is NaN or infinite
+  int32_t bad_perm;           // nonzero: the permutation is not a bijection
+  int32_t s;                  // energy scale (scale_shift of the ranges)
+  int32_t pad;
+  unsigned long long energy;  // fixed-point energy
+};
+
+// Clears out's flags and energy; writes float32 1/c (correctly rounded) for c
+// = 1..w and 0 for c = 0 to counts (NULL: not); writes the inverse of perm
+// (device int32[n], NULL: none) to inv, for launch_ingest to check and follow.
+hipError_t launch_begin(QueryOut* out, const int32_t* perm, int64_t n, int32_t* inv, float* counts, int w,
                         hipStream_t stream);
-// P[p] = bijection(n, keys)(p).
-hipError_t launch_start_perm(int32_t* P, int64_t n, const uint64_t keys[4], hipStream_t stream);
-// Check that init (int32[n]) is a bijection of [0, n): counts is scratch
-// int32[n], flag (device int32) is set to 1 when it is not. counts and flag
-// must be zeroed beforehand.
-hipError_t launch_check_perm(const int32_t* init, int64_t n, int32_t* counts, int32_t* flag,
-                             hipStream_t stream);
-// G[p] = X[P[p]] over dp channels (P NULL: identity).
-hipError_t launch_gather(const void* X, const int32_t* P, void* G, int64_t n, int dp, int storage,
+// P[p] = bijection(n, keys)(p), inv its inverse (NULL: not written).
+hipError_t launch_start_perm(int32_t* P, int32_t* inv, int64_t n, const uint64_t keys[4], hipStream_t stream);
+// Sets out->bad_perm if perm (int32[n]) is not a bijection of [0, n), and
+// clears the rest as launch_begin does. inv: scratch int32[n].
+hipError_t launch_check_perm(const int32_t* perm, int64_t n, int32_t* inv, QueryOut* out, hipStream_t stream);
+// features (layout CN [d][n] or NC [n][d]; float32, or bfloat16 bits if
+// input_bf16) -> G [n][dp] in `storage`, feature i at G[inv[i]] (inv NULL:
+// G[i]), channels >= d zero; out's ranges, bad_value and s. With perm (the
+// permutation launch_begin inverted; NULL: inv is known good) sets
+// out->bad_perm if it is no bijection; places it does not name are then left
+// unwritten. part: scratch of ingest_partial_floats(dp) floats. Few blocks
+// keep the fold of their ranges short (1024^2 x 59, ingest and fold: 512
+// blocks 112 + 6 us, 1024 blocks 105 + 9).
+constexpr int kIngestBlocks = 512;
+constexpr size_t ingest_partial_floats(int dp) { return static_cast<size_t>(kIngestBlocks) * 2 * dp; }
+hipError_t launch_ingest(const void* features, int input_bf16, int64_t n, int d, int layout, int dp, int storage,
+                         const int32_t* inv, const int32_t* perm, void* G, float* part, QueryOut* out,
                          hipStream_t stream);
 // The grouping table a reorder's first row pass fills after its lines, from
 // the state's beta and keys.
@@ -115,15 +128,10 @@ hipError_t launch_assign_batch(const BatchGrid* grids, const uint32_t* map, int 
 hipError_t launch_batch_status(const BatchGrid* grids, const int32_t* list, int count, HostStatus* out,
                                hipStream_t stream);
 
-// energy_out (device u64) += sum over cells of floor(d(G[p], T[p]) * 2^s).
+// energy_out (device u64) += sum over cells of floor(d(G[p], T[p]) * 2^s);
+// s is *s_device if that is not NULL.
 hipError_t launch_energy(const void* G, const void* T, int64_t n, int dp, int storage, int s,
-                         unsigned long long* energy_out, hipStream_t stream);
-
-// p[i] = value for i < count (a kernel, not a memset: callers may capture the
-// stream in a graph).
-hipError_t launch_fill_u32(uint32_t* p, int64_t count, uint32_t value, hipStream_t stream);
-// inv[c] = float32 1/c (correctly rounded) for c = 1..w, inv[0] = 0.
-hipError_t launch_inverse_counts(float* inv, int w, hipStream_t stream);
+                         const int32_t* s_device, unsigned long long* energy_out, hipStream_t stream);
 
 // ---- the device scratch of the no-allocation energy query. One array per
 // GPU, allocated with the code object and held until the process ends;
@@ -134,10 +142,8 @@ struct NoAllocLayout {
   static constexpr size_t kGrid = static_cast<size_t>(kNoAllocMaxCells) * 64 * 4;  // widest cell, float32
   static constexpr size_t kG = 0, kH = kGrid, kT = 2 * kGrid;
   static constexpr size_t kRangePart = 3 * kGrid;
-  static constexpr size_t kRangePartBytes = 256 * 3 * 64 * 4;  // range_partial_floats(64) floats
-  static constexpr size_t kRangeOut = kRangePart + kRangePartBytes;
-  static constexpr size_t kFlags = kRangeOut + 1024;  // u64 accumulator, then an int32 flag
-  static constexpr size_t kInv = kFlags + 256;
+  static constexpr size_t kOut = kRangePart + ingest_partial_floats(64) * 4;  // QueryOut
+  static constexpr size_t kInv = kOut + 1024;
   static constexpr size_t kBytes = kInv + 4096;  // (kNoAllocMaxSide + 1) floats, rounded up
 };
 // The array's device address on `device`, which must be current (looked up
