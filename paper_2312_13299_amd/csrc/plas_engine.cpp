@@ -377,27 +377,37 @@ int32_t plas_vad(plas_handle h, const void* features, const int32_t* perm, int64
   if (vad == nullptr) return fail(h, PLAS_ERR_INVALID_ARGUMENT, "vad is NULL");
   DeviceScope scope(h->device);
   if (!scope.ok()) return fail(h, PLAS_ERR_HIP, "hipSetDevice failed");
-  if (perm != nullptr) {
-    PLAS_HIP(h, reserve(h->grid_h, static_cast<size_t>(n) * sizeof(int32_t)));
-    PLAS_HIP(h, reserve(h->query, sizeof(plas::QueryOut)));
-    plas::QueryOut* out = as<plas::QueryOut>(h->query);
-    PLAS_HIP(h, plas::launch_check_perm(perm, n, as<int32_t>(h->grid_h), out, h->stream));
-    PLAS_HIP(h, hipMemcpyAsync(&h->query_host->bad_perm, &out->bad_perm, sizeof(int32_t), hipMemcpyDeviceToHost,
-                               h->stream));
-    PLAS_HIP(h, hipStreamSynchronize(h->stream));
-    if (h->query_host->bad_perm != 0)
-      return fail(h, PLAS_ERR_INVALID_ARGUMENT, "permutation is not a bijection of [0, n)");
+  const int dp = padded_channels(d);
+  const int32_t storage = dtype == PLAS_DTYPE_BF16 ? PLAS_STORAGE_BF16 : PLAS_STORAGE_F32;  // holds the values exactly
+  if (perm != nullptr) PLAS_HIP(h, reserve(h->grid_h, static_cast<size_t>(n) * sizeof(int32_t)));
+  PLAS_HIP(h, reserve(h->vad, plas::vad_partial_doubles() * sizeof(double)));
+  st = reserve_query(h, dp);
+  if (st != PLAS_OK) return st;
+  const IngestPlan plan{nullptr, as<int32_t>(h->grid_h), as<float>(h->range_part), as<plas::QueryOut>(h->query)};
+  // In arranged order if a grid fits beside the features, else where they are.
+  const bool grid = reserve(h->grid_g, static_cast<size_t>(n) * dp * storage_bytes(storage)) == hipSuccess;
+  if (grid) {
+    IngestPlan arranged = plan;
+    arranged.G = h->grid_g.ptr;
+    st = queue_arranged(h, features, dtype, n, d, side, layout, dp, storage, perm, arranged, nullptr);
+    if (st != PLAS_OK) return st;
+    PLAS_HIP(h, plas::launch_vad_grid(arranged.G, d, side, dp, storage, as<double>(h->vad), &plan.out->vad[1],
+                                      h->stream));
+  } else {
+    (void)hipGetLastError();  // the failed allocation's
+    if (perm != nullptr) {
+      PLAS_HIP(h, plas::launch_check_perm(perm, n, plan.inv, plan.out, h->stream));
+      st = read_query(h, plan.out, false);
+      if (st != PLAS_OK) return st;
+    } else {
+      PLAS_HIP(h, plas::launch_begin(plan.out, nullptr, n, nullptr, nullptr, 0, h->stream));
+    }
+    PLAS_HIP(h, plas::launch_vad_in_place(features, dtype == PLAS_DTYPE_BF16, perm, n, d, side, layout,
+                                          as<double>(h->vad), plan.out->vad, h->stream));
   }
-  const size_t parts = plas::vad_partial_doubles();
-  PLAS_HIP(h, reserve(h->vad, (parts + 2) * sizeof(double)));
-  double* part = as<double>(h->vad);
-  double* out = part + parts;
-  PLAS_HIP(h, plas::launch_vad(features, dtype == PLAS_DTYPE_BF16, perm, n, d, side, layout, part, out, h->stream));
-  PLAS_HIP(h, hipMemcpyAsync(h->u64_host, out, 2 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-  PLAS_HIP(h, hipStreamSynchronize(h->stream));
-  double v[2];
-  std::memcpy(v, h->u64_host, sizeof(v));
-  *vad = v[1];
+  st = read_query(h, plan.out, false);  // values that are not finite show in the result
+  if (st != PLAS_OK) return st;
+  *vad = h->query_host->vad[1];
   return PLAS_OK;
 }
 

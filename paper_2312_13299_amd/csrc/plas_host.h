@@ -267,11 +267,11 @@ inline int32_t queue_start(plas_context* h, const void* features, int32_t dtype,
 }
 
 // Reads the results of what is queued (to h->query_host) and reports features
-// that are not finite and permutations that are none.
-inline int32_t read_query(plas_context* h, const plas::QueryOut* out) {
+// that are not finite (if `finite`) and permutations that are none.
+inline int32_t read_query(plas_context* h, const plas::QueryOut* out, bool finite = true) {
   PLAS_HIP(h, hipMemcpyAsync(h->query_host, out, sizeof(plas::QueryOut), hipMemcpyDeviceToHost, h->stream));
   PLAS_HIP(h, hipStreamSynchronize(h->stream));
-  if (h->query_host->bad_value != 0) return fail(h, PLAS_ERR_NONFINITE, "features contain NaN or infinity");
+  if (finite && h->query_host->bad_value != 0) return fail(h, PLAS_ERR_NONFINITE, "features contain NaN or infinity");
   if (h->query_host->bad_perm != 0)
     return fail(h, PLAS_ERR_INVALID_ARGUMENT, "permutation is not a bijection of [0, n)");
   return PLAS_OK;

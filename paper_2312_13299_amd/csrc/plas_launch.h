@@ -31,6 +31,7 @@ struct QueryOut {
   int32_t s;                  // energy scale (scale_shift of the ranges)
   int32_t pad;
   unsigned long long energy;  // fixed-point energy
+  double vad[2];              // of a VAD: the mean (in place only) and the variance
 };
 
 // Clears out's flags and energy; writes float32 1/c (correctly rounded) for c
@@ -87,12 +88,16 @@ struct ControlArgs {
 // shift and grouping keys); without it, st keeps the sums for the caller.
 hipError_t launch_assign(void* G, const void* T, int32_t* P, const int32_t* table, DevState* st, int dp,
                          int storage, int64_t max_items, hipStream_t stream, const ControlArgs* control = nullptr);
-// VAD (App. C) of features[perm] on a w x w grid: out[0] receives the mean
-// |a - b| over neighbour pairs and channels, out[1] the variance. part:
-// device scratch of vad_partial_doubles() doubles; out: device double[2].
+// VAD (App. C) of a grid [w * w][dp] of d channels, the rest zero: the variance
+// of |a - b| over neighbour pairs and channels, to *out (device). part: device
+// scratch of vad_partial_doubles() doubles.
 size_t vad_partial_doubles();
-hipError_t launch_vad(const void* features, int input_bf16, const int32_t* perm, int64_t n, int d, int w,
-                      int layout, double* part, double* out, hipStream_t stream);
+hipError_t launch_vad_grid(const void* G, int d, int w, int dp, int storage, double* part, double* out,
+                           hipStream_t stream);
+// The same of features[perm] without a grid: out[0] the mean, out[1] the
+// variance.
+hipError_t launch_vad_in_place(const void* features, int input_bf16, const int32_t* perm, int64_t n, int d, int w,
+                               int layout, double* part, double* out, hipStream_t stream);
 
 // ---- batches of sorts (BatchGrid in plas_device.h). A launch's block map
 // (device uint32[blocks]) holds (grid index << 16) | block index within the
