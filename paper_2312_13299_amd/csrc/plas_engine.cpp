@@ -83,7 +83,7 @@ int32_t plas_create(plas_handle* out, int32_t device) {
   }
   bool ok = hipHostMalloc(reinterpret_cast<void**>(&h->query_host), sizeof(plas::QueryOut)) == hipSuccess &&
             hipHostMalloc(reinterpret_cast<void**>(&h->u64_host), 16 * sizeof(unsigned long long)) == hipSuccess &&
-            hipHostMalloc(reinterpret_cast<void**>(&h->state_host), sizeof(DevState)) == hipSuccess &&
+            hipHostMalloc(reinterpret_cast<void**>(&h->state_host), 2 * sizeof(DevState)) == hipSuccess &&
             reserve(h->state, sizeof(DevState)) == hipSuccess &&
             reserve(h->stage_state, sizeof(DevState)) == hipSuccess &&
             reserve(h->scratch, 16 * sizeof(unsigned long long)) == hipSuccess;
@@ -204,17 +204,16 @@ int32_t plas_sort(plas_handle h, const void* features, int64_t n, int32_t d, int
   const int chunk = prm.reorders_per_sync > 0 ? prm.reorders_per_sync : kDefaultReordersPerSync;
   const int passes = prm.filter == PLAS_FILTER_BOX3 ? 3 : 1;  // box passes per axis
   const bool profile = prm.profile != 0;
-  if (profile) {
-    st = ensure_events(h, static_cast<size_t>(chunk) * 3);
-    if (st != PLAS_OK) return st;
-  }
+  st = ensure_events(h, profile ? static_cast<size_t>(chunk) * 3 : 2);
+  if (st != PLAS_OK) return st;
   const int64_t max_k = reorder_bound(levels.size(), prm.inv_threshold);
   double blur_ms = 0.0, assign_ms = 0.0;
   int64_t timed_reorders = 0;
   int64_t slots = 0;  // reorder slots queued so far; slot i runs reorder k0 + i unless the sort has ended
   const int64_t k0 = S->k;  // reorders done before this call (a resumed sort)
-  for (;;) {
-    for (int i = 0; i < chunk; ++i) {
+  // Queues the reorders [from, to) of a chunk.
+  auto queue_reorders = [&](int from, int to) -> int32_t {
+    for (int i = from; i < to; ++i) {
       // Each axis takes `passes` box passes (PLAS_FILTER_BOX3: three),
       // through H and T in turn, the last column pass writing T: rows G -> H
       // [-> T -> H], columns [H -> T -> H ->] H -> T. The first row pass
@@ -239,10 +238,34 @@ int32_t plas_sort(plas_handle h, const void* features, int64_t n, int32_t d, int
       PLAS_HIP(h, plas::launch_assign(G, T, P, table, Sd, dp, storage, max_items, h->stream, &control));
       if (timed) PLAS_HIP(h, hipEventRecord(h->events[3 * i + 2], h->stream));
     }
-    const int64_t first_slot = slots;
-    slots += chunk;
-    PLAS_HIP(h, hipMemcpyAsync(S, Sd, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
-    PLAS_HIP(h, hipStreamSynchronize(h->stream));
+    slots += to - from;
+    return PLAS_OK;
+  };
+  // Reads the state into slot `at` after what is queued.
+  auto queue_status = [&](int at) -> int32_t {
+    PLAS_HIP(h, hipMemcpyAsync(&h->state_host[at], Sd, sizeof(DevState), hipMemcpyDeviceToHost, h->stream));
+    if (!profile) PLAS_HIP(h, hipEventRecord(h->events[at], h->stream));
+    return PLAS_OK;
+  };
+  // While the host waits for a chunk's state, the device starts on the next
+  // chunk: a few reorders cover the wait (about 25 us), and as many launches
+  // return at once when the sort has ended. Timed chunks run one by one, since
+  // they share their events.
+  const int lead = profile ? 0 : std::min(chunk, kLeadReorders);
+  int at = 0;
+  st = queue_reorders(0, chunk);
+  if (st == PLAS_OK) st = queue_status(at);
+  if (st != PLAS_OK) return st;
+  for (;;) {
+    const int64_t ran_slots = slots, first_slot = slots - chunk;
+    const bool ahead = lead > 0 && (prm.max_reorders <= 0 || k0 + slots < prm.max_reorders);
+    if (ahead) {
+      st = queue_reorders(0, lead);
+      if (st != PLAS_OK) return st;
+    }
+    if (profile) PLAS_HIP(h, hipStreamSynchronize(h->stream));
+    else PLAS_HIP(h, hipEventSynchronize(h->events[at]));
+    S = &h->state_host[at];
     const bool done = S->done != 0;
     const int64_t k_now = S->k;
     if (profile) {
@@ -262,8 +285,14 @@ int32_t plas_sort(plas_handle h, const void* features, int64_t n, int32_t d, int
     // the device state is broken. Also stop at the bound on reorders that
     // the stall test implies (energies strictly fall by at least 1/M per
     // improvement, two stalls end a level).
-    if (k_now - k0 != slots || k_now > max_k)
+    if (k_now - k0 != ran_slots || k_now > max_k) {
+      (void)hipStreamSynchronize(h->stream);
       return fail(h, PLAS_ERR_HIP, "device controller made no progress");
+    }
+    at ^= 1;
+    st = queue_reorders(ahead ? lead : 0, chunk);
+    if (st == PLAS_OK) st = queue_status(at);
+    if (st != PLAS_OK) return st;
   }
 
   PLAS_HIP(h, hipMemcpyAsync(perm_out, P, static_cast<size_t>(n) * sizeof(int32_t), hipMemcpyDeviceToDevice,

@@ -30,6 +30,7 @@ struct plas_batch_state;
 namespace plas_host {
 
 constexpr int kDefaultReordersPerSync = 32;
+constexpr int kLeadReorders = 4;  // reorders queued ahead of a chunk's status
 // With profiling, every kProfileEvery-th reorder slot of a chunk is timed
 // (three events: before the blur passes, between them and the assignment,
 // after it). A HIP event record between two launches costs about 5 us of
@@ -65,7 +66,7 @@ struct plas_context {
   // Pinned host memory for small read-backs.
   plas::QueryOut* query_host = nullptr;
   unsigned long long* u64_host = nullptr;
-  DevState* state_host = nullptr;
+  DevState* state_host = nullptr;  // two: the status read-backs of a sort alternate
   std::vector<hipEvent_t> events;
   // Batch engine resources (plas_batch.cpp), created on first use.
   plas_batch_state* batch = nullptr;
