@@ -2861,7 +2861,8 @@ int batch_assign_blocks(int64_t max_items, int dp, int storage, int cap) {
 // two per CU in float32, three in bfloat16, whose waves hold half the bytes
 // in flight. 512 / 768 / 1024 / 2048 / 4096 blocks, us per assignment inside
 // sorts: 723^2 x 64 float32 53 / 54 / 53 / 58 / 71, 1024^2 x 64 98 / 101 / 101
-// / 99 / 101, 1448^2 x 64 bfloat16 116 / 111 / 127 / 114 / 118.
+// / 99 / 101, 1448^2 x 64 219 / 230 / 241 / 231 / 234 (256 / 384 blocks: 259 /
+// 237), 1448^2 x 64 bfloat16 116 / 111 / 127 / 114 / 118.
 int assign_blocks_cap(int storage) { return storage == kStorageBF16 ? 768 : 512; }
 
 template <typename S, int DP>
