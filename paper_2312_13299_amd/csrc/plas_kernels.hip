@@ -299,12 +299,16 @@ __global__ __launch_bounds__(kFinishBlock) void k_ingest_finish(const float* __r
 
 // ------------------------------------------------------------------- blur
 
-// The radius of a pass: st->r, or the fixed radius when st is NULL. Returns
-// false when the sort has ended (every kernel queued after the end returns
-// at once).
-__device__ __forceinline__ bool pass_radius(const DevState* __restrict__ st, int radius, int& r) {
+// The radius of a pass over lines of w positions: st->r, or the fixed radius
+// when st is NULL. Every window of half-width w - 1 or more is the whole line,
+// so it is clipped there, for every kernel: callers may give any radius, and
+// the walks take r / 16 steps more than the line has and add r to positions.
+// Returns false when the sort has ended (every kernel queued after the end
+// returns at once).
+__device__ __forceinline__ bool pass_radius(const DevState* __restrict__ st, int radius, int w, int& r) {
   if (st != nullptr && st->done) return false;
   r = st != nullptr ? st->r : radius;
+  if (r > w - 1) r = w - 1;
   return true;
 }
 
@@ -338,7 +342,7 @@ __device__ __forceinline__ void wave_lds_sync() {
 // One separable box-blur pass. Lane = (line, channel): DP consecutive lanes
 // walk one line, 64 / DP lines per wave. Along the line the window sum is
 // kept as a running sum: it starts as the ascending sum of the first
-// min(r, w-1) + 1 values; at each next position the entering value is added
+// r + 1 values; at each next position the entering value is added
 // and then the leaving value subtracted, and the output is the running sum
 // times float32(1 / count) for the window clipped to the grid.
 //
@@ -478,23 +482,22 @@ __device__ __forceinline__ void blur_reg_lines(const S* __restrict__ in, S* __re
     for (int x = 0; x < w; ++x) L.dst[x * L.step] = L.src[x * L.step];
     return;
   }
-  // Start: ascending sum of positions 0 .. first_hi, loaded kBlurUnroll at a time.
-  const int first_hi = r < w - 1 ? r : w - 1;
+  // Start: ascending sum of positions 0 .. r, loaded kBlurUnroll at a time.
   float s = L.load(0);
   int t = 1;
-  for (; t + kBlurUnroll - 1 <= first_hi; t += kBlurUnroll) {
+  for (; t + kBlurUnroll - 1 <= r; t += kBlurUnroll) {
     float v[kBlurUnroll];
 #pragma unroll
     for (int i = 0; i < kBlurUnroll; ++i) v[i] = L.load(t + i);
 #pragma unroll
     for (int i = 0; i < kBlurUnroll; ++i) s = s + v[i];
   }
-  for (; t <= first_hi; ++t) s = s + L.load(t);
+  for (; t <= r; ++t) s = s + L.load(t);
   L.store(0, s, L.mult(0));
   // Position x has an entering value iff x + r <= w - 1 and a leaving value
   // iff x - r - 1 >= 0. Both bounds split [1, w) into at most three ranges.
-  const int enter_end = w - r < 1 ? 1 : (w - r > w ? w : w - r);  // x < enter_end: entering
-  const int leave_begin = r + 1 < w ? r + 1 : w;                 // x >= leave_begin: leaving
+  const int enter_end = w - r;    // x < enter_end: entering
+  const int leave_begin = r + 1;  // x >= leave_begin: leaving
   if (enter_end <= leave_begin) {
     blur_range<true, false>(L, 1, enter_end, s);
     blur_range<false, false>(L, enter_end, leave_begin, s);
@@ -518,7 +521,7 @@ __global__ __launch_bounds__(kBlock) void k_blur(const S* __restrict__ in, S* __
                                                  int vertical, const float* __restrict__ inv,
                                                  int32_t* __restrict__ table) {
   int r;
-  if (!pass_radius(st, radius, r)) return;
+  if (!pass_radius(st, radius, w, r)) return;
   const int64_t wave = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) >> 6;
   blur_reg_lines<DP, S>(in, out, w, r, vertical, inv, wave, threadIdx.x & 63);
   if (table != nullptr) fill_group_table<kBlock>(table, st->beta, st->keys, blockIdx.x, gridDim.x);
@@ -995,8 +998,6 @@ __device__ __forceinline__ void blur_relay_lines(const S* __restrict__ in, S* __
     }
     return;
   }
-  // Every window of half-width w - 1 or more is the whole line.
-  if (r > w - 1) r = w - 1;
   L_t L;
   L.init(w, r, stream, lane, lds[sub]);
   const int j = lane % Sh::kLanesPerRow;
@@ -1033,7 +1034,7 @@ void k_blur_relay(const S* __restrict__ in, S* __restrict__ out, int w, const De
                   int vertical, int stream, int32_t* __restrict__ table) {
   __shared__ RelayLds<S> s_lds[GPB];
   int r;
-  if (!pass_radius(st, radius, r)) return;
+  if (!pass_radius(st, radius, w, r)) return;
   blur_relay_lines<S, DP, GPB>(in, out, w, r, vertical, stream != 0, blockIdx.x, gridDim.x, s_lds);
   if (table != nullptr) fill_group_table<GPB * kRelayWaves * 64>(table, st->beta, st->keys, blockIdx.x, gridDim.x);
 }
@@ -1045,7 +1046,7 @@ void k_blur_relay(const S* __restrict__ in, S* __restrict__ out, int w, const De
 //
 // The line is loaded chunk by chunk (16 positions aligned to multiples of 16)
 // into a ring of rows (row = position modulo the ring). Step e takes chunk e:
-// first its positions up to min(r, w - 1) go into the starting sum, then, from
+// first its positions up to r go into the starting sum, then, from
 // step A = ceil(r / kChunk) on, the outputs x of chunk e - A (x + r lies in
 // chunk e or e - 1). While the ring also holds every leaving position
 // x - r - 1 still to come beside the chunks in flight, leaving values are read
@@ -1135,7 +1136,7 @@ struct RingLine {
   int64_t step;     // elements between consecutive positions of a line
   int64_t ld_off;   // element offset of this lane's load piece at position 0
   bool ld_ok;       // the load piece's line exists (else its loads are clamped and its stores skipped)
-  int w, r, first_hi;
+  int w, r;
   int n_chunks;  // M: chunks of the line
   int ahead;     // A = ceil(r / kChunk): step e sums the outputs of chunk e - A
   int lag;       // the leaving chunk needed at step e is e - lag (split ring)
@@ -1271,14 +1272,14 @@ struct RingLine {
     }
   }
 
-  // The positions of chunk e up to first_hi, in ascending order, into the
+  // The positions of chunk e up to r, in ascending order, into the
   // starting sum (position 0 starts it).
   __device__ __forceinline__ void start_sum(int e, float& s) const {
     const int t0 = e * kChunk;
     float v[kChunk];
 #pragma unroll
     for (int p = 0; p < kChunk; ++p) v[p] = (lds->ring[(t0 + p) & enter_mask][lane]);
-    if (t0 > 0 && t0 + kChunk - 1 <= first_hi) {
+    if (t0 > 0 && t0 + kChunk - 1 <= r) {
 #pragma unroll
       for (int p = 0; p < kChunk; ++p) s = s + v[p];
     } else {
@@ -1286,7 +1287,7 @@ struct RingLine {
       for (int p = 0; p < kChunk; ++p) {
         const int t = t0 + p;
         const float added = t == 0 ? v[p] : s + v[p];
-        s = t <= first_hi ? added : s;
+        s = t <= r ? added : s;
       }
     }
   }
@@ -1389,7 +1390,7 @@ struct RingLine {
     for (int e = 0; e < n_steps; ++e) {
       if (slot_loads(e) > 0) wait_vm_dyn(ops_after(e));
       exchange<Sh::kRegChunks>(keep, slot, e);
-      if (e * kChunk <= first_hi) start_sum(e, s);
+      if (e * kChunk <= r) start_sum(e, s);
       if (e >= ahead) outputs(e - ahead, s);
       issue(e + Sh::kDepth - 1);
       slot = slot + 1 == lag ? 0 : slot + 1;
@@ -1405,7 +1406,7 @@ struct RingLine {
     float s = 0.0f;
     for (int e = 0; e < n_steps; ++e) {
       if (slot_loads(e) > 0) wait_vm_dyn(ops_after(e));
-      if (e * kChunk <= first_hi) start_sum(e, s);
+      if (e * kChunk <= r) start_sum(e, s);
       if (e >= ahead) outputs(e - ahead, s);
       issue(e + Sh::kDepth - 1);
     }
@@ -1440,7 +1441,6 @@ __device__ __forceinline__ void blur_ring_line(const float* __restrict__ in, flo
       for (int x = 0; x < w; ++x) L.dst[own_off + x * L.step] = L.src[own_off + x * L.step];
     return;
   }
-  L.first_hi = r < w - 1 ? r : w - 1;
   L.n_chunks = (w + Sh::kChunk - 1) / Sh::kChunk;
   L.ahead = (r + Sh::kChunk - 1) / Sh::kChunk;
   L.n_steps = L.ahead + L.n_chunks;
@@ -1465,7 +1465,7 @@ void k_blur_ring(const float* __restrict__ in, float* __restrict__ out, int w, c
                  int radius, int vertical, int32_t* __restrict__ table) {
   __shared__ RingLds s_ring[kRingWavesPerBlock];
   int r;
-  if (!pass_radius(st, radius, r)) return;
+  if (!pass_radius(st, radius, w, r)) return;
   const int wib = threadIdx.x >> 6;
   const int64_t nwaves = static_cast<int64_t>(gridDim.x) * kRingWavesPerBlock;
   for (int64_t g = static_cast<int64_t>(blockIdx.x) * kRingWavesPerBlock + wib; g * (64 / DP) < w; g += nwaves)
@@ -2487,7 +2487,7 @@ void k_blur_relay_batch(const BatchGrid* __restrict__ grids, const uint32_t* __r
   const BatchGridView& g = batch_grid(grids, map, local);
   const DevState* st = global_ptr<const DevState>(g.state);
   int r;
-  if (!pass_radius(st, 0, r)) return;
+  if (!pass_radius(st, 0, g.w, r)) return;
   const int vertical = route_vertical(route);
   const S* in = route_grid<S>(g, (route >> 1) & 3);
   S* out = route_grid<S>(g, (route >> 3) & 3);
@@ -2503,7 +2503,7 @@ __global__ __launch_bounds__(kBlock) void k_blur_batch(const BatchGrid* __restri
   const BatchGridView& g = batch_grid(grids, map, local);
   const DevState* st = global_ptr<const DevState>(g.state);
   int r;
-  if (!pass_radius(st, 0, r)) return;
+  if (!pass_radius(st, 0, g.w, r)) return;
   const int vertical = route_vertical(route);
   const S* in = route_grid<S>(g, (route >> 1) & 3);
   S* out = route_grid<S>(g, (route >> 3) & 3);
