@@ -211,6 +211,7 @@ int32_t plas_sort(plas_handle h, const void* features, int64_t n, int32_t d, int
   int64_t timed_reorders = 0;
   int64_t slots = 0;  // reorder slots queued so far; slot i runs reorder k0 + i unless the sort has ended
   const int64_t k0 = S->k;  // reorders done before this call (a resumed sort)
+  int32_t r_seen = S->r;    // the radius when the host last looked; it only falls
   // Queues the reorders [from, to) of a chunk.
   auto queue_reorders = [&](int from, int to) -> int32_t {
     for (int i = from; i < to; ++i) {
@@ -224,13 +225,13 @@ int32_t plas_sort(plas_handle h, const void* features, int64_t n, int32_t d, int
       const void* src = G;
       for (int p = 0; p < passes; ++p) {
         void* dst = bufs[p & 1];
-        PLAS_HIP(h, plas::launch_blur_pass(src, dst, w, dp, storage, Sd, 0, 0, as<float>(h->inv), h->stream,
+        PLAS_HIP(h, plas::launch_blur_pass(src, dst, w, dp, storage, Sd, r_seen, 0, as<float>(h->inv), h->stream,
                                            p == 0 ? &table_fill : nullptr));
         src = dst;
       }
       for (int p = 0; p < passes; ++p) {
         void* dst = p == passes - 1 ? T : bufs[(passes + p) & 1];
-        PLAS_HIP(h, plas::launch_blur_pass(src, dst, w, dp, storage, Sd, 0, 1, as<float>(h->inv), h->stream));
+        PLAS_HIP(h, plas::launch_blur_pass(src, dst, w, dp, storage, Sd, r_seen, 1, as<float>(h->inv), h->stream));
         src = dst;
       }
       // One event ends the blur passes and starts the assignment.
@@ -268,6 +269,7 @@ int32_t plas_sort(plas_handle h, const void* features, int64_t n, int32_t d, int
     S = &h->state_host[at];
     const bool done = S->done != 0;
     const int64_t k_now = S->k;
+    r_seen = S->r;
     if (profile) {
       // Slots at or after the end of the sort returned at once.
       const int64_t ran = done ? std::max<int64_t>(0, std::min<int64_t>(chunk, k_now - k0 - first_slot)) : chunk;

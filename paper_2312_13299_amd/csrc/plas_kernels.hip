@@ -556,6 +556,14 @@ __device__ __forceinline__ Q load_quad(const Q* p) {
   }
 }
 
+template <bool nt>
+__device__ __forceinline__ void store_quad(float* p, const float4& v) {
+  if constexpr (nt)
+    __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v), reinterpret_cast<u32x4_t*>(p));
+  else
+    *reinterpret_cast<float4*>(p) = v;
+}
+
 // Blur pass for cells of at least 16 bytes: same arithmetic as k_blur (one
 // running sum per line and channel, same operation order), with the work of a
 // group of 64 / DP lines split over three waves of a block that meet at a
@@ -693,7 +701,7 @@ struct ChunkValues<uint16_t> {
   __device__ __forceinline__ float get(int i) const { return bf16_to_float(v[i]); }
 };
 
-template <typename S, int DP>
+template <typename S, int DP, bool NTS>
 struct RelayLine {
   using Sh = RelayShape<S>;
   static constexpr int kChunk = Sh::kChunk;
@@ -959,7 +967,7 @@ struct RelayLine {
   }
   __device__ static __forceinline__ void store_piece(S* dst, const float (&v)[16 / sizeof(S)]) {
     if constexpr (sizeof(S) == 4) {
-      *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+      store_quad<NTS>(dst, make_float4(v[0], v[1], v[2], v[3]));
     } else {
       uint4 u;
       u.x = float_to_bf16(v[0]) | (float_to_bf16(v[1]) << 16);
@@ -975,14 +983,15 @@ struct RelayLine {
 // block: group `sub` of block `bid` takes lines (bid * GPB + sub) * 64/DP ..
 // and walks on with a stride. Every group of a block takes the same number of
 // steps (past the last line it repeats that line without storing), so that
-// all its waves meet at the same barriers.
-template <typename S, int DP, int GPB>
+// all its waves meet at the same barriers. NTS: streaming stores (see
+// relay_streams_stores).
+template <typename S, int DP, int GPB, bool NTS>
 __device__ __forceinline__ void blur_relay_lines(const S* __restrict__ in, S* __restrict__ out, int w, int r,
                                                  int vertical, bool stream, int64_t bid, int64_t nblocks,
                                                  RelayLds<S>* lds) {
   constexpr int kLines = 64 / DP;
   using Sh = RelayShape<S>;
-  using L_t = RelayLine<S, DP>;
+  using L_t = RelayLine<S, DP, NTS>;
   const int wib = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
   const int lane = threadIdx.x & 63;
   const int sub = wib / kRelayWaves, role = wib % kRelayWaves;
@@ -1028,21 +1037,20 @@ constexpr int relay_waves_per_eu() {
   return sizeof(S) == 4 || GPB == 4 ? 3 : 5;
 }
 
-template <typename S, int DP, int GPB>
+template <typename S, int DP, int GPB, bool NTS>
 __global__ __launch_bounds__(GPB * kRelayWaves * 64) __attribute__((amdgpu_waves_per_eu(relay_waves_per_eu<S, GPB>())))
 void k_blur_relay(const S* __restrict__ in, S* __restrict__ out, int w, const DevState* __restrict__ st, int radius,
                   int vertical, int stream, int32_t* __restrict__ table) {
   __shared__ RelayLds<S> s_lds[GPB];
   int r;
   if (!pass_radius(st, radius, w, r)) return;
-  blur_relay_lines<S, DP, GPB>(in, out, w, r, vertical, stream != 0, blockIdx.x, gridDim.x, s_lds);
+  blur_relay_lines<S, DP, GPB, NTS>(in, out, w, r, vertical, stream != 0, blockIdx.x, gridDim.x, s_lds);
   if (table != nullptr) fill_group_table<GPB * kRelayWaves * 64>(table, st->beta, st->keys, blockIdx.x, gridDim.x);
 }
 
-// Blur pass of large float32 grids at middle radii (see blur_pass_dp): one
-// wave per group of 64 / DP lines loads, sums and stores, and keeps leaving
-// values in registers. Same arithmetic, LDS rows and direct loads as the
-// relay pass.
+// Blur pass of large float32 grids (see ring_rows and batch_ring): one wave
+// per group of 64 / DP lines loads, sums and stores, and keeps leaving values
+// in registers. Same arithmetic, LDS rows and direct loads as the relay pass.
 //
 // The line is loaded chunk by chunk (16 positions aligned to multiples of 16)
 // into a ring of rows (row = position modulo the ring). Step e takes chunk e:
@@ -1051,35 +1059,38 @@ void k_blur_relay(const S* __restrict__ in, S* __restrict__ out, int w, const De
 // chunk e or e - 1). While the ring also holds every leaving position
 // x - r - 1 still to come beside the chunks in flight, leaving values are read
 // back from it; otherwise the ring is split in two halves and the leaving
-// chunks reach the upper half from 24 register slots, where each chunk was
-// kept since it entered (48 <= r <= 192), or from a second load stream (the
-// same positions again). Loads are issued at positions clamped into the line,
-// so every chunk is exactly kVec load instructions.
+// chunks reach the upper half from register slots, where each chunk was kept
+// since it entered (ring of 128 rows, one wave per SIMD: 24 slots, 48 <= r <=
+// 192; ring of 64 rows, two waves per SIMD: 8 slots, 16 <= r <= 64), or from a
+// second load stream (the same positions again). Loads are issued at positions
+// clamped into the line, so every chunk is exactly kVec load instructions.
 //
 // Waits. Every step issues, in this order, the stores of the chunk it summed
 // and then the loads of issue slot e + kDepth - 1 (entering chunk, then leaving
 // chunk); the number of operations issued after a chunk's last load follows
 // from that schedule (ops_after).
+template <int RR>
 struct RingShape {
   static constexpr int kRowBytes = 256;  // one position of the wave's lines
   static constexpr int kLanesPerRow = kRowBytes / 16;
   static constexpr int kPos = 64 / kLanesPerRow;  // positions per load instruction
   static constexpr int kChunk = 16;               // positions per chunk
   static constexpr int kVec = kChunk / kPos;      // load instructions per chunk
-  static constexpr int kDepth = 3;                // issue slots in flight, the one being summed included
-  static constexpr int kRingRows = 128;
+  static constexpr int kDepth = RR >= 128 ? 3 : 2;  // issue slots in flight, the one being summed included
+  static constexpr int kRingRows = RR;
   static constexpr int kSlots = kRingRows / kChunk;
-  static constexpr int kRegChunks = 24;      // register slots of leaving chunks
+  static constexpr int kRegChunks = RR >= 128 ? 24 : 8;  // register slots of leaving chunks
   static constexpr int kRegWords = kChunk;   // registers per chunk
   static constexpr int kHalfRows = kRingRows / 2;  // rows of each stream when the ring is split
   static_assert((kRingRows & (kRingRows - 1)) == 0, "ring shape");
   static_assert(kHalfRows / kChunk >= kDepth, "a split half holds the chunks in use and in flight");
 };
 
-// LDS of one wave: 36 KB.
+// LDS of one wave: 36 KB with 128 rows, 20 KB with 64.
+template <int RR>
 struct alignas(16) RingLds {
-  float ring[RingShape::kRingRows][64];
-  float out[RingShape::kChunk][64];
+  float ring[RingShape<RR>::kRingRows][64];
+  float out[RingShape<RR>::kChunk][64];
 };
 
 // Leaving values come from the entering ring when, at every step, the chunk
@@ -1087,8 +1098,9 @@ struct alignas(16) RingLds {
 // ceil(r / kChunk) chunks between a step's chunk and its outputs and
 // ceil((r + 1) / kChunk) between an output chunk and its leaving positions,
 // A + ceil((r + 1) / kChunk) <= kSlots + 1 - kDepth.
+template <int RR>
 __device__ __forceinline__ bool ring_leave(int r) {
-  using Sh = RingShape;
+  using Sh = RingShape<RR>;
   const int a = (r + Sh::kChunk - 1) / Sh::kChunk;
   const int b = (r + Sh::kChunk) / Sh::kChunk;
   return a + b <= Sh::kSlots + 1 - Sh::kDepth;
@@ -1126,9 +1138,9 @@ __device__ __forceinline__ void wait_vm_dyn(int n) {
   }
 }
 
-template <int DP, bool NT>
+template <int DP, int RR, bool NT>
 struct RingLine {
-  using Sh = RingShape;
+  using Sh = RingShape<RR>;
   static constexpr int kChunk = Sh::kChunk;
   static constexpr int kPiecesPerCell = DP / 4;
   const float* __restrict__ src;  // the pass's input grid
@@ -1146,7 +1158,7 @@ struct RingLine {
   bool regs;         // split, and the leaving chunks come from registers instead of a second load stream
   int enter_mask;    // ring rows of the entering stream - 1
   uint32_t ring_m0;  // LDS byte address of ring row 0 (the same for all lanes)
-  RingLds* lds;
+  RingLds<RR>* lds;
 
   __device__ __forceinline__ int clamp_pos(int t) const { return t < 0 ? 0 : (t > w - 1 ? w - 1 : t); }
 
@@ -1202,10 +1214,10 @@ struct RingLine {
     return split ? Sh::kHalfRows + (t & (Sh::kHalfRows - 1)) : (t & (Sh::kRingRows - 1));
   }
   __device__ __forceinline__ float enter_val(int x) const {
-    return (lds->ring[enter_row(x)][lane]);
+    return lds->ring[enter_row(x)][lane];
   }
   __device__ __forceinline__ float leave_val(int x) const {
-    return (lds->ring[leave_row(x)][lane]);
+    return lds->ring[leave_row(x)][lane];
   }
 
   // Outputs x0 .. x0 + kChunk - 1, all inside the grid, all with (ENTER) or
@@ -1230,8 +1242,8 @@ struct RingLine {
       const float* lp = &lds->ring[LEAVE ? lb : 0][lane];
 #pragma unroll
       for (int p = 0; p < kChunk; ++p) {
-        if (ENTER) e[p] = (ep[p * 64]);
-        if (LEAVE) l[p] = (lp[p * 64]);
+        if (ENTER) e[p] = ep[p * 64];
+        if (LEAVE) l[p] = lp[p * 64];
       }
     } else {
 #pragma unroll
@@ -1278,7 +1290,7 @@ struct RingLine {
     const int t0 = e * kChunk;
     float v[kChunk];
 #pragma unroll
-    for (int p = 0; p < kChunk; ++p) v[p] = (lds->ring[(t0 + p) & enter_mask][lane]);
+    for (int p = 0; p < kChunk; ++p) v[p] = lds->ring[(t0 + p) & enter_mask][lane];
     if (t0 > 0 && t0 + kChunk - 1 <= r) {
 #pragma unroll
       for (int p = 0; p < kChunk; ++p) s = s + v[p];
@@ -1293,7 +1305,9 @@ struct RingLine {
   }
 
   // Output chunk k (positions x0 = k kChunk ..): sum, then store the chunk's
-  // rows as 16-byte pieces.
+  // rows as 16-byte pieces, with a streaming hint where the grids are beyond
+  // the Infinity Cache (the 64-row ring; 1448^2 x 64: whole sort 5568 against
+  // 5668 ms).
   __device__ __forceinline__ void outputs(int k, float& s) const {
     const int x0 = k * kChunk;
     const int x1 = x0 + kChunk - 1;
@@ -1323,8 +1337,8 @@ struct RingLine {
     for (int i = 0; i < Sh::kVec; ++i) {
       const int x = x0 + Sh::kPos * i + q;
       if (x < w && ld_ok)
-        *reinterpret_cast<float4*>(dst + ld_off + static_cast<int64_t>(x) * step) =
-            *reinterpret_cast<const float4*>(&lds->out[Sh::kPos * i + q][4 * j]);
+        store_quad<(RR < 128)>(dst + ld_off + static_cast<int64_t>(x) * step,
+                               *reinterpret_cast<const float4*>(&lds->out[Sh::kPos * i + q][4 * j]));
     }
   }
 
@@ -1332,7 +1346,7 @@ struct RingLine {
   // entering half and swaps it with register slot e mod lag, which holds
   // chunk e - lag, the newest leaving chunk of the step; that chunk goes to
   // its rows of the leaving half. A chunk is used as leaving values at steps
-  // e and e + 1 only, and the leaving half holds four. A chunk's kChunk rows
+  // e and e + 1 only, and the leaving half holds at least two. A chunk's rows
   // are contiguous in both halves, so it moves as 16-byte pieces (lane l
   // holds bytes 16 l .. of each KB) in whatever order: only its place in the
   // leaving half matters. Past the last chunk the rows read are stale; what
@@ -1414,11 +1428,11 @@ struct RingLine {
 };
 
 // Lines line0 .. line0 + 64/DP - 1 of a ring pass (those below w), by one wave.
-template <int DP, bool NT>
+template <int DP, int RR, bool NT>
 __device__ __forceinline__ void blur_ring_line(const float* __restrict__ in, float* __restrict__ out, int w, int r,
-                                               int vertical, int64_t line0, int lane, RingLds* lds) {
-  using Sh = RingShape;
-  using L_t = RingLine<DP, NT>;
+                                               int vertical, int64_t line0, int lane, RingLds<RR>* lds) {
+  using Sh = RingShape<RR>;
+  using L_t = RingLine<DP, RR, NT>;
   L_t L;
   // Element offset of line l at position 0, and between positions.
   auto line_off = [&](int64_t l) { return vertical ? l * DP : l * w * DP; };
@@ -1444,7 +1458,7 @@ __device__ __forceinline__ void blur_ring_line(const float* __restrict__ in, flo
   L.n_chunks = (w + Sh::kChunk - 1) / Sh::kChunk;
   L.ahead = (r + Sh::kChunk - 1) / Sh::kChunk;
   L.n_steps = L.ahead + L.n_chunks;
-  L.split = !ring_leave(r);
+  L.split = !ring_leave<RR>(r);
   // Step e sums outputs of chunk k = e - A, whose leaving positions reach
   // up to k kChunk + kChunk - 2 - r: chunk e - lag.
   L.lag = L.ahead - ((Sh::kChunk - 2 - r) >= 0 ? (Sh::kChunk - 2 - r) / Sh::kChunk
@@ -1456,20 +1470,27 @@ __device__ __forceinline__ void blur_ring_line(const float* __restrict__ in, flo
   L.run();
 }
 
-// One group of 64/DP lines per wave; two-wave blocks of 72 KB LDS, so that
-// four waves share a CU, one per SIMD with all its registers.
+// One group of 64/DP lines per wave, in two-wave blocks; block `bid` of
+// `nblocks` takes groups 2 bid and 2 bid + 1 and walks on with a stride. With
+// 128 rows (72 KB LDS) four waves share a CU, one per SIMD with all its
+// registers; with 64 rows (40 KB) eight do.
 constexpr int kRingWavesPerBlock = 2;
-template <int DP, bool NT>
-__global__ __launch_bounds__(kRingWavesPerBlock * 64) __attribute__((amdgpu_waves_per_eu(1)))
+template <int DP, int RR, bool NT>
+__device__ __forceinline__ void blur_ring_lines(const float* __restrict__ in, float* __restrict__ out, int w, int r,
+                                                int vertical, int64_t bid, int64_t nblocks, RingLds<RR>* lds) {
+  const int wib = threadIdx.x >> 6;
+  for (int64_t g = bid * kRingWavesPerBlock + wib; g * (64 / DP) < w; g += nblocks * kRingWavesPerBlock)
+    blur_ring_line<DP, RR, NT>(in, out, w, r, vertical, g * (64 / DP), threadIdx.x & 63, lds + wib);
+}
+
+template <int DP, int RR, bool NT>
+__global__ __launch_bounds__(kRingWavesPerBlock * 64) __attribute__((amdgpu_waves_per_eu(RR >= 128 ? 1 : 2)))
 void k_blur_ring(const float* __restrict__ in, float* __restrict__ out, int w, const DevState* __restrict__ st,
                  int radius, int vertical, int32_t* __restrict__ table) {
-  __shared__ RingLds s_ring[kRingWavesPerBlock];
+  __shared__ RingLds<RR> s_ring[kRingWavesPerBlock];
   int r;
   if (!pass_radius(st, radius, w, r)) return;
-  const int wib = threadIdx.x >> 6;
-  const int64_t nwaves = static_cast<int64_t>(gridDim.x) * kRingWavesPerBlock;
-  for (int64_t g = static_cast<int64_t>(blockIdx.x) * kRingWavesPerBlock + wib; g * (64 / DP) < w; g += nwaves)
-    blur_ring_line<DP, NT>(in, out, w, r, vertical, g * (64 / DP), threadIdx.x & 63, s_ring + wib);
+  blur_ring_lines<DP, RR, NT>(in, out, w, r, vertical, blockIdx.x, gridDim.x, s_ring);
   if (table != nullptr)
     fill_group_table<kRingWavesPerBlock * 64>(table, st->beta, st->keys, blockIdx.x, gridDim.x);
 }
@@ -2491,7 +2512,7 @@ void k_blur_relay_batch(const BatchGrid* __restrict__ grids, const uint32_t* __r
   const int vertical = route_vertical(route);
   const S* in = route_grid<S>(g, (route >> 1) & 3);
   S* out = route_grid<S>(g, (route >> 3) & 3);
-  blur_relay_lines<S, DP, GPB>(in, out, g.w, r, vertical, stream != 0, local, g.blur_blocks, s_lds);
+  blur_relay_lines<S, DP, GPB, false>(in, out, g.w, r, vertical, stream != 0, local, g.blur_blocks, s_lds);
   if (route_table(route))
     fill_group_table<GPB * kRelayWaves * 64>(global_ptr<int32_t>(g.table), st->beta, st->keys, local, g.blur_blocks);
 }
@@ -2656,16 +2677,44 @@ hipError_t launch_ingest(const void* features, int input_bf16, int64_t n, int d,
   return hipGetLastError();
 }
 
-// Line groups of a pass that takes the ring kernel (float32, grids in flight
-// over kLargeWorkingSetBytes): about one per SIMD. There memory bounds the
-// pass, and the register slots spare the second read of leaving values that
-// the relay ring does not hold (1024^2 x 64, row / column pass inside sorts:
-// 97 / 90 us against 126 / 122 us at radii 32 to 192, 117 / 114 against 122 /
-// 119 above, 92 / 86 both below). With fewer groups a wave that loads, sums
-// and stores in turn is the bound (2091^2 x 16, 523 groups: 140 / 138 us
-// against 117 / 129); with more than fit the chip at four per CU its waves
-// run in two rounds.
-constexpr int64_t kRingMinGroups = 769, kRingMaxGroups = 1024;
+constexpr int64_t kInfinityCacheBytes = int64_t(256) << 20;
+// Above this the Infinity Cache does not hold a pass's input and output beside
+// what the assignment reads next.
+constexpr int64_t kLargeWorkingSetBytes = kInfinityCacheBytes / 2;
+
+bool blur_large_working_set(int64_t working_bytes) { return working_bytes > kLargeWorkingSetBytes; }
+
+// Ring rows of a float32 pass at radius r over `groups` line groups of cells of
+// DP channels, in a grid of `bytes`; 0: the relay kernel.
+//
+// 128 rows, about one group per SIMD: where memory bounds the pass, the
+// register slots spare the second read of leaving values that the relay ring
+// does not hold (1024^2 x 64, row / column pass inside sorts: 97 / 90 us
+// against 126 / 122 us at radii 32 to 192, 117 / 114 against 122 / 119 above,
+// 92 / 86 both below). With fewer groups a wave that loads, sums and stores in
+// turn is the bound (2091^2 x 16, 523 groups: 140 / 138 us against 117 / 129);
+// with more than fit the chip at four per CU its waves run in two rounds.
+//
+// 64 rows, up to two groups per SIMD. Reorders of whole sorts, us, against the
+// relay kernel:
+//  - r = 32 to 64, where the slots hold the leaving values: 1040^2 x 64 342 and
+//    354 at r = 32, 1150^2 400 and 453, 1448^2 583 and 706, 2020^2 1166 and
+//    1405, 2600^2 x 32 1019 and 1231. Cells of 16 channels gain too little
+//    from it (4200^2 x 16 1916 and 1752);
+//  - r of 2/5 of a side and more, where lines take up to half as many steps
+//    again and the relay's, four groups per CU, run in two rounds: 1150^2 x 64
+//    483 and 489 at half a side, 1448^2 705 and 741, 2020^2 1358 and 1439,
+//    4200^2 x 16 2370 and 2555 (at 3/10: 1448^2 735 and 712, 2020^2 1442 and
+//    1385). Grids of little more than the cache stay (1040^2 398 and 387).
+//    Between, and below r = 32, the relay pass is as fast or faster.
+constexpr int64_t kRingMinGroups = 769, kRingMaxGroups = 1024, kSmallRingMaxGroups = 2048;
+template <int DP>
+inline int ring_rows(int w, int64_t groups, int64_t bytes, int r) {
+  if (groups >= kRingMinGroups && groups <= kRingMaxGroups) return blur_large_working_set(bytes) ? 128 : 0;
+  if (DP < 16 || groups <= kRingMaxGroups || groups > kSmallRingMaxGroups) return 0;
+  if (DP >= 32 && r >= 32 && r <= 64) return bytes > kInfinityCacheBytes ? 64 : 0;
+  return 5 * static_cast<int64_t>(r) >= 2 * static_cast<int64_t>(w) && 8 * bytes > 9 * kInfinityCacheBytes ? 64 : 0;
+}
 
 // Line groups per block of a relay column pass over a large working set:
 // neighbouring groups walk down the same grid rows at the same time, and one
@@ -2680,6 +2729,19 @@ constexpr int64_t kRingMinGroups = 769, kRingMaxGroups = 1024;
 template <typename S>
 inline int relay_column_groups(int64_t groups) {
   return sizeof(S) == 2 || groups <= 768 ? 3 : 2;
+}
+
+// Streaming stores of a float32 relay pass over more than kRingMaxGroups line
+// groups (so of two groups per block along columns): what the next kernel reads
+// back from the Infinity Cache is then worth less than the lines the stores
+// push out. Below r = 32, where a pass reads once, that takes larger grids.
+// Reorders of whole sorts, us, with plain and streaming stores: 1448^2 x 64 584
+// and 592 (r = 3), 725 and 708 (65); 1800^2 948 and 927, 1158 and 1088; 2091^2
+// 1299 and 1243, 1589 and 1495; 2100^2 x 32 664 and 658, 840 and 789; 1100^2 x
+// 64 342 and 354, 430 and 436; with fewer groups (2091^2 x 16) the same within
+// 1 %.
+inline bool relay_streams_stores(int64_t groups, int64_t bytes, int r) {
+  return groups > kRingMaxGroups && 2 * bytes > (r >= 32 ? 3 : 5) * kInfinityCacheBytes;
 }
 
 // One pass for storage S and DP channels: the relay or ring kernel when
@@ -2698,32 +2760,53 @@ hipError_t blur_pass_dp(const void* in, void* out, int w, const DevState* st, in
   S* dst = static_cast<S*>(out);
   if constexpr (staged_cells<S, DP>()) {
     const int64_t groups = staged_groups<DP>(w);
-    const bool large = blur_large_working_set(static_cast<int64_t>(w) * w * DP * static_cast<int64_t>(sizeof(S)));
+    const int64_t bytes = static_cast<int64_t>(w) * w * DP * static_cast<int64_t>(sizeof(S));
+    const bool large = blur_large_working_set(bytes);
     const int streams = large && vertical ? 1 : 0;
     if constexpr (sizeof(S) == 4) {
-      if (large && groups >= kRingMinGroups && groups <= kRingMaxGroups) {
-        const int blocks = with_table((groups + kRingWavesPerBlock - 1) / kRingWavesPerBlock, kRingWavesPerBlock * 64);
-        if (streams)
-          k_blur_ring<DP, true><<<blocks, kRingWavesPerBlock * 64, 0, stream>>>(src, dst, w, st, radius, vertical, ta.table);
-        else
-          k_blur_ring<DP, false><<<blocks, kRingWavesPerBlock * 64, 0, stream>>>(src, dst, w, st, radius, vertical, ta.table);
+      const int rows = ring_rows<DP>(w, groups, bytes, radius);
+      if (rows != 0) {
+        constexpr int kThreads = kRingWavesPerBlock * 64;
+        const int blocks = with_table((groups + kRingWavesPerBlock - 1) / kRingWavesPerBlock, kThreads);
+        if (rows == 128 && streams)
+          k_blur_ring<DP, 128, true><<<blocks, kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, ta.table);
+        else if (rows == 128)
+          k_blur_ring<DP, 128, false><<<blocks, kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, ta.table);
+        else if constexpr (DP >= 16) {
+          if (streams)
+            k_blur_ring<DP, 64, true><<<blocks, kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, ta.table);
+          else
+            k_blur_ring<DP, 64, false><<<blocks, kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, ta.table);
+        }
         return hipGetLastError();
       }
     }
     const int per_block = large && vertical ? relay_column_groups<S>(groups) : 1;
     const int blocks = with_table((groups + per_block - 1) / per_block, per_block * kRelayWaves * 64);
     constexpr int kThreads = kRelayWaves * 64;
+    if constexpr (sizeof(S) == 4 && DP >= 16) {
+      if (relay_streams_stores(groups, bytes, radius)) {
+        if (per_block == 1)
+          k_blur_relay<S, DP, 1, true><<<blocks, kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, streams,
+                                                                        ta.table);
+        else
+          k_blur_relay<S, DP, 2, true><<<blocks, 2 * kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, streams,
+                                                                            ta.table);
+        return hipGetLastError();
+      }
+    }
     switch (per_block) {
       case 1:
-        k_blur_relay<S, DP, 1><<<blocks, kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, streams, ta.table);
+        k_blur_relay<S, DP, 1, false><<<blocks, kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, streams,
+                                                                       ta.table);
         break;
       case 2:
-        k_blur_relay<S, DP, 2><<<blocks, 2 * kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, streams,
-                                                                   ta.table);
+        k_blur_relay<S, DP, 2, false><<<blocks, 2 * kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, streams,
+                                                                          ta.table);
         break;
       default:
-        k_blur_relay<S, DP, 3><<<blocks, 3 * kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, streams,
-                                                                   ta.table);
+        k_blur_relay<S, DP, 3, false><<<blocks, 3 * kThreads, 0, stream>>>(src, dst, w, st, radius, vertical, streams,
+                                                                          ta.table);
     }
   } else {
     const int blocks = with_table((blur_reg_waves<DP>(w) + kWavesPerBlock - 1) / kWavesPerBlock, kBlock);
@@ -2821,12 +2904,6 @@ hipError_t launch_vad_in_place(const void* features, int input_bf16, const int32
 // ---- batch
 
 bool staged_blur(int dp, int storage) { return dp * (storage == kStorageBF16 ? 2 : 4) >= 16; }
-
-// Above this the Infinity Cache (256 MB) does not hold a pass's input and
-// output beside what the assignment reads next.
-constexpr int64_t kLargeWorkingSetBytes = int64_t(128) << 20;
-
-bool blur_large_working_set(int64_t working_bytes) { return working_bytes > kLargeWorkingSetBytes; }
 
 int batch_blur_blocks(int w, int dp, int storage, int groups_per_block, int64_t max_cells) {
   int64_t blocks = 0, threads = 0;

@@ -66,7 +66,8 @@ struct TableArgs {
 
 // One blur pass (vertical = 0: rows, 1: columns) with radius st->r, or
 // `radius` if st is NULL (a pass queued after the end of the sort returns at
-// once). inv: float32 1/c for c = 0..w (the register kernel's multipliers).
+// once). With st, `radius` is the one the caller last saw there: it helps to
+// choose the kernel, and every kernel is right at every radius. inv: float32 1/c for c = 0..w (the register kernel's multipliers).
 hipError_t launch_blur_pass(const void* in, void* out, int w, int dp, int storage, const DevState* st,
                             int radius, int vertical, const float* inv, hipStream_t stream,
                             const TableArgs* table = nullptr);
