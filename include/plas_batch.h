@@ -54,7 +54,9 @@ typedef struct {
     int32_t side_hi;
     int32_t blur_waves_per_block; /* blur of cells of 16 bytes or more: summing waves per block, each
                                      walking 64/dp lines (with a loading and a storing wave beside
-                                     it); 1, 2 or 4; 0: the library's choice */
+                                     it); 1, 2 or 4; 0: the library's choice. float32 grids that run
+                                     in more than 128 MiB together may take a pass of one fixed
+                                     shape instead, as their radii suit it. */
     int32_t assign_blocks;        /* blocks per sort for the assignment; 0: the library's choice */
 } plas_tune_entry;
 

@@ -73,7 +73,7 @@ struct Launch {
   int kind;
   int dp;
   int storage;
-  int wpb;
+  int wpb;         // blur: groups_per_block of plas::launch_blur_batch
   int large;       // blur: the running grids are a large working set (plas::blur_large_working_set)
   size_t map_off;  // byte offset of the block map in the plan
   int blocks;
@@ -89,6 +89,8 @@ struct Sort {
   DeviceBuffer mem;
   plas::BatchGrid grid{};
   int wpb = kDefaultWavesPerBlock;
+  bool ring = false;  // the plan sends the blur to the ring kernel
+  int32_t r = 0;      // the radius when the host last looked; it only falls
   int assign_cap = 0;
   int slot = -1;
   bool running = false;
@@ -100,9 +102,11 @@ struct Sort {
   int64_t footprint = 0;
 };
 
-// Lines per block of a sort's blur launches (0 for the register kernel,
-// which has one fixed shape).
-int blur_wpb(const Sort& s) { return plas::staged_blur(s.dp, s.storage) ? s.wpb : 0; }
+// Line groups per block of a sort's blur launches (the ring and the register
+// kernel have one fixed shape).
+int blur_wpb(const Sort& s) {
+  return s.ring ? plas::kBatchRing : plas::staged_blur(s.dp, s.storage) ? s.wpb : kDefaultWavesPerBlock;
+}
 
 }  // namespace
 
@@ -283,8 +287,8 @@ class BatchRun {
     g.trace = reinterpret_cast<plas_level_out*>(base + o_trace);
     g.state = reinterpret_cast<DevState*>(base + o_state);
     g.w = s.w;
-    g.blur_blocks = plas::batch_blur_blocks(s.w, s.dp, s.storage, s.wpb, s.max_cells);
-    // The assignment's share is set with the plan (rebuild).
+    s.r = s.levels[0].r;
+    // The block counts are set with the plan (rebuild).
 
     // The start arrangement and the features in its order (as plas_sort).
     hipStream_t stream = b_->stream;
@@ -372,10 +376,13 @@ class BatchRun {
         finished_.push_back(s.tag);
         continue;
       }
+      s.r = hs.r;
       // Every queued slot has run and been controlled by now.
       if (hs.k != s.slots || hs.k > s.max_k)
         return fail(h_, PLAS_ERR_HIP, "device controller made no progress");
     }
+    // Radii at which the blur is to take another kernel.
+    if (!dirty_ && ring_widths() != ring_widths_) dirty_ = true;
     return PLAS_OK;
   }
 
@@ -394,6 +401,22 @@ class BatchRun {
   }
 
  private:
+  // The cell widths (a power of two each) whose float32 grids take the ring kernel.
+  int32_t ring_widths() const {
+    int32_t widths = 0;
+    for (int dp = 16; dp <= 64 && large_; dp *= 2) {
+      int64_t groups = 0, gain = 0;
+      for (int slot : run_list_) {
+        const Sort& s = sorts_[slot];
+        if (s.dp != dp || s.storage != plas::kStorageF32) continue;
+        groups += plas::blur_groups(s.w, s.dp);
+        gain += plas::batch_ring_gain(s.w, s.dp, s.r);
+      }
+      if (plas::batch_ring(groups, gain)) widths |= dp;
+    }
+    return widths;
+  }
+
   int32_t apply_tuning(Sort& s) {
     s.wpb = kDefaultWavesPerBlock;
     s.assign_cap = 0;
@@ -468,10 +491,20 @@ class BatchRun {
                      [&](int a, int c) { return sorts_[a].w > sorts_[c].w; });
     // Assignment blocks: what the tuning table says, else the sort's share of
     // the blocks that a launch over all of them takes.
-    int64_t all_items = 0;
-    for (int slot : run_list_) all_items += sorts_[slot].max_items;
+    // The blur's kernels: the working set is the bytes of all running grids,
+    // which the passes of a reorder stream through together.
+    int64_t all_items = 0, working_bytes = 0;
+    for (int slot : run_list_) {
+      const Sort& s = sorts_[slot];
+      all_items += s.max_items;
+      working_bytes += s.n * s.dp * (s.storage == plas::kStorageBF16 ? 2 : 4);
+    }
+    large_ = plas::blur_large_working_set(working_bytes) ? 1 : 0;
+    ring_widths_ = ring_widths();
     for (int slot : run_list_) {
       Sort& s = sorts_[slot];
+      s.ring = s.storage == plas::kStorageF32 && (ring_widths_ & s.dp) != 0;
+      s.grid.blur_blocks = plas::batch_blur_blocks(s.w, s.dp, s.storage, blur_wpb(s), s.max_cells);
       const int64_t most = kBatchAssignShare * static_cast<int64_t>(plas::assign_blocks_cap(s.storage));
       const int share = static_cast<int>(std::max<int64_t>(1, (most * s.max_items + all_items - 1) / all_items));
       s.grid.assign_blocks =
@@ -483,7 +516,7 @@ class BatchRun {
     off = align_up(off + run_list_.size() * sizeof(int32_t));
     launches_.clear();
     std::vector<std::vector<uint32_t>> maps;
-    auto add_launch = [&](int kind, int dp, int storage, int wpb, int regs, const std::vector<int>& members) {
+    auto add_launch = [&](int kind, int dp, int storage, int wpb, int large, const std::vector<int>& members) {
       std::vector<uint32_t> map;
       for (int slot : members) {
         const plas::BatchGrid& g = sorts_[slot].grid;
@@ -491,24 +524,17 @@ class BatchRun {
         for (int b = 0; b < nb; ++b) map.push_back((static_cast<uint32_t>(slot) << 16) | static_cast<uint32_t>(b));
       }
       if (map.empty()) return;
-      Launch L{kind, dp, storage, wpb, regs, off, static_cast<int>(map.size())};
+      Launch L{kind, dp, storage, wpb, large, off, static_cast<int>(map.size())};
       off = align_up(off + map.size() * sizeof(uint32_t));
       launches_.push_back(L);
       maps.push_back(std::move(map));
     };
-    // Blur launches per (dp, storage, lines per block); assignment per (dp,
-    // storage). The working set is the bytes of all running grids, which the
-    // passes of a reorder stream through together.
-    int64_t working_bytes = 0;
-    for (int slot : run_list_) {
-      const Sort& s = sorts_[slot];
-      working_bytes += s.n * s.dp * (s.storage == plas::kStorageBF16 ? 2 : 4);
-    }
-    const int large = plas::blur_large_working_set(working_bytes) ? 1 : 0;
+    // Blur launches per (dp, storage, kernel and line groups per block);
+    // assignment per (dp, storage).
     for (int pass = 0; pass < 2; ++pass) {
       std::vector<std::array<int, 4>> keys;
       auto key_of = [&](const Sort& s) -> std::array<int, 4> {
-        return {s.dp, s.storage, pass == 0 ? blur_wpb(s) : 0, pass == 0 ? large : 0};
+        return {s.dp, s.storage, pass == 0 ? blur_wpb(s) : 0, pass == 0 ? large_ : 0};
       };
       for (int slot : run_list_) {
         const std::array<int, 4> k = key_of(sorts_[slot]);
@@ -564,8 +590,8 @@ class BatchRun {
       for (const int route : routes_)
         for (const Launch& L : launches_)
           if (L.kind == kBlur)
-            PLAS_HIP(h_, plas::launch_blur_batch(grids, map_of(L), L.blocks, L.dp, L.storage, L.wpb == 0 ? 4 : L.wpb,
-                                                 route, L.large, stream));
+            PLAS_HIP(h_, plas::launch_blur_batch(grids, map_of(L), L.blocks, L.dp, L.storage, L.wpb, route, L.large,
+                                                 stream));
       if (timed) PLAS_HIP(h_, hipEventRecord(b_->events[3 * i + 1], stream));
       for (const Launch& L : launches_)
         if (L.kind == kAssign)
@@ -584,6 +610,9 @@ class BatchRun {
   std::vector<int> routes_;  // blur passes of a reorder, in order
   bool graph_ = false;
   bool dirty_ = true;
+  // Of the plan: the running grids are a large working set; the ring's widths.
+  int large_ = 0;
+  int32_t ring_widths_ = 0;
   std::vector<Sort> sorts_;
   std::vector<int> run_list_;
   std::vector<Launch> launches_;

@@ -99,7 +99,7 @@ struct DevState {
 // Small status block copied to pinned host memory at each sync.
 struct HostStatus {
   int32_t done;
-  int32_t pad;
+  int32_t r;  // the radius of the next reorder
   int64_t k;
 };
 

@@ -2451,8 +2451,10 @@ __device__ void reorder_done(DevState* __restrict__ st, const LevelInfo* __restr
 // grids[i] holds sort i's buffers and state pair; a launch covers several
 // sorts, and its block map gives each block its sort and its index among
 // that sort's blocks: map[b] = (grid index << 16) | block index. Every block
-// then runs exactly the code of a single-sort launch of that sort's shape,
-// so each sort's result does not depend on the batch it runs in.
+// then runs the device functions of single-sort launches. A sort's blur may
+// take another kernel than it would alone (batch_ring, ring_rows); all of them
+// do the same operations in the same order, so each sort's result does not
+// depend on the batch it runs in.
 
 // The kernels' view of BatchGrid: the same layout, with every pointer
 // declared as device (global) memory. Pointers read from memory are
@@ -2517,6 +2519,23 @@ void k_blur_relay_batch(const BatchGrid* __restrict__ grids, const uint32_t* __r
     fill_group_table<GPB * kRelayWaves * 64>(global_ptr<int32_t>(g.table), st->beta, st->keys, local, g.blur_blocks);
 }
 
+template <int DP, bool NT>
+__global__ __launch_bounds__(kRingWavesPerBlock * 64) __attribute__((amdgpu_waves_per_eu(1)))
+void k_blur_ring_batch(const BatchGrid* __restrict__ grids, const uint32_t* __restrict__ map, int route) {
+  __shared__ RingLds<128> s_ring[kRingWavesPerBlock];
+  uint32_t local;
+  const BatchGridView& g = batch_grid(grids, map, local);
+  const DevState* st = global_ptr<const DevState>(g.state);
+  int r;
+  if (!pass_radius(st, 0, g.w, r)) return;
+  const int vertical = route_vertical(route);
+  const float* in = route_grid<float>(g, (route >> 1) & 3);
+  float* out = route_grid<float>(g, (route >> 3) & 3);
+  blur_ring_lines<DP, 128, NT>(in, out, g.w, r, vertical, local, g.blur_blocks, s_ring);
+  if (route_table(route))
+    fill_group_table<kRingWavesPerBlock * 64>(global_ptr<int32_t>(g.table), st->beta, st->keys, local, g.blur_blocks);
+}
+
 template <int DP, typename S>
 __global__ __launch_bounds__(kBlock) void k_blur_batch(const BatchGrid* __restrict__ grids,
                                                        const uint32_t* __restrict__ map, int route) {
@@ -2555,7 +2574,7 @@ void k_assign_batch(const BatchGrid* __restrict__ grids, const uint32_t* __restr
                  static_cast<uint32_t>(g.assign_blocks));
 }
 
-// (done, k) of each listed sort's state, for the host's check between
+// (done, r, k) of each listed sort's state, for the host's check between
 // chunks.
 __global__ __launch_bounds__(kBlock) void k_batch_status(const BatchGrid* __restrict__ grids,
                                                          const int32_t* __restrict__ list, int count,
@@ -2565,7 +2584,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_status(const BatchGrid* __rest
   const DevState* st = global_ptr<const DevState>(reinterpret_cast<const BatchGridView*>(grids)[list[i]].state);
   HostStatus hs;
   hs.done = st->done;
-  hs.pad = 0;
+  hs.r = st->r;
   hs.k = st->k;
   out[i] = hs;
 }
@@ -2905,21 +2924,44 @@ hipError_t launch_vad_in_place(const void* features, int input_bf16, const int32
 
 bool staged_blur(int dp, int storage) { return dp * (storage == kStorageBF16 ? 2 : 4) >= 16; }
 
+int64_t blur_groups(int w, int dp) { return (static_cast<int64_t>(w) * dp + 63) / 64; }
+
+// The ring kernel (128 rows) in batches. It reads leaving values once up to r =
+// 192, the relay up to r = 31; but it waits for its own loads, sums and stores
+// in turn, so many short lines run slower in it. Reorders, us, relay and ring
+// for all grids:
+//  - 32 <= r <= 192: four grids of 1024^2 x 64 1475 / 1210 at r = 40 and 1490 /
+//    1264 at 190, two of 1448^2 1534 / 1256 and 1536 / 1314, six of 724^2 1118 /
+//    975 and 1108 / 1091, two of 3600^2 x 16 2791 / 2232 and 3145 / 2573, eight
+//    of 300^2 to 724^2 x 64 794 / 702 and (140) 801 / 788; not where windows
+//    are a good part of the line (32 of 256^2 x 64 683 / 707 at r = 100);
+//  - below, 1024^2 1240 / 1201 at r = 3, 1448^2 1280 / 1244, 900^2 967 / 958,
+//    but 800^2 757 / 796, 300^2 to 724^2 663 / 683;
+//  - above, nothing (1024^2 1471 / 1466 at r = 300).
+// Two launches instead of one cost more than either (300^2 to 1024^2 at r =
+// 40: ring for all 888, for the three largest 944, for none 1065), so a batch
+// decides for all its grids of a width at once, by these gains times cells.
+// Cells of 16 channels and less have too few lines below 769 groups (2091^2 x
+// 16 814 / 952), and a launch of fewer than 769 groups leaves SIMDs idle.
+int64_t batch_ring_gain(int w, int dp, int r) {
+  const int64_t groups = blur_groups(w, dp), cells = static_cast<int64_t>(w) * w;
+  if (dp < 32 && groups < kRingMinGroups) return r < 32 ? -4 * cells : 0;
+  if (r < 32) return groups > 896 ? cells : -cells;
+  return r <= 192 && 3 * r <= w ? 4 * cells : 0;
+}
+bool batch_ring(int64_t groups, int64_t gain) { return groups >= kRingMinGroups && gain > 0; }
+
 int batch_blur_blocks(int w, int dp, int storage, int groups_per_block, int64_t max_cells) {
   int64_t blocks = 0, threads = 0;
-  int64_t groups = 0, waves = 0;
-  switch (dp) {
-    case 4: groups = staged_groups<4>(w); waves = blur_reg_waves<4>(w); break;
-    case 8: groups = staged_groups<8>(w); waves = blur_reg_waves<8>(w); break;
-    case 16: groups = staged_groups<16>(w); waves = blur_reg_waves<16>(w); break;
-    case 32: groups = staged_groups<32>(w); waves = blur_reg_waves<32>(w); break;
-    default: groups = staged_groups<64>(w); waves = blur_reg_waves<64>(w); break;
-  }
-  if (staged_blur(dp, storage)) {
+  const int64_t groups = blur_groups(w, dp);
+  if (staged_blur(dp, storage) && groups_per_block == kBatchRing) {
+    blocks = (groups + kRingWavesPerBlock - 1) / kRingWavesPerBlock;
+    threads = kRingWavesPerBlock * 64;
+  } else if (staged_blur(dp, storage)) {
     blocks = (groups + groups_per_block - 1) / groups_per_block;
     threads = kRelayWaves * 64 * groups_per_block;
   } else {
-    blocks = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
+    blocks = (groups + kWavesPerBlock - 1) / kWavesPerBlock;
     threads = kBlock;
   }
   const int64_t need = std::min<int64_t>(1024, (max_cells + threads - 1) / threads);
@@ -2947,6 +2989,15 @@ hipError_t blur_batch_dp(const BatchGrid* grids, const uint32_t* map, int blocks
                          int route, int large, hipStream_t stream) {
   if constexpr (staged_cells<S, DP>()) {
     const int streams = large && route_vertical(route) ? 1 : 0;
+    if constexpr (sizeof(S) == 4 && DP >= 16) {
+      if (groups_per_block == kBatchRing) {
+        if (streams)
+          k_blur_ring_batch<DP, true><<<blocks, kRingWavesPerBlock * 64, 0, stream>>>(grids, map, route);
+        else
+          k_blur_ring_batch<DP, false><<<blocks, kRingWavesPerBlock * 64, 0, stream>>>(grids, map, route);
+        return hipGetLastError();
+      }
+    }
     constexpr int kThreads = kRelayWaves * 64;
     switch (groups_per_block) {
       case 1: k_blur_relay_batch<S, DP, 1><<<blocks, kThreads, 0, stream>>>(grids, map, route, streams); break;

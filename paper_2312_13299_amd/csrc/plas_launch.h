@@ -104,17 +104,28 @@ hipError_t launch_vad_in_place(const void* features, int input_bf16, const int32
 // (device uint32[blocks]) holds (grid index << 16) | block index within the
 // grid's blocks; a grid's entries run from 0 to its block count - 1.
 // Blocks each grid takes per launch kind.
-// Whether blur passes of this shape use the staged kernel (cells of at
-// least 16 bytes); waves_per_block applies to those only.
+// Whether blur passes of this shape go through LDS (cells of at least 16
+// bytes): the relay or the ring kernel; groups_per_block applies to those only.
 bool staged_blur(int dp, int storage);
 // Whether the grids in flight (the one grid of a sort, every running grid
-// of a batch) are a large working set, more than 128 MiB: then staged
-// float32 passes keep the leaving values in registers rather than reading
-// them a second time, and column passes stream their loads.
+// of a batch) are a large working set, more than 128 MiB: then column passes
+// stream their loads, and float32 passes may take the ring kernel (ring_rows,
+// batch_ring).
 bool blur_large_working_set(int64_t working_bytes);
+// Groups of 64 / dp lines of a pass.
+int64_t blur_groups(int w, int dp);
+// What the ring kernel gains (or, negative, costs) a float32 grid of a batch at
+// radius r, in shares of the pass times cells; and whether the grids of one
+// width (16 channels or more) of a large working set take it, from the sums of
+// their groups and gains.
+int64_t batch_ring_gain(int w, int dp, int r);
+bool batch_ring(int64_t groups, int64_t gain);
+// groups_per_block of blur launches: 1, 2 or 4 line groups per block of the
+// relay kernel, or kBatchRing for the ring kernel.
+constexpr int kBatchRing = -1;
 // Blur blocks: enough for every line, and for filling a grouping table of
 // max_cells entries at about one entry per thread.
-int batch_blur_blocks(int w, int dp, int storage, int groups_per_block, int64_t max_cells);  // wpb: 1, 2, 4
+int batch_blur_blocks(int w, int dp, int storage, int groups_per_block, int64_t max_cells);
 int batch_assign_blocks(int64_t max_items, int dp, int storage, int cap);  // cap <= 0: the single-sort default
 int assign_blocks_cap(int storage);  // blocks of an assignment launch without a tuned value
 // A batch blur pass's route: its axis (vertical 0: rows, 1: columns), its
