@@ -113,13 +113,14 @@ int32_t plas_sort_batch(plas_handle h, const plas_batch_item* items, int32_t cou
 /*
  * Measure launch shapes for these items and write a tuning table: the items
  * are grouped into side buckets [ceil(2^(b/2)), ceil(2^((b+1)/2)) - 1]; for
- * each bucket, truncated batch sorts of its items (6 reorders at the first,
- * coarsest level and 6 at radius 15) are timed under each candidate blur
- * shape (1, 2, 4 summing waves per block, grids with cells of 16 bytes or more) and then each
- * candidate assignment block count (default, 256, 1024, 16384), keeping the
- * fastest. graph: as in plas_batch_config. table: host array of cap entries;
- * *entries receives the number written. The items' perm_out contents are
- * overwritten with those of the truncated runs.
+ * each bucket, each other blur shape (1, 2, 4 summing waves per block, grids
+ * with cells of 16 bytes or more) and then each other assignment block count
+ * (the library's choice, 256, 1024, 16384) is timed in the whole batch (all
+ * items running, those left out that do not fit the device together; 6
+ * reorders at the first, coarsest level and 6 at radius 15) and taken if the
+ * batch runs faster by more than measurements differ. graph: as in
+ * plas_batch_config. table: host array of cap entries; *entries receives the
+ * number written. The items' perm_out contents may be overwritten.
  */
 int32_t plas_autotune_batch(plas_handle h, const plas_batch_item* items, int32_t count,
                             const plas_sort_params* params, int32_t graph, plas_tune_entry* table,

@@ -30,6 +30,9 @@ constexpr int kDefaultWavesPerBlock = 1;
 // / 2 / 3 / 4 / 6: float32 79 / 76 / 75 / 71 / 72, bfloat16 44 / 39 / 37 / 38 /
 // 41 (4096 blocks for every sort: 145 and 103).
 constexpr int64_t kBatchAssignShare = 4;
+// A measured launch shape is taken if the batch's reorders take less than this
+// share of the time without it (repeated measurements differ by up to 1 %).
+constexpr double kTuneGain = 0.985;
 constexpr int kMaxSlots = 1 << 16;     // grid index field of a block map entry
 constexpr int kMaxLocalBlocks = 1 << 16;  // block index field
 
@@ -91,6 +94,7 @@ struct Sort {
   int wpb = kDefaultWavesPerBlock;
   bool ring = false;  // the plan sends the blur to the ring kernel
   int32_t r = 0;      // the radius when the host last looked; it only falls
+  DevState start{};   // the state before the first reorder
   int assign_cap = 0;
   int slot = -1;
   bool running = false;
@@ -306,6 +310,7 @@ class BatchRun {
     DevState* S = h_->state_host;
     plas_sort_params prm = prm_;
     init_sort_state(S, s.w, s.s, s.levels, prm, it.seed);
+    s.start = *S;
     PLAS_HIP(h_, hipMemcpyAsync(g.state, S, sizeof(DevState), hipMemcpyHostToDevice, stream));
     // The host sources above are freed or reused at return.
     PLAS_HIP(h_, hipStreamSynchronize(stream));
@@ -314,31 +319,62 @@ class BatchRun {
     return PLAS_OK;
   }
 
+  // The plan, and with graphs its capture, if the running sorts have changed.
+  int32_t prepare() {
+    if (dirty_) {
+      const int32_t st = rebuild();
+      if (st != PLAS_OK) return st;
+    }
+    if (!graph_ || exec_ != nullptr) return PLAS_OK;
+    hipStream_t stream = b_->stream;
+    PLAS_HIP(h_, hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
+    const int32_t st = enqueue_reorders(false);
+    hipGraph_t graph = nullptr;
+    const hipError_t e = hipStreamEndCapture(stream, &graph);
+    if (st != PLAS_OK) {
+      if (graph != nullptr) (void)hipGraphDestroy(graph);
+      return st;
+    }
+    if (e != hipSuccess) return hip_fail(h_, e, "hipStreamEndCapture");
+    graph_obj_ = graph;
+    PLAS_HIP(h_, hipGraphInstantiate(&exec_, graph_obj_, nullptr, nullptr, 0));
+    ++graph_builds;
+    return PLAS_OK;
+  }
+
+  // Sends every running sort back to the start of its first level with radius
+  // `most` or less (of its last level, if none has), on the arrangement it has
+  // by now, under another tuning table (for measurements: no sort's result).
+  int32_t restart(const plas_tune_entry* tune, int32_t tune_count, int32_t most) {
+    cfg_.tune = tune;
+    cfg_.tune_count = tune_count;
+    for (Sort& s : sorts_) {
+      if (!s.running) continue;
+      const int32_t st = apply_tuning(s);
+      if (st != PLAS_OK) return st;
+      size_t level = 0;
+      while (level + 1 < s.levels.size() && s.levels[level].r > most) ++level;
+      DevState at = s.start;
+      fill_state_for_level(&at, s.levels[level]);
+      at.level = static_cast<int32_t>(level);
+      PLAS_HIP(h_, hipMemcpyAsync(s.grid.state, &at, sizeof(DevState), hipMemcpyHostToDevice, b_->stream));
+      PLAS_HIP(h_, hipStreamSynchronize(b_->stream));
+      s.slots = 0;
+      s.r = at.r;
+    }
+    dirty_ = true;
+    return PLAS_OK;
+  }
+
   // Queue one chunk of reorders for every running sort and read their
   // status. Finished sorts are written out and leave the batch.
   int32_t chunk() {
     if (running() == 0) return PLAS_OK;
-    if (dirty_) {
-      int32_t st = rebuild();
-      if (st != PLAS_OK) return st;
-    }
+    const int32_t ready = prepare();
+    if (ready != PLAS_OK) return ready;
     hipStream_t stream = b_->stream;
     const plas::BatchGrid* grids = static_cast<const plas::BatchGrid*>(b_->plan.ptr);
     if (graph_) {
-      if (exec_ == nullptr) {
-        PLAS_HIP(h_, hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
-        const int32_t st = enqueue_reorders(false);
-        hipGraph_t graph = nullptr;
-        const hipError_t e = hipStreamEndCapture(stream, &graph);
-        if (st != PLAS_OK) {
-          if (graph != nullptr) (void)hipGraphDestroy(graph);
-          return st;
-        }
-        if (e != hipSuccess) return hip_fail(h_, e, "hipStreamEndCapture");
-        graph_obj_ = graph;
-        PLAS_HIP(h_, hipGraphInstantiate(&exec_, graph_obj_, nullptr, nullptr, 0));
-        ++graph_builds;
-      }
       PLAS_HIP(h_, hipGraphLaunch(exec_, stream));
       launches += launches_per_chunk_;
     } else {
@@ -673,6 +709,14 @@ int32_t run_batch(plas_context* h, const plas_batch_item* items, int32_t count, 
   return PLAS_OK;
 }
 
+int64_t job_footprint(int32_t side, int32_t d, int32_t storage, const plas_sort_params& prm) {
+  std::vector<LevelInfo> levels;
+  if (build_schedule(side, prm.radius_decay, prm.min_block, prm.start_radius, &levels) != PLAS_OK) return -1;
+  int64_t max_cells = 0;
+  for (const LevelInfo& lv : levels) max_cells = std::max<int64_t>(max_cells, static_cast<int64_t>(lv.beta) * lv.beta);
+  return static_cast<int64_t>(sort_layout(side, padded_channels(d), storage, levels.size(), max_cells).bytes);
+}
+
 int side_bucket(int32_t side) { return static_cast<int>(std::floor(2.0 * std::log2(static_cast<double>(side)))); }
 
 }  // namespace
@@ -745,79 +789,115 @@ int32_t plas_autotune_batch(plas_handle h, const plas_batch_item* items, int32_t
   if (static_cast<int32_t>(buckets.size()) > cap)
     return fail(h, PLAS_ERR_INVALID_ARGUMENT, "tune table capacity below the number of side buckets");
 
-  // Two truncated regimes: the first, coarsest level and the finest block
-  // size (radius 15, beta 16).
-  plas_sort_params coarse = base, fine = base;
-  coarse.max_reorders = 6;
-  fine.max_reorders = 6;
-  fine.start_radius = 15.0;
-  for (int b : buckets) {
-    std::vector<plas_batch_item> sub;
-    bool staged = false;
-    for (int32_t i = 0; i < count; ++i)
-      if (side_bucket(std::max(2, items[i].side)) == b) {
-        plas_batch_item it = items[i];
-        it.stats = nullptr;
-        sub.push_back(it);
-        staged = staged || plas::staged_blur(padded_channels(it.d), it.storage);
-      }
-    plas_tune_entry e{};
-    e.side_lo = static_cast<int32_t>(std::ceil(std::pow(2.0, b / 2.0)));
-    e.side_hi = static_cast<int32_t>(std::ceil(std::pow(2.0, (b + 1) / 2.0))) - 1;
-    // Sides exactly on a bucket edge: make sure the range holds them.
-    for (const plas_batch_item& it : sub) {
-      e.side_lo = std::min(e.side_lo, it.side);
-      e.side_hi = std::max(e.side_hi, it.side);
+  // A shape is worth what it does to the launches that it runs in, which hold
+  // every sort of the batch, so each candidate is timed with all of them
+  // running: six reorders at the first, coarsest level and six at radius 15
+  // (the finest block size). Sorts that would not fit the device together are
+  // left out.
+  const auto t0 = std::chrono::steady_clock::now();
+  base.max_reorders = 0;
+  plas_batch_config cfg;
+  plas_batch_config_init(&cfg);
+  cfg.graph = graph;
+  cfg.reorders_per_sync = 6;
+  size_t free_bytes = 0, total_bytes = 0;
+  PLAS_HIP(h, hipStreamSynchronize(h->stream));
+  PLAS_HIP(h, hipMemGetInfo(&free_bytes, &total_bytes));
+  StreamSwap swap(h, h->batch->stream);
+  BatchRun run(h, h->batch, base, cfg, t0);
+  int64_t room = static_cast<int64_t>(free_bytes) / 10 * 9;
+  for (int32_t i = 0; i < count; ++i) {
+    plas_batch_item it = items[i];
+    it.stats = nullptr;
+    st = check_features(h, it.features, it.n, it.d, it.side, it.layout, it.dtype);
+    if (st != PLAS_OK) return st;
+    if (valid_storage(it.storage)) {
+      const int64_t bytes = job_footprint(it.side, it.d, it.storage, base);
+      if (i > 0 && bytes > room) continue;
+      room -= bytes;
     }
-    auto measure = [&](const plas_tune_entry& cand, double* ms) -> int32_t {
-      plas_batch_config cfg;
-      plas_batch_config_init(&cfg);
-      cfg.graph = graph;
-      cfg.tune = &cand;
-      cfg.tune_count = 1;
-      double best = 1e300;
-      for (int rep = 0; rep < 2; ++rep) {
-        double total = 0.0;
-        for (const plas_sort_params* p : {&coarse, &fine}) {
-          plas_batch_stats bs{};
-          bs.struct_size = sizeof(bs);
-          const int32_t r = run_batch(h, sub.data(), static_cast<int32_t>(sub.size()), *p, cfg, &bs);
-          if (r != PLAS_OK) return r;
-          total += bs.loop_ms;
-        }
-        best = std::min(best, total);
-      }
-      *ms = best;
-      return PLAS_OK;
-    };
-    double best_ms = 1e300;
-    e.blur_waves_per_block = kDefaultWavesPerBlock;
-    e.assign_blocks = 0;
-    for (int wpb : {2, 1, 4}) {
-      if (!staged && wpb != kDefaultWavesPerBlock) continue;
-      plas_tune_entry cand = e;
-      cand.blur_waves_per_block = wpb;
-      double ms = 0.0;
-      st = measure(cand, &ms);
-      if (st != PLAS_OK) return st;
-      if (ms < best_ms) {
-        best_ms = ms;
-        e.blur_waves_per_block = wpb;
-      }
-    }
-    for (int cap_blocks : {256, 1024, 16384}) {
-      plas_tune_entry cand = e;
-      cand.assign_blocks = cap_blocks;
-      double ms = 0.0;
-      st = measure(cand, &ms);
-      if (st != PLAS_OK) return st;
-      if (ms < best_ms) {
-        best_ms = ms;
-        e.assign_blocks = cap_blocks;
-      }
-    }
-    table[(*entries)++] = e;
+    st = run.add(it, i);
+    if (st != PLAS_OK) return st;
   }
+
+  std::vector<plas_tune_entry> best(buckets.size());
+  // The better of two chunks at each radius, summed.
+  auto measure = [&](const std::vector<plas_tune_entry>& entries_now, double* ms) -> int32_t {
+    *ms = 0.0;
+    for (const int32_t most : {INT32_MAX, 15}) {
+      double least = 1e300;
+      for (int rep = 0; rep < 2 && run.running() > 0; ++rep) {
+        int32_t r = run.restart(entries_now.data(), static_cast<int32_t>(entries_now.size()), most);
+        if (r == PLAS_OK) r = run.prepare();
+        if (r != PLAS_OK) return r;
+        const double from = ms_since(t0);
+        r = run.chunk();
+        if (r != PLAS_OK) return r;
+        least = std::min(least, ms_since(t0) - from);
+      }
+      *ms += least;
+    }
+    return PLAS_OK;
+  };
+  std::vector<bool> staged(buckets.size(), false);
+  for (size_t b = 0; b < buckets.size(); ++b) {
+    plas_tune_entry& e = best[b];
+    e.side_lo = static_cast<int32_t>(std::ceil(std::pow(2.0, buckets[b] / 2.0)));
+    e.side_hi = static_cast<int32_t>(std::ceil(std::pow(2.0, (buckets[b] + 1) / 2.0))) - 1;
+    e.blur_waves_per_block = kDefaultWavesPerBlock;
+    for (int32_t i = 0; i < count; ++i) {
+      const int32_t side = items[i].side;
+      if (side_bucket(std::max(2, side)) != buckets[b]) continue;
+      // Sides exactly on a bucket edge: make sure the range holds them.
+      e.side_lo = std::min(e.side_lo, side);
+      e.side_hi = std::max(e.side_hi, side);
+      staged[b] = staged[b] || plas::staged_blur(padded_channels(items[i].d), items[i].storage);
+    }
+  }
+  double best_ms = 0.0;
+  for (int rep = 0; rep < 2; ++rep) {  // the first loads the kernels
+    st = measure(best, &best_ms);
+    if (st != PLAS_OK) return st;
+  }
+  // Keeps the entries of `cand` if they are faster by more than measurements
+  // differ, twice, with the present best timed in between. A sort of very few
+  // levels may end on the way: then the times do not compare, and the present
+  // best is timed again without it.
+  auto consider = [&](const std::vector<plas_tune_entry>& cand) -> int32_t {
+    const int before = run.running();
+    double ms = 0.0;
+    for (int rep = 0; rep < 2 && run.running() > 0; ++rep) {
+      int32_t r = measure(cand, &ms);
+      if (r != PLAS_OK) return r;
+      const bool faster = ms < best_ms * kTuneGain;
+      if (run.running() == before && !faster) return PLAS_OK;
+      if (run.running() == before && rep == 1) break;
+      r = measure(best, &best_ms);
+      if (r != PLAS_OK) return r;
+      if (run.running() != before || !(ms < best_ms * kTuneGain)) return PLAS_OK;
+    }
+    if (run.running() == before && before > 0) {
+      best_ms = ms;
+      best = cand;
+    }
+    return PLAS_OK;
+  };
+  for (size_t b = 0; b < buckets.size(); ++b) {
+    for (const int wpb : {1, 2, 4}) {
+      if (!staged[b] || wpb == kDefaultWavesPerBlock) continue;
+      std::vector<plas_tune_entry> cand = best;
+      cand[b].blur_waves_per_block = wpb;
+      st = consider(cand);
+      if (st != PLAS_OK) return st;
+    }
+    for (const int blocks : {256, 1024, 16384}) {
+      std::vector<plas_tune_entry> cand = best;
+      cand[b].assign_blocks = blocks;
+      st = consider(cand);
+      if (st != PLAS_OK) return st;
+    }
+  }
+  for (const plas_tune_entry& e : best) table[(*entries)++] = e;
   return PLAS_OK;
 }
 
@@ -833,14 +913,6 @@ struct Job {
   int64_t footprint;
   double submit_ms;
 };
-
-int64_t job_footprint(int32_t side, int32_t d, int32_t storage, const plas_sort_params& prm) {
-  std::vector<LevelInfo> levels;
-  if (build_schedule(side, prm.radius_decay, prm.min_block, prm.start_radius, &levels) != PLAS_OK) return -1;
-  int64_t max_cells = 0;
-  for (const LevelInfo& lv : levels) max_cells = std::max<int64_t>(max_cells, static_cast<int64_t>(lv.beta) * lv.beta);
-  return static_cast<int64_t>(sort_layout(side, padded_channels(d), storage, levels.size(), max_cells).bytes);
-}
 
 }  // namespace
 
