@@ -223,8 +223,14 @@ int32_t plas_grid_energy_noalloc(plas_handle h, const void* features, const int3
  * absolute differences |a - b| between the values of right and down
  * neighbouring cells (no wrap-around) of the arranged grid
  * features[perm] (perm: device int32[n] in gather form, or NULL for the
- * identity), over every channel, computed in float64 in two passes (mean,
- * then mean squared deviation). Lower is smoother. vad: host output.
+ * identity), over every channel, computed in float64: parts of the grid are
+ * taken by their mean and squared deviations from it, and merged. Lower is
+ * smoother. vad: host output. NaN if a value is not finite.
+ * The call arranges the features in one of the handle's working grids, which
+ * it allocates if need be and which the handle keeps (n cells of 4 to 64
+ * channels of the features' type: 268 MB for 1024 x 1024 x 59 float32). On a
+ * device without room for it the features are read where they are, about
+ * 25 times slower.
  */
 int32_t plas_vad(plas_handle h, const void* features, const int32_t* perm, int64_t n, int32_t d,
                  int32_t side, int32_t layout, int32_t dtype, double* vad);

@@ -64,6 +64,12 @@ int32_t plas_stage_assign(plas_handle h, void* grid, const void* target, int32_t
 int32_t plas_stage_energy(plas_handle h, const void* grid, const void* target, int32_t side,
                           int32_t dp, int32_t storage, int32_t scale_shift, uint64_t* energy);
 
+/* plas_vad's way on a device without room for the arranged grid: the
+ * permutation checked, then every value read at its own place, in two passes
+ * (mean, then mean squared deviation). Arguments and result as plas_vad's. */
+int32_t plas_stage_vad_in_place(plas_handle h, const void* features, const int32_t* perm, int64_t n, int32_t d,
+                                int32_t side, int32_t layout, int32_t dtype, double* vad);
+
 /* out[i] = pi(i) for i < n, pi the keyed bijection of [0, n) (the random
  * start arrangement of Sec. 3.1 uses the keys of draw (seed, 0, 0)).
  * out: device int32[n], 1 <= n <= 2^31 - 1. */

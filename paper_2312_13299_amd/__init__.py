@@ -45,7 +45,7 @@ EXPORTS = (
     "plas_set_stream", "plas_sort", "plas_grid_energy", "plas_grid_energy_noalloc", "plas_status_string",
     "plas_last_error",
     "plas_vad", "plas_stage_blur", "plas_stage_group_table", "plas_stage_assign", "plas_stage_energy",
-    "plas_stage_bijection", "plas_philox4x64_10", "plas_draw", "plas_schedule",
+    "plas_stage_vad_in_place", "plas_stage_bijection", "plas_philox4x64_10", "plas_draw", "plas_schedule",
     "plas_scale_shift_from_ranges",
     "plas_batch_config_init", "plas_sort_batch", "plas_autotune_batch",
     "plas_job_footprint", "plas_server_create", "plas_server_submit", "plas_server_step",
@@ -214,6 +214,7 @@ def library() -> ctypes.CDLL:
         "plas_grid_energy_noalloc": (i32, [vp, vp, vp, i64, i32, i32, i32, i32, i32, i32, u64p, i32p,
                                            ctypes.POINTER(ctypes.c_double)]),
         "plas_vad": (i32, [vp, vp, vp, i64, i32, i32, i32, i32, ctypes.POINTER(ctypes.c_double)]),
+        "plas_stage_vad_in_place": (i32, [vp, vp, vp, i64, i32, i32, i32, i32, ctypes.POINTER(ctypes.c_double)]),
         "plas_status_string": (ctypes.c_char_p, [i32]),
         "plas_last_error": (ctypes.c_char_p, [vp]),
         "plas_stage_blur": (i32, [vp, vp, vp, i32, i32, i32, i32]),
@@ -504,6 +505,9 @@ class Context:
 
     def vad(self, features, perm=None, side: int | None = None, layout: str = "cn") -> float:
         """VAD (App. C) of features[perm] on the side x side grid."""
+        return self._vad("plas_vad", features, perm, side, layout)
+
+    def _vad(self, name, features, perm, side, layout) -> float:
         import torch
         dtype = _feature_dtype(features)
         if layout == "cn":
@@ -520,9 +524,9 @@ class Context:
             p = ctypes.c_void_p(perm.data_ptr())
         v = ctypes.c_double()
         self._bind_stream()
-        st = library().plas_vad(self._h, ctypes.c_void_p(features.data_ptr()), p, n, d, side, lay, dtype,
-                                ctypes.byref(v))
-        self._check(st, "plas_vad")
+        st = getattr(library(), name)(self._h, ctypes.c_void_p(features.data_ptr()), p, n, d, side, lay, dtype,
+                                      ctypes.byref(v))
+        self._check(st, name)
         return v.value
 
     # ---- stages (working layout [n][dp] float32)
@@ -576,6 +580,10 @@ class Context:
                                                 grid.shape[1], storage, scale_shift, ctypes.byref(E)),
                     "plas_stage_energy")
         return int(E.value)
+
+    def stage_vad_in_place(self, features, perm=None, side: int | None = None, layout: str = "cn") -> float:
+        """vad() as a device without room for an arranged grid computes it."""
+        return self._vad("plas_stage_vad_in_place", features, perm, side, layout)
 
     def stage_bijection(self, n: int, round_keys):
         import torch

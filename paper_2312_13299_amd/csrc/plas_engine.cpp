@@ -400,8 +400,10 @@ int32_t plas_grid_energy_noalloc(plas_handle h, const void* features, const int3
                       energy_mean);
 }
 
-int32_t plas_vad(plas_handle h, const void* features, const int32_t* perm, int64_t n, int32_t d, int32_t side,
-                 int32_t layout, int32_t dtype, double* vad) {
+// A VAD over an arranged grid, or (in_place, or no room for the grid) over the
+// features where they are.
+static int32_t query_vad(plas_handle h, const void* features, const int32_t* perm, int64_t n, int32_t d, int32_t side,
+                         int32_t layout, int32_t dtype, double* vad, bool in_place) {
   int32_t st = check_features(h, features, n, d, side, layout, dtype);
   if (st != PLAS_OK) return st;
   h->error.clear();
@@ -414,18 +416,18 @@ int32_t plas_vad(plas_handle h, const void* features, const int32_t* perm, int64
   PLAS_HIP(h, reserve(h->vad, plas::vad_partial_doubles() * sizeof(double)));
   st = reserve_query(h, dp);
   if (st != PLAS_OK) return st;
-  const IngestPlan plan{nullptr, as<int32_t>(h->grid_h), as<float>(h->range_part), as<plas::QueryOut>(h->query)};
-  // In arranged order if a grid fits beside the features, else where they are.
-  const bool grid = reserve(h->grid_g, static_cast<size_t>(n) * dp * storage_bytes(storage)) == hipSuccess;
-  if (grid) {
-    IngestPlan arranged = plan;
-    arranged.G = h->grid_g.ptr;
-    st = queue_arranged(h, features, dtype, n, d, side, layout, dp, storage, perm, arranged, nullptr);
+  IngestPlan plan{nullptr, as<int32_t>(h->grid_h), as<float>(h->range_part), as<plas::QueryOut>(h->query)};
+  if (!in_place) {
+    if (reserve(h->grid_g, static_cast<size_t>(n) * dp * storage_bytes(storage)) == hipSuccess)
+      plan.G = h->grid_g.ptr;
+    else
+      (void)hipGetLastError();  // the failed allocation's
+  }
+  if (plan.G != nullptr) {
+    st = queue_arranged(h, features, dtype, n, d, side, layout, dp, storage, perm, plan, nullptr);
     if (st != PLAS_OK) return st;
-    PLAS_HIP(h, plas::launch_vad_grid(arranged.G, d, side, dp, storage, as<double>(h->vad), &plan.out->vad[1],
-                                      h->stream));
+    PLAS_HIP(h, plas::launch_vad_grid(plan.G, d, side, dp, storage, as<double>(h->vad), &plan.out->vad[1], h->stream));
   } else {
-    (void)hipGetLastError();  // the failed allocation's
     if (perm != nullptr) {
       PLAS_HIP(h, plas::launch_check_perm(perm, n, plan.inv, plan.out, h->stream));
       st = read_query(h, plan.out, false);
@@ -440,6 +442,11 @@ int32_t plas_vad(plas_handle h, const void* features, const int32_t* perm, int64
   if (st != PLAS_OK) return st;
   *vad = h->query_host->vad[1];
   return PLAS_OK;
+}
+
+int32_t plas_vad(plas_handle h, const void* features, const int32_t* perm, int64_t n, int32_t d, int32_t side,
+                 int32_t layout, int32_t dtype, double* vad) {
+  return query_vad(h, features, perm, n, d, side, layout, dtype, vad, false);
 }
 
 // ------------------------------------------------------------------ stages
@@ -542,6 +549,11 @@ int32_t plas_stage_energy(plas_handle h, const void* grid, const void* target, i
   PLAS_HIP(h, hipStreamSynchronize(h->stream));
   if (energy) *energy = h->u64_host[0];
   return PLAS_OK;
+}
+
+int32_t plas_stage_vad_in_place(plas_handle h, const void* features, const int32_t* perm, int64_t n, int32_t d,
+                                int32_t side, int32_t layout, int32_t dtype, double* vad) {
+  return query_vad(h, features, perm, n, d, side, layout, dtype, vad, true);
 }
 
 int32_t plas_stage_bijection(plas_handle h, int64_t n, const uint64_t round_keys[4], int32_t* out) {
