@@ -1031,7 +1031,8 @@ __device__ __forceinline__ void blur_relay_lines(const S* __restrict__ in, S* __
 }
 
 // Waves per SIMD of a relay kernel: what its LDS lets share a CU (four
-// float32 groups; six bfloat16 groups, or one block of four).
+// float32 groups; six bfloat16 groups, or one block of four). At five the
+// bfloat16 kernels spill five to seven registers, outside the steps.
 template <typename S, int GPB>
 constexpr int relay_waves_per_eu() {
   return sizeof(S) == 4 || GPB == 4 ? 3 : 5;
@@ -2043,7 +2044,9 @@ __device__ void reorder_done(DevState* __restrict__ st, const LevelInfo* __restr
                              plas_level_out* __restrict__ trace, uint32_t nblocks);
 
 // Waves per SIMD the assignment kernels keep room for in registers: more do
-// not help (see assign_blocks_cap), and with four some lane layouts spill.
+// not help (see assign_blocks_cap), and with four many lane layouts spill. At
+// three those of two lanes per item do, by four to eight registers (16
+// bfloat16 channels, and in batches 8 float32 ones).
 constexpr int kAssignWavesPerEu = 3;
 
 template <int DP, typename S>
