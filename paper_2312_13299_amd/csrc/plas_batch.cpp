@@ -441,14 +441,15 @@ class BatchRun {
   int32_t ring_widths() const {
     int32_t widths = 0;
     for (int dp = 16; dp <= 64 && large_; dp *= 2) {
-      int64_t groups = 0, gain = 0;
+      int64_t groups = 0, cells = 0, gain = 0;
       for (int slot : run_list_) {
         const Sort& s = sorts_[slot];
         if (s.dp != dp || s.storage != plas::kStorageF32) continue;
         groups += plas::blur_groups(s.w, s.dp);
+        cells += s.n;
         gain += plas::batch_ring_gain(s.w, s.dp, s.r);
       }
-      if (plas::batch_ring(groups, gain)) widths |= dp;
+      if (plas::batch_ring(groups, cells, cells * dp * 4, gain)) widths |= dp;
     }
     return widths;
   }

@@ -2934,25 +2934,38 @@ int64_t blur_groups(int w, int dp) { return (static_cast<int64_t>(w) * dp + 63) 
 // in turn, so many short lines run slower in it. Reorders, us, relay and ring
 // for all grids:
 //  - 32 <= r <= 192: four grids of 1024^2 x 64 1475 / 1210 at r = 40 and 1490 /
-//    1264 at 190, two of 1448^2 1534 / 1256 and 1536 / 1314, six of 724^2 1118 /
+//    1264 at 190, two of 1448^2 1532 / 1256 and 1536 / 1313, six of 724^2 1118 /
 //    975 and 1108 / 1091, two of 3600^2 x 16 2791 / 2232 and 3145 / 2573, eight
 //    of 300^2 to 724^2 x 64 794 / 702 and (140) 801 / 788; not where windows
 //    are a good part of the line (32 of 256^2 x 64 683 / 707 at r = 100);
 //  - below, 1024^2 1240 / 1201 at r = 3, 1448^2 1280 / 1244, 900^2 967 / 958,
-//    but 800^2 757 / 796, 300^2 to 724^2 663 / 683;
-//  - above, nothing (1024^2 1471 / 1466 at r = 300).
+//    but 800^2 757 / 796, 300^2 to 724^2 663 / 683, 2091^2 x 16 814 / 952;
+//  - above, little (1024^2 1471 / 1466 at r = 300, 1448^2 1537 / 1523).
 // Two launches instead of one cost more than either (300^2 to 1024^2 at r =
 // 40: ring for all 888, for the three largest 944, for none 1065), so a batch
-// decides for all its grids of a width at once, by these gains times cells.
-// Cells of 16 channels and less have too few lines below 769 groups (2091^2 x
-// 16 814 / 952), and a launch of fewer than 769 groups leaves SIMDs idle.
+// decides for all its grids of a width at once, by these gains (in percent of
+// a reorder) times cells.
 int64_t batch_ring_gain(int w, int dp, int r) {
   const int64_t groups = blur_groups(w, dp), cells = static_cast<int64_t>(w) * w;
-  if (dp < 32 && groups < kRingMinGroups) return r < 32 ? -4 * cells : 0;
-  if (r < 32) return groups > 896 ? cells : -cells;
-  return r <= 192 && 3 * r <= w ? 4 * cells : 0;
+  if (dp < 32 && groups < kRingMinGroups) return r < 32 ? -16 * cells : 0;
+  if (r < 32) return groups > 896 ? 4 * cells : -4 * cells;
+  return r <= 192 && 3 * r <= w ? 16 * cells : 0;
 }
-bool batch_ring(int64_t groups, int64_t gain) { return groups >= kRingMinGroups && gain > 0; }
+
+// Fewer than 769 groups leave SIMDs idle. The chip takes 1024 at once, and a
+// last round that is partly idle costs its share of about a third of the time
+// (one grid of n^2 x 64, relay and ring, us, r = 3 and r = 40: 1024 294 / 282
+// and 354 / 288, 1280 490 / 547 and 599 / 552, 1448 627 / 652 and 754 / 656,
+// 1800 1007 / 970 and 1219 / 986). Where the cache holds the relay's second
+// read, only whole rounds are worth it (whole batches, ms: 900^2 and 400^2,
+// 1300 groups, 112.5 / 115.5; two of 740^2 125.9 / 126.8; four of 512^2, 2048
+// groups, 110.2 / 107.7).
+bool batch_ring(int64_t groups, int64_t cells, int64_t bytes, int64_t gain) {
+  if (groups < kRingMinGroups) return false;
+  const int64_t slots = (groups + kRingMaxGroups - 1) / kRingMaxGroups * kRingMaxGroups;
+  if (slots == 2 * kRingMaxGroups && groups < slots && 2 * bytes <= 3 * kInfinityCacheBytes) return false;
+  return gain * slots > 32 * (slots - groups) * cells;
+}
 
 int batch_blur_blocks(int w, int dp, int storage, int groups_per_block, int64_t max_cells) {
   int64_t blocks = 0, threads = 0;

@@ -115,11 +115,11 @@ bool blur_large_working_set(int64_t working_bytes);
 // Groups of 64 / dp lines of a pass.
 int64_t blur_groups(int w, int dp);
 // What the ring kernel gains (or, negative, costs) a float32 grid of a batch at
-// radius r, in shares of the pass times cells; and whether the grids of one
+// radius r, in percent of a reorder times cells; and whether the grids of one
 // width (16 channels or more) of a large working set take it, from the sums of
-// their groups and gains.
+// their groups, cells, bytes and gains.
 int64_t batch_ring_gain(int w, int dp, int r);
-bool batch_ring(int64_t groups, int64_t gain);
+bool batch_ring(int64_t groups, int64_t cells, int64_t bytes, int64_t gain);
 // groups_per_block of blur launches: 1, 2 or 4 line groups per block of the
 // relay kernel, or kBatchRing for the ring kernel.
 constexpr int kBatchRing = -1;

@@ -1,7 +1,8 @@
 """GPU parity of batches whose blur changes kernels as the radii fall: float32
-grids of a large working set take the ring kernel at radii 32 to 192 and the
-relay kernel above and (up to 896 line groups) below. Every sort equals the
-same sort run alone, which takes kernels of its own choice, bit for bit."""
+grids of a large working set whose line groups fill the chip take the ring
+kernel at radii 32 to 192 and the relay kernel above and (up to 896 line
+groups each) below. Every sort equals the same sort run alone, which takes
+kernels of its own choice, bit for bit."""
 import numpy as np
 import pytest
 
@@ -26,11 +27,11 @@ def _features(torch, side, d, seed):
 CASES = [
     # Radii 230, 138, .., 1: relay, ring, relay. Both storages, an odd side out.
     ([905, 800, 701], [59, 59, 59], ["f32"] * 3, 230.0),
-    ([905, 801, 300, 512], [59, 59, 3, 59], ["f32", "bf16", "f32", "f32"], 100.0),
-    # More than 896 groups: the ring below r = 32, too.
-    ([1030, 1031], [64, 59], ["f32"] * 2, 40.0),
+    ([905, 801, 300, 512, 700], [59, 59, 3, 59, 59], ["f32", "bf16", "f32", "f32", "f32"], 100.0),
+    # Two rounds of more than 896 groups each: the ring below r = 32, too.
+    ([1020, 1021], [64, 59], ["f32"] * 2, 40.0),
     # Two lines per group, and four; ragged last groups.
-    ([1541, 641], [31, 17], ["f32"] * 2, 100.0),
+    ([1541, 1301], [31, 17], ["f32"] * 2, 100.0),
     ([3077], [14], ["f32"], 70.0),
 ]
 
