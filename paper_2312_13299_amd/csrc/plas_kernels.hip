@@ -586,8 +586,9 @@ __device__ __forceinline__ void store_quad(float* p, const float4& v) {
 // in turn took 135 cycles per position, waiting for its own LDS round trips:
 // 512^2 x 4 float32 33 -> 12 us per pass (r = 1; 42 -> 22 us at r = 255), 700^2
 // x 16 float32 45 -> 18 us, 300^2 x 64 float32 23 -> 12 us, 724^2 x 64 bfloat16
-// 57 -> 26 us, 2091^2 x 64 float32 641 -> 455 us (r = 20). Two waves (the sums
-// stored by the summing wave) reached 15 us on the first of these.
+// 57 -> 26 us, 2091^2 x 64 float32 641 -> 455 us (r = 20; with streaming
+// stores about 430). Two waves (the sums stored by the summing wave) reached 15
+// us on the first of these.
 //
 // Steps walk t = 0 .. w - 1 + r. Every t < w adds value t to the sum (up to t
 // = r that is the starting sum, from then on the entering value of output
