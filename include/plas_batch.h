@@ -116,8 +116,8 @@ int32_t plas_sort_batch(plas_handle h, const plas_batch_item* items, int32_t cou
  * each bucket, each other blur shape (1, 2, 4 summing waves per block, grids
  * with cells of 16 bytes or more) and then each other assignment block count
  * (the library's choice, 256, 1024, 16384) is timed in the whole batch (all
- * items running, those left out that do not fit the device together; 6
- * reorders at the first, coarsest level and 6 at radius 15) and taken if the
+ * items running, those left out that do not fit the device together; 4
+ * reorders at the first, coarsest level and 4 at radius 15) and taken if the
  * batch runs faster by more than measurements differ. graph: as in
  * plas_batch_config. table: host array of cap entries; *entries receives the
  * number written. The items' perm_out contents may be overwritten.

@@ -344,26 +344,31 @@ class BatchRun {
 
   // Sends every running sort back to the start of its first level with radius
   // `most` or less (of its last level, if none has), on the arrangement it has
-  // by now, under another tuning table (for measurements: no sort's result).
-  int32_t restart(const plas_tune_entry* tune, int32_t tune_count, int32_t most) {
-    cfg_.tune = tune;
-    cfg_.tune_count = tune_count;
-    for (Sort& s : sorts_) {
+  // by now, under another tuning table (NULL: the same, at the same radii) and
+  // with its plan made. For measurements: no sort's result.
+  int32_t restart(const std::vector<plas_tune_entry>* tune, int32_t most) {
+    if (tune != nullptr) {
+      cfg_.tune = tune->data();
+      cfg_.tune_count = static_cast<int32_t>(tune->size());
+      dirty_ = true;
+    }
+    std::vector<DevState> at(sorts_.size());
+    for (size_t i = 0; i < sorts_.size(); ++i) {
+      Sort& s = sorts_[i];
       if (!s.running) continue;
       const int32_t st = apply_tuning(s);
       if (st != PLAS_OK) return st;
       size_t level = 0;
       while (level + 1 < s.levels.size() && s.levels[level].r > most) ++level;
-      DevState at = s.start;
-      fill_state_for_level(&at, s.levels[level]);
-      at.level = static_cast<int32_t>(level);
-      PLAS_HIP(h_, hipMemcpyAsync(s.grid.state, &at, sizeof(DevState), hipMemcpyHostToDevice, b_->stream));
-      PLAS_HIP(h_, hipStreamSynchronize(b_->stream));
+      at[i] = s.start;
+      fill_state_for_level(&at[i], s.levels[level]);
+      at[i].level = static_cast<int32_t>(level);
+      PLAS_HIP(h_, hipMemcpyAsync(s.grid.state, &at[i], sizeof(DevState), hipMemcpyHostToDevice, b_->stream));
       s.slots = 0;
-      s.r = at.r;
+      s.r = at[i].r;
     }
-    dirty_ = true;
-    return PLAS_OK;
+    PLAS_HIP(h_, hipStreamSynchronize(b_->stream));
+    return prepare();
   }
 
   // Queue one chunk of reorders for every running sort and read their
@@ -792,7 +797,7 @@ int32_t plas_autotune_batch(plas_handle h, const plas_batch_item* items, int32_t
 
   // A shape is worth what it does to the launches that it runs in, which hold
   // every sort of the batch, so each candidate is timed with all of them
-  // running: six reorders at the first, coarsest level and six at radius 15
+  // running: four reorders at the first, coarsest level and four at radius 15
   // (the finest block size). Sorts that would not fit the device together are
   // left out.
   const auto t0 = std::chrono::steady_clock::now();
@@ -800,7 +805,7 @@ int32_t plas_autotune_batch(plas_handle h, const plas_batch_item* items, int32_t
   plas_batch_config cfg;
   plas_batch_config_init(&cfg);
   cfg.graph = graph;
-  cfg.reorders_per_sync = 6;
+  cfg.reorders_per_sync = 4;
   size_t free_bytes = 0, total_bytes = 0;
   PLAS_HIP(h, hipStreamSynchronize(h->stream));
   PLAS_HIP(h, hipMemGetInfo(&free_bytes, &total_bytes));
@@ -828,8 +833,7 @@ int32_t plas_autotune_batch(plas_handle h, const plas_batch_item* items, int32_t
     for (const int32_t most : {INT32_MAX, 15}) {
       double least = 1e300;
       for (int rep = 0; rep < 2 && run.running() > 0; ++rep) {
-        int32_t r = run.restart(entries_now.data(), static_cast<int32_t>(entries_now.size()), most);
-        if (r == PLAS_OK) r = run.prepare();
+        int32_t r = run.restart(rep == 0 ? &entries_now : nullptr, most);
         if (r != PLAS_OK) return r;
         const double from = ms_since(t0);
         r = run.chunk();
